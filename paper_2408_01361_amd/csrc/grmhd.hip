@@ -353,6 +353,17 @@ __device__ __forceinline__ void recon_pair(const double* __restrict__ P, long nz
   }
 }
 
+// sqrt(-g) ((FL + FR)/2 - cmax (UR - UL)/2) from the sum of the fluxes and the
+// jump of the conserved variables (FP64: the factors sqrt(-g)/2 and
+// sqrt(-g) cmax/2 are the same for every component).
+__device__ __forceinline__ double llf_dens(double gdet, double cmax, double fsum, double jump) {
+  const double h = 0.5 * gdet;
+  return fma(-(h * cmax), jump, h * fsum);
+}
+__device__ __forceinline__ float llf_dens(float gdet, float cmax, float fsum, float jump) {
+  return gdet * fmaf(-0.5f * cmax, jump, 0.5f * fsum);
+}
+
 // Local Lax-Friedrichs flux of one face from its left and right states qL,
 // qR, with the face metric at table position q2; stored at padded index c.
 template <int D, typename R, typename FT>
@@ -362,18 +373,15 @@ __device__ __forceinline__ void face_llf(const Dev& g, const R qL[NVAR], const R
   FaceMetric<R> m;
   load_face_metric<R>(tab, g.plane, q2, m);
   const R gam = (R)g.gam;
-  R FL[NVAR], UL[NVAR], cpl, cml;
-  face_side<D, R>(qL, m, gam, FL, UL, cpl, cml);
-  R FR[NVAR], UR[NVAR], cpr, cmr;
-  face_side<D, R>(qR, m, gam, FR, UR, cpr, cmr);
-  R cmax = fmax(fmax(cpl, cpr), fmax(-cml, -cmr));
-  cmax = fmax(cmax, (R)0);
+  R FL[NVAR], UL[NVAR], FR[NVAR], UR[NVAR];
+  const R cl = face_side<D, R>(qL, m, gam, FL, UL);
+  const R cr = face_side<D, R>(qR, m, gam, FR, UR);
+  const R cmax = fmax(fmax(cl, cr), (R)0);
   // the normal field component's flux is not stored: Flux-CT replaces it by
   // zero and nothing reads it
 #pragma unroll
   for (int v = 0; v < NVAR; v++)
-    if (v != B1 + D - 1)
-      F[v * g.nz + c] = (FT)(m.gdet * fma((R)-0.5 * cmax, UR[v] - UL[v], (R)0.5 * (FL[v] + FR[v])));
+    if (v != B1 + D - 1) F[v * g.nz + c] = (FT)llf_dens(m.gdet, cmax, FL[v] + FR[v], UR[v] - UL[v]);
 }
 
 template <int D>

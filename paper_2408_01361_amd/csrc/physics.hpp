@@ -139,90 +139,105 @@ using fdual::llf;
 
 // WENO5 (Jiang-Shu weights d_k / (eps + beta_k)^2, d = (1, 6, 3)/10) from
 // point values a..e of zones c-2..c+2: the value at the right edge of zone c.
-// The smoothness indicator of each three-zone stencil is formed by an
-// expression that is symmetric under reversing the stencil -- (x + z) - 2y,
-// fma(-4, y, fma(3, centre, outer)), y - z squared -- so a zone's left-edge
-// value, weno5(e, d, c, b, a), reuses its right edge's indicators and
-// weight products bit for bit (weno5_pair).  Arranged for few operations:
-// every indicator is scaled by 12 (12 beta_k = 13 t_k^2 + 3 u_k^2, with
-// 12 eps), which leaves the weights unchanged; the factors 1/10 of d and 1/6
-// of the candidate polynomials cancel or move into the single quotient that
-// normalises the weights over a common denominator.
+// The FP64 form works on the four differences of the stencil: the second
+// differences t_k and one-sided slopes u_k of the smoothness indicators and
+// the candidates' offsets from c are short sums of them, and the edge value
+// is c plus the weighted offset, so only that offset goes through the
+// normalising quotient.  Reversing the stencil negates and swaps the
+// differences exactly, so a zone's left-edge value, weno5(e, d, c, b, a),
+// reuses its right edge's indicators and weight products bit for bit
+// (weno5_pair).  Arranged for few operations: every indicator is scaled by 4
+// (4 beta_k = (13/3) t_k^2 + u_k^2, with 4 eps), which leaves the weights
+// unchanged; the factors 1/10 of d and 1/6 of the candidate polynomials
+// cancel or move into the final fused multiply-add.  58 FP64 operations and
+// two hardware reciprocals per edge pair, against 75 for the form on the
+// zone values.
 //
 // FP64: only the fused multiply-adds written out (contraction off), so an
 // evaluation rounds the same way in whatever code it is inlined; the
-// normalising quotient comes from the hardware reciprocal refined by Newton
-// steps (within about an ulp of the correctly rounded quotient; the weights'
-// denominator is a sum of positive normal numbers for weno_eps >= 1e-36).
+// normalising quotient comes from the hardware reciprocal (relative error
+// below 2^-23) with the two leading terms of its error series (within about
+// an ulp of the offset; the weights' denominator is a sum of positive normal
+// numbers for weno_eps >= 1e-36).
 #pragma clang fp contract(off)
 namespace wd {
 typedef double R;
+// n / d: with e = 1 - d r of the hardware estimate r, 1/d = r (1 + e + e^2 + ..)
 __device__ __forceinline__ R qdiv(R n, R d) {
-  R r = __builtin_amdgcn_rcp(d);
-  r = fma(fma(-d, r, (R)1), r, r);
-  r = fma(fma(-d, r, (R)1), r, r);
+  const R r = __builtin_amdgcn_rcp(d);
+  const R e = fma(-d, r, (R)1);
   const R q = n * r;
-  return fma(fma(-d, q, n), r, q);
+  return fma(q, fma(e, e, e), q);
 }
-// 12 (eps + beta) of the stencils (a, b, c), (b, c, d), (c, d, e)
-__device__ __forceinline__ void indicators12(R a, R b, R c, R d, R e, R eps, R& s0, R& s1, R& s2) {
-  const R eps12 = (R)12 * eps;
-  R t0 = fma((R)-2, b, a + c), u0 = fma((R)-4, b, fma((R)3, c, a));
-  R t1 = fma((R)-2, c, b + d), u1 = b - d;
-  R t2 = fma((R)-2, d, c + e), u2 = fma((R)-4, d, fma((R)3, c, e));
-  s0 = fma((R)13 * t0, t0, fma((R)3 * u0, u0, eps12));
-  s1 = fma((R)13 * t1, t1, fma((R)3 * u1, u1, eps12));
-  s2 = fma((R)13 * t2, t2, fma((R)3 * u2, u2, eps12));
+// Differences of the stencil and 4 (eps + beta) of (a, b, c), (b, c, d),
+// (c, d, e).
+struct Stencil5 {
+  R d1, d2, d3, d4, s0, s1, s2;
+};
+__device__ __forceinline__ Stencil5 stencil5(R a, R b, R c, R d, R e, R eps) {
+  Stencil5 z;
+  const R eps4 = (R)4 * eps, k = (R)(13.0 / 3.0);
+  z.d1 = b - a;
+  z.d2 = c - b;
+  z.d3 = d - c;
+  z.d4 = e - d;
+  const R t0 = z.d2 - z.d1, u0 = fma((R)3, z.d2, -z.d1);
+  const R t1 = z.d3 - z.d2, u1 = z.d2 + z.d3;
+  const R t2 = z.d4 - z.d3, u2 = fma((R)3, z.d3, -z.d4);
+  z.s0 = fma(k * t0, t0, fma(u0, u0, eps4));
+  z.s1 = fma(k * t1, t1, fma(u1, u1, eps4));
+  z.s2 = fma(k * t2, t2, fma(u2, u2, eps4));
+  return z;
 }
-// (eps + beta)^2 of the three stencils, scaled by 144
-__device__ __forceinline__ void indicators(R a, R b, R c, R d, R e, R eps, R& s0, R& s1, R& s2) {
-  indicators12(a, b, c, d, e, eps, s0, s1, s2);
-  s0 *= s0;
-  s1 *= s1;
-  s2 *= s2;
+// c + offset / 6 of the candidates' offsets (5 d2 - 2 d1, d2 + 2 d3,
+// 4 d3 - d4) with weights w0, c6, 3 w2 over their sum (c6 = 6 times the middle
+// product)
+__device__ __forceinline__ R combine(R c, R d1, R d2, R d3, R d4, R w0, R c6, R w2) {
+  const R p0 = fma((R)5, d2, (R)-2 * d1);
+  const R p1 = fma((R)2, d3, d2);
+  const R p2 = fma((R)4, d3, -d4);
+  const R v2 = (R)3 * w2;
+  return fma((R)(1.0 / 6.0), qdiv(fma(w0, p0, fma(c6, p1, v2 * p2)), (w0 + c6) + v2), c);
 }
-// weighted value with weight products w0 = s1 s2, w1 = 6 s0 s2, w2 = 3 s0 s1
-__device__ __forceinline__ R combine(R a, R b, R c, R d, R e, R s12, R s02, R s01) {
-  R p0 = fma((R)11, c, fma((R)-7, b, (R)2 * a));
-  R p1 = fma((R)2, d, fma((R)5, c, -b));
-  R p2 = fma((R)5, d, fma((R)2, c, -e));
-  R w0 = s12, w1 = (R)6 * s02, w2 = (R)3 * s01;
-  return qdiv(fma(w0, p0, fma(w1, p1, w2 * p2)), (R)6 * ((w0 + w1) + w2));
+// Right and left edge from the weight products w0 = s1 s2, w1 = s0 s2,
+// w2 = s0 s1 (of squared indicators).
+__device__ __forceinline__ R right_edge(const Stencil5& z, R c, R w0, R w1, R w2) {
+  return combine(c, z.d1, z.d2, z.d3, z.d4, w0, (R)6 * w1, w2);
+}
+__device__ __forceinline__ R left_edge(const Stencil5& z, R c, R w0, R w1, R w2) {
+  return combine(c, -z.d4, -z.d3, -z.d2, -z.d1, w2, (R)6 * w1, w0);
 }
 }  // namespace wd
 
 __device__ __forceinline__ double weno5(double a, double b, double c, double d, double e, double eps) {
-  double s0, s1, s2;
-  wd::indicators(a, b, c, d, e, eps, s0, s1, s2);
-  return wd::combine(a, b, c, d, e, s1 * s2, s0 * s2, s0 * s1);
+  const wd::Stencil5 z = wd::stencil5(a, b, c, d, e, eps);
+  const double q0 = z.s0 * z.s0, q1 = z.s1 * z.s1, q2 = z.s2 * z.s2;
+  return wd::right_edge(z, c, q1 * q2, q0 * q2, q0 * q1);
 }
 
 // Both edges of zone c: left = weno5(e, d, c, b, a), right = weno5(a, b, c,
 // d, e), from one set of indicators (reversing the stencil swaps s0 and s2).
 __device__ __forceinline__ void weno5_pair(double a, double b, double c, double d, double e, double eps,
                                            double& left, double& right) {
-  double s0, s1, s2;
-  wd::indicators(a, b, c, d, e, eps, s0, s1, s2);
-  const double s12 = s1 * s2, s02 = s0 * s2, s01 = s0 * s1;
-  right = wd::combine(a, b, c, d, e, s12, s02, s01);
-  left = wd::combine(e, d, c, b, a, s01, s02, s12);
+  const wd::Stencil5 z = wd::stencil5(a, b, c, d, e, eps);
+  const double q0 = z.s0 * z.s0, q1 = z.s1 * z.s1, q2 = z.s2 * z.s2;
+  const double w0 = q1 * q2, w1 = q0 * q2, w2 = q0 * q1;
+  right = wd::right_edge(z, c, w0, w1, w2);
+  left = wd::left_edge(z, c, w0, w1, w2);
 }
 
 // WENO-Z (Borges et al. 2008, power 2 as in Castro, Costa & Don 2011): the
 // WENO5 candidates and indicators with weights d_k (1 + (tau5 / (eps +
 // beta_k))^2), tau5 = |beta_0 - beta_2|.  Over the common denominator of the
-// squared indicators s_k = (12 (eps + beta_k))^2 (tau5 scaled by 12 alike,
-// T = (12 tau5)^2) the weight products are d_k (s_k + T) prod_{j != k} s_j,
+// squared indicators s_k = (4 (eps + beta_k))^2 (tau5 scaled by 4 alike,
+// T = (4 tau5)^2) the weight products are d_k (s_k + T) prod_{j != k} s_j,
 // formed like WENO5's; with weno_eps >= 1e-36 they stay normal while
-// 12 (eps + beta) < 1e100, i.e. for differences of primitives below ~1e49.
+// 4 (eps + beta) < 1e100, i.e. for differences of primitives below ~1e49.
 __device__ __forceinline__ double wenoz(double a, double b, double c, double d, double e, double eps) {
-  double s0, s1, s2;
-  wd::indicators12(a, b, c, d, e, eps, s0, s1, s2);
-  const double tau = fabs(s0 - s2), T = tau * tau;
-  s0 *= s0;
-  s1 *= s1;
-  s2 *= s2;
-  return wd::combine(a, b, c, d, e, (s0 + T) * (s1 * s2), (s1 + T) * (s0 * s2), (s2 + T) * (s0 * s1));
+  const wd::Stencil5 z = wd::stencil5(a, b, c, d, e, eps);
+  const double tau = fabs(z.s0 - z.s2), T = tau * tau;
+  const double q0 = z.s0 * z.s0, q1 = z.s1 * z.s1, q2 = z.s2 * z.s2;
+  return wd::right_edge(z, c, (q0 + T) * (q1 * q2), (q1 + T) * (q0 * q2), (q2 + T) * (q0 * q1));
 }
 
 // FP32 forms: contraction into fused multiply-adds allowed.
@@ -427,7 +442,8 @@ __device__ __forceinline__ void mc_right_grad(double l, double c, double r, doub
 // The state on one side of a face as the flux kernels need it: conserved
 // variables U, the flux F^d along the face normal (both without the factor
 // sqrt(-g), which is common to the two sides and applied once to their
-// Lax-Friedrichs combination) and the two fast signal speeds, from the
+// Lax-Friedrichs combination) and the larger of the two fast signal speeds'
+// magnitudes (all the combination reads of them), from the
 // reconstructed prims and the face metric.  The same
 // formulas as fluid_state / prim_to_flux / char_speeds, arranged for the
 // face, where these evaluations dominate the step's arithmetic:
@@ -436,21 +452,52 @@ __device__ __forceinline__ void mc_right_grad(double l, double c, double r, doub
 //     Kerr-Schild coordinates both have g_{2 mu} = g^{2 mu} = 0 for mu != 2
 //     (x2 is orthogonal to the other coordinates), so those table entries,
 //     exactly zero, are never read and their products never formed;
-//   * one reciprocal each of u^t, of w (b^2 + w) (sound and Alfven speeds
-//     together) and of 2A (the two roots) per side, and of the lapse per
-//     face, in place of the eight quotients per side of the written form;
+//   * FP64: the speeds' quadratic times w (b^2 + w), which leaves its roots
+//     unchanged, needs neither the sound nor the Alfven speed: with
+//     n = gam p + b^2 and m = (b^2 + w) - n = rho + gam (2 - gam) u (w = rho +
+//     gam u), c^2 = n / (n + m) exactly and A = m u^t u^t - n g^tt, likewise B
+//     and C.  That leaves one reciprocal (of A) and two square roots per side,
+//     of which the Lorentz factor's gives its reciprocal too;
+//   * the two roots (b +- s)/A (b = -B/2, s >= 0) have the larger magnitude
+//     (|b| + s)/|A|;
 //   * fused multiply-adds, written out (contraction off), so that a face
 //     rounds the same way in every kernel that evaluates it.
-// In FP64 the reciprocals are the hardware estimate refined by two Newton
-// steps; the results differ from the written form by rounding only.
+// In FP64 the reciprocals and square roots are the hardware estimates
+// refined by Newton steps to about an ulp; the results differ from the
+// written form by rounding only.
 #pragma clang fp contract(off)
 
 __device__ __forceinline__ double face_rcp(double x) {
-  double r = __builtin_amdgcn_rcp(x);
-  r = fma(fma(-x, r, 1.0), r, r);
-  return fma(fma(-x, r, 1.0), r, r);
+  const double r = __builtin_amdgcn_rcp(x);
+  const double e = fma(-x, r, 1.0);
+  return fma(r, fma(e, e, e), r);
 }
 __device__ __forceinline__ float face_rcp(float x) { return __builtin_amdgcn_rcpf(x); }
+
+__device__ __forceinline__ double hw_rsqrt(double x) {
+#ifdef __AMDGCN__
+  return __builtin_amdgcn_rsq(x);
+#else
+  return 1.0 / sqrt(x);
+#endif
+}
+// sqrt(x) for normal x > 0 (Goldschmidt from the hardware estimate; about an
+// ulp), and with it h close to 1 / (2 sqrt(x)) (2^-46 relative).
+__device__ __forceinline__ double face_sqrt(double x, double& h) {
+  const double y = hw_rsqrt(x);
+  const double g = x * y;
+  const double k = 0.5 * y;
+  const double r = fma(-k, g, 0.5);
+  const double g1 = fma(g, r, g);
+  h = fma(k, r, k);
+  return fma(fma(-g1, g1, x), h, g1);
+}
+// 2^-e with 2^e <= |x| < 2^(e+1): scales a homogeneous expression without
+// rounding (x normal, below 2^1023).
+__device__ __forceinline__ double unit_scale(double x) {
+  const unsigned hi = (unsigned)(__builtin_bit_cast(unsigned long long, x) >> 32);
+  return __builtin_bit_cast(double, (unsigned long long)(0x7fe00000u - (hi & 0x7ff00000u)) << 32);
+}
 
 template <typename R>
 struct FaceMetric {
@@ -458,6 +505,10 @@ struct FaceMetric {
   R ctt, ct1, ct3, c11, c13, c22, c33;   // contravariant
   R gdet, alpha, ialpha;
 };
+
+// 1 / alpha = -g^tt alpha in FP64 (alpha = (-g^tt)^-1/2).
+__device__ __forceinline__ double inverse_lapse(double alpha, double ctt) { return -ctt * alpha; }
+__device__ __forceinline__ float inverse_lapse(float alpha, float) { return __builtin_amdgcn_rcpf(alpha); }
 
 template <typename R>
 __device__ __forceinline__ void load_face_metric(const double* __restrict__ tab, long plane, long q,
@@ -479,23 +530,75 @@ __device__ __forceinline__ void load_face_metric(const double* __restrict__ tab,
   m.c33 = at(G_CON + sidx(3, 3));
   m.gdet = at(G_DET);
   m.alpha = at(G_ALPHA);
-  m.ialpha = face_rcp(m.alpha);
+  m.ialpha = inverse_lapse(m.alpha, m.ctt);
 }
 
-// U / sqrt(-g), F^D / sqrt(-g) (D = 1..3) and the signal speeds cp >= cm of
-// the prims p.
+// Lorentz factor g = sqrt(x) of x = gamma^2 and alpha / g (FP64, FP32).
+__device__ __forceinline__ double lorentz(double x, double alpha, double& iut) {
+  double h;
+  const double g = face_sqrt(x, h);
+  const double i = h + h;                     // 1/g to 2^-46, then one step
+  iut = alpha * fma(fma(-g, i, 1.0), i, i);
+  return g;
+}
+__device__ __forceinline__ float lorentz(float x, float alpha, float& iut) {
+  const float g = sqrt(x);
+  iut = alpha * __builtin_amdgcn_rcpf(g);
+  return g;
+}
+
+// Larger magnitude of the two fast speeds along D, from the gas pressure pg,
+// b^2, the four-velocity components ut, ud and the metric's g^tt, g^tD, g^DD:
+// roots v of (u^D - v u^t)^2 (1 - c^2) = c^2 (v^2 g^tt - 2 v g^tD + g^DD),
+// c^2 = cs^2 + vA^2 - cs^2 vA^2, cs^2 = gam p / w, vA^2 = b^2 / (b^2 + w),
+// w = rho + gam u.
+__device__ __forceinline__ double fast_speed(double rho, double uu, double pg, double bsq, double gam, double ut,
+                                             double ud, double ctt, double ctd, double cdd) {
+  const double n0 = fma(gam, pg, bsq);
+  const double m0 = fma(gam * (2.0 - gam), uu, rho);
+  const double sc = unit_scale(n0 + m0);
+  const double n = n0 * sc, m = m0 * sc;
+  const double mut = m * ut, mud = m * ud;
+  const double A = fma(mut, ut, -n * ctt);
+  const double b = fma(mut, ud, -n * ctd);
+  const double C = fma(mud, ud, -n * cdd);
+  // a discriminant that is not positive counts as zero (1e-280: its root
+  // vanishes against every speed)
+  const double disc = fma(b, b, -(A * C));
+  double h;
+  const double s = face_sqrt(disc > 1e-280 ? disc : 1e-280, h);
+  return (fabs(b) + s) * fabs(face_rcp(A));
+}
+__device__ __forceinline__ float fast_speed(float rho, float uu, float pg, float bsq, float gam, float ut, float ud,
+                                            float ctt, float ctd, float cdd) {
+  const float we = fmaf(gam, uu, rho);
+  const float sw = bsq + we;
+  const float rr = face_rcp(we * sw);
+  const float cs2 = ((gam * pg) * sw) * rr;
+  const float va2 = (bsq * we) * rr;
+  const float c2 = fmaf(-cs2, va2, cs2 + va2);
+  const float ut2 = ut * ut, udt = ud * ut, ud2 = ud * ud;
+  const float A = fmaf(-c2, ctt + ut2, ut2);
+  const float B = -2.0f * fmaf(-c2, ctd + udt, udt);
+  const float C = fmaf(-c2, cdd + ud2, ud2);
+  float disc = fmaf(B, B, -4.0f * A * C);
+  disc = disc > 0.0f ? disc : 0.0f;
+  return (fabsf(B) + sqrt(disc)) * fabsf(0.5f * face_rcp(A));
+}
+
+// U / sqrt(-g), F^D / sqrt(-g) (D = 1..3) and the larger signal speed
+// magnitude of the prims p.
 template <int D, typename R>
-__device__ __forceinline__ void face_side(const R p[NVAR], const FaceMetric<R>& m, R gam, R F[NVAR],
-                                          R U[NVAR], R& cp, R& cm) {
+__device__ __forceinline__ R face_side(const R p[NVAR], const FaceMetric<R>& m, R gam, R F[NVAR], R U[NVAR]) {
   const R rho = p[RHO], uu = p[UU], v1 = p[U1], v2 = p[U2], v3 = p[U3];
   const R Bc1 = p[B1], Bc2 = p[B2], Bc3 = p[B3];
   // four-velocity: gamma^2 = 1 + g_ij u~i u~j, u^t = gamma / alpha,
   // u^i = u~i - gamma alpha g^{ti}, lowered with the face metric
   const R qsq = fma(m.g11 * v1, v1, fma(m.g22 * v2, v2, fma(m.g33 * v3, v3, (R)2 * (m.g13 * v1) * v3)));
-  const R gamma = sqrt((R)1 + qsq);
+  R iut;
+  const R gamma = lorentz((R)1 + qsq, m.alpha, iut);
   const R ga = gamma * m.alpha;
   const R ut = gamma * m.ialpha;
-  const R iut = m.alpha * face_rcp(gamma);
   const R u1 = fma(-ga, m.ct1, v1), u2 = v2, u3 = fma(-ga, m.ct3, v3);
   const R l0 = fma(m.gtt, ut, fma(m.gt1, u1, m.gt3 * u3));
   const R l1 = fma(m.gt1, ut, fma(m.g11, u1, m.g13 * u3));
@@ -540,27 +643,9 @@ __device__ __forceinline__ void face_side(const R p[NVAR], const FaceMetric<R>& 
     F[B2] = fma(b2, ud, -bd * u2);
     F[B3] = fma(b3, ud, -bd * u3);
   }
-  // fast speeds: roots v of (u^D - v u^t)^2 (1 - c^2) = c^2 (v^2 g^tt - 2 v g^tD + g^DD),
-  // c^2 = cs^2 + vA^2 - cs^2 vA^2, cs^2 = gam p / w, vA^2 = b^2 / (b^2 + w), w = rho + gam u
-  const R we = fma(gam, uu, rho);
-  const R sw = bsq + we;
-  const R rr = face_rcp(we * sw);
-  const R cs2 = ((gam * pg) * sw) * rr;
-  const R va2 = (bsq * we) * rr;
-  const R c2 = fma(-cs2, va2, cs2 + va2);
   const R cdd = D == 1 ? m.c11 : (D == 2 ? m.c22 : m.c33);
   const R ctd = D == 1 ? m.ct1 : (D == 2 ? (R)0 : m.ct3);
-  const R ut2 = ut * ut, udt = ud * ut, ud2 = ud * ud;
-  const R A = fma(-c2, m.ctt + ut2, ut2);
-  const R B = (R)-2 * fma(-c2, ctd + udt, udt);
-  const R C = fma(-c2, cdd + ud2, ud2);
-  R disc = fma(B, B, (R)-4 * A * C);
-  disc = disc > (R)0 ? disc : (R)0;
-  const R sq = sqrt(disc);
-  const R i2a = (R)0.5 * face_rcp(A);
-  const R va = (sq - B) * i2a, vb = (-B - sq) * i2a;
-  cp = va > vb ? va : vb;
-  cm = va > vb ? vb : va;
+  return fast_speed(rho, uu, pg, bsq, gam, ut, ud, m.ctt, ctd, cdd);
 }
 
 }  // namespace grmhd
