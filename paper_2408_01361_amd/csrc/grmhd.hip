@@ -415,6 +415,17 @@ __device__ __forceinline__ void flux_face(const Dev& g, const double* __restrict
   face_llf<D, R, FT>(g, qL, qR, tab, q2, F, c);
 }
 
+// Position of this thread in workgroup wg of a plane of m1 by m2 positions
+// from (lo1, lo2), x1 fastest.
+__device__ __forceinline__ bool plane_index(int m1, int lo1, int m2, int lo2, unsigned wg, int& i, int& j) {
+  const unsigned t = wg * BLOCK + threadIdx.x;
+  if (t >= (unsigned)m1 * (unsigned)m2) return false;
+  const unsigned jj = t / (unsigned)m1;
+  i = lo1 + (int)(t - jj * (unsigned)m1);
+  j = lo2 + (int)jj;
+  return true;
+}
+
 #ifndef FLUX_WAVES
 #define FLUX_WAVES 3
 #endif
@@ -430,17 +441,63 @@ __device__ __forceinline__ void flux_face(const Dev& g, const double* __restrict
 #endif
 constexpr int TILE_FACES = 4 * TILE_STEPS - 1;
 constexpr int TILE_NBUF = 3;
+constexpr long FLUX_TURN_BYTES = 4L << 20;  // (the L2 of an XCD)
 
-// All three face directions in one launch: workgroups [0, nb1) take x1
-// faces, [nb1, nb1 + nb2) x2 faces, the rest x3 faces (nb1 and nb2 are
-// multiples of 8, so each part keeps the XCD-aware order of its schedule).
+// Work order of the flux launch.  Each direction has a list of workgroups
+// that goes through the grid in blocks of kb x3 planes and, inside a block,
+// along x2 (x1_item, tile_item below).  Every XCD takes the same eighth of
+// each list -- so all hold equal shares of the heavy and the light workgroups
+// and the same region of the grid -- in `rounds` turns, each a piece of the x2
+// faces, of the x3 faces and of the x1 faces.  The three directions of a
+// region then read the same prims out of that XCD's L2 instead of passing
+// over the whole array one after the other: HBM reads of the 128^3 WENO5
+// launch 936 -> 337 MB.
+struct FluxPlan {
+  int kb;                       // planes of a block
+  int lj, lk, nj, nk;           // tiled sweeps: faces of a segment and segments along x2, x3
+  unsigned per1, per2, per3;    // workgroups of a plane (x2 tiles, x3 tiles: column groups in all)
+  unsigned n1, n2, n3;          // lengths of the lists
+  unsigned rounds, q1, q2, q3;  // turns of an XCD, and its workgroups of each list in a turn
+};
+inline unsigned flux_blocks(const FluxPlan& pl) { return 8u * pl.rounds * (pl.q1 + pl.q2 + pl.q3); }
+
+// Direction d and list position t that dispatched workgroup b takes; false
+// for none.
+__device__ __forceinline__ bool flux_item(const FluxPlan& pl, unsigned b, int& d, unsigned& t) {
+  const unsigned x = b & 7u, slot = b >> 3, per = pl.q1 + pl.q2 + pl.q3, round = slot / per;
+  unsigned r = slot - round * per;
+  d = r < pl.q2 ? 2 : (r < pl.q2 + pl.q3 ? 3 : 1);
+  const unsigned q = d == 2 ? pl.q2 : (d == 3 ? pl.q3 : pl.q1), n = d == 2 ? pl.n2 : (d == 3 ? pl.n3 : pl.n1);
+  r -= d == 2 ? 0u : (d == 3 ? pl.q2 : pl.q2 + pl.q3);
+  const unsigned lo = (unsigned)((unsigned long long)n * x / 8), hi = (unsigned)((unsigned long long)n * (x + 1) / 8);
+  t = lo + round * q + r;
+  return t < hi;
+}
+// Position t of a list of `per` workgroups per plane over np planes: workgroup
+// `wg` of plane `k` (from 0), the planes of a block next to each other.
+__device__ __forceinline__ void plane_item(const FluxPlan& pl, unsigned per, int np, unsigned t, unsigned& wg, int& k) {
+  const unsigned kb = (unsigned)pl.kb, blk = t / (per * kb), r = t - blk * per * kb;
+  const unsigned left = (unsigned)np - blk * kb, n = left < kb ? left : kb;
+  wg = r / n;
+  k = (int)(blk * kb + (r - wg * n));
+}
+// Position t of the x2 tiles' list (column groups of 64 over (x1, x3), nj
+// segments): the column groups of about kb planes, segment by segment.
+__device__ __forceinline__ void tile2_item(const FluxPlan& pl, int n1, unsigned t, unsigned& cg, unsigned& seg) {
+  const unsigned most = (unsigned)((n1 + 2) * pl.kb + 63) / 64u, nj = (unsigned)pl.nj;
+  const unsigned blk = t / (most * nj), r = t - blk * most * nj;
+  const unsigned left = pl.per2 - blk * most, n = left < most ? left : most;
+  seg = r / n;
+  cg = blk * most + (r - seg * n);
+}
+
+// All three face directions in one launch, in the order of FluxPlan.
 // For MC and WENO5 the x1 part is the shared-edge sweep, for WENO5 the x2
 // and x3 parts are the LDS-tiled sweeps (below); other schemes and parts
 // evaluate face by face.
 template <int RECON, typename R, typename FT, bool FACE>
 __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(FACE ? 3 : FLUX_WAVES, 8)))
-k_flux_all(Dev g, Sched b1, Sched b2, Sched b3, unsigned nb1, unsigned nb2, unsigned nb3,
-           const double* __restrict__ P, const double* __restrict__ tabF1,
+k_flux_all(Dev g, FluxPlan pl, const double* __restrict__ P, const double* __restrict__ tabF1,
            const double* __restrict__ tabF2, const double* __restrict__ tabC, FT* __restrict__ F1,
            FT* __restrict__ F2, FT* __restrict__ F3, const double* __restrict__ ph1,
            const double* __restrict__ ph2, const double* __restrict__ ph3) {
@@ -449,23 +506,35 @@ k_flux_all(Dev g, Sched b1, Sched b2, Sched b3, unsigned nb1, unsigned nb2, unsi
   // registers and LDS cost a wave per SIMD)
   constexpr bool tiled = RECON == GRMHD_RECON_WENO5 && FLUX_TILE;
   __shared__ R rows[tiled ? TILE_NBUF * 4 * NVAR * 64 : 1];
-  const unsigned b = blockIdx.x;
+  int d;
+  unsigned t;
+  if (!flux_item(pl, blockIdx.x, d, t)) return;
+  unsigned wg, seg;
   int i, j, k;
-  if (b < nb1) {
-    if (shared)
-      sweep_x1<RECON, R, FT, FACE>(g, xcd_order(b, nb1), P, tabF1, F1, ph1);
-    else if (sched_index(b1, b, nb1, i, j, k))
-      flux_face<1, RECON, R, FT>(g, P, tabF1, F1, i, j, k, FACE ? ph1 : nullptr);
-  } else if (b < nb1 + nb2) {
-    if (tiled)
-      sweep_tile<2, RECON, R, FT, FACE>(g, xcd_order(b - nb1, nb2), P, tabF2, F2, ph2, rows);
-    else if (sched_index(b2, b - nb1, nb2, i, j, k))
-      flux_face<2, RECON, R, FT>(g, P, tabF2, F2, i, j, k, FACE ? ph2 : nullptr);
-  } else {
-    if (tiled)
-      sweep_tile<3, RECON, R, FT, FACE>(g, xcd_order(b - nb1 - nb2, nb3), P, tabC, F3, ph3, rows);
-    else if (sched_index(b3, b - nb1 - nb2, nb3, i, j, k))
+  if (d == 2) {
+    if (tiled) {
+      tile2_item(pl, g.n1, t, wg, seg);
+      sweep_tile<2, RECON, R, FT, FACE>(g, wg, (int)seg * pl.lj, pl.lj, P, tabF2, F2, ph2, rows);
+      return;
+    }
+    plane_item(pl, pl.per2, g.n3 + 2, t, wg, k);
+    if (plane_index(g.n1 + 2, -1, g.n2 + 1, 0, wg, i, j))
+      flux_face<2, RECON, R, FT>(g, P, tabF2, F2, i, j, k - 1, FACE ? ph2 : nullptr);
+  } else if (d == 3) {
+    if (tiled) {
+      seg = t / pl.per3;
+      sweep_tile<3, RECON, R, FT, FACE>(g, t - seg * pl.per3, (int)seg * pl.lk, pl.lk, P, tabC, F3, ph3, rows);
+      return;
+    }
+    plane_item(pl, pl.per3, g.n3 + 1, t, wg, k);
+    if (plane_index(g.n1 + 2, -1, g.n2 + 2, -1, wg, i, j))
       flux_face<3, RECON, R, FT>(g, P, tabC, F3, i, j, k, FACE ? ph3 : nullptr);
+  } else {
+    plane_item(pl, pl.per1, g.n3 + 2, t, wg, k);
+    if (shared)
+      sweep_x1<RECON, R, FT, FACE>(g, wg, k - 1, 1, P, tabF1, F1, ph1);
+    else if (plane_index(g.n1 + 1, 0, g.n2 + 2, -1, wg, i, j))
+      flux_face<1, RECON, R, FT>(g, P, tabF1, F1, i, j, k - 1, FACE ? ph1 : nullptr);
   }
 }
 
@@ -524,27 +593,27 @@ __device__ __forceinline__ void zone_edges_x1(const double* __restrict__ P, long
   }
 }
 
-// Workgroups of the shared-edge x1 part for a box of n1z zones (4 wavefronts
-// of 63 new zones each), rounded up to a multiple of 8.
-inline unsigned x1_sweep_blocks(long n1z) {
+// Workgroups of the shared-edge x1 part for n1z zones (4 wavefronts of 63 new
+// zones each).
+__host__ __device__ inline unsigned x1_sweep_blocks(long n1z) {
   const long waves = (n1z + 62) / 63;
-  return (unsigned)(((waves + 3) / 4 + 7) / 8 * 8);
+  return (unsigned)((waves + BLOCK / 64 - 1) / (BLOCK / 64));
 }
 
-// lb: this workgroup's place in the part (XCD-ordered).
+// Workgroup wg of the x1 faces of the nk planes from k0 (rows -1..n2).
 template <int RECON, typename R, typename FT, bool FACE>
-__device__ __forceinline__ void sweep_x1(const Dev& g, unsigned lb, const double* __restrict__ P,
+__device__ __forceinline__ void sweep_x1(const Dev& g, unsigned wg, int k0, int nk, const double* __restrict__ P,
                                          const double* __restrict__ tabF1, FT* __restrict__ F1,
                                          const double* __restrict__ ph1) {
   const int lane = (int)(threadIdx.x & 63u);
-  const int wave = (int)(lb * (BLOCK / 64) + (threadIdx.x >> 6));
+  const int wave = (int)(wg * (BLOCK / 64) + (threadIdx.x >> 6));
   const unsigned m1 = (unsigned)g.n1 + 2u, m12 = m1 * ((unsigned)g.n2 + 2u);
   const int t = wave * 63 + lane - 1;
-  const bool valid = t >= 0 && t < (int)(m12 * ((unsigned)g.n3 + 2u));
+  const bool valid = t >= 0 && t < (int)(m12 * (unsigned)nk);
   const unsigned tt = valid ? (unsigned)t : 0u;
   const unsigned kk = tt / m12, r = tt - kk * m12;
   const unsigned jj = r / m1;
-  const int i = (int)(r - jj * m1) - 1, j = (int)jj - 1, k = (int)kk - 1;
+  const int i = (int)(r - jj * m1) - 1, j = (int)jj - 1, k = k0 + (int)kk;
   const long c = zid(g, i, j, k);
   R left[NVAR], right[NVAR];
   zone_edges_x1<RECON, R>(P, g.nz, c, (R)g.weno_eps, left, right);
@@ -579,19 +648,6 @@ __device__ __forceinline__ void sweep_x1(const Dev& g, unsigned lb, const double
 // previous one, and every wavefront has passed the barrier in between.
 // The face values are those of the per-face evaluation bit for bit.
 
-// Columns and faces of the tiled part for direction D (2 or 3).
-__host__ __device__ inline long tile_columns(const Dev& g, int D) {
-  return (long)(g.n1 + 2) * ((D == 2 ? g.n3 : g.n2) + 2);
-}
-__host__ __device__ inline int tile_faces(const Dev& g, int D) { return (D == 2 ? g.n2 : g.n3) + 1; }
-// Workgroups of the tiled part: column groups of 64 times segments, rounded
-// up to a multiple of 8.
-inline unsigned tile_blocks(const Dev& g, int D) {
-  const long ncg = (tile_columns(g, D) + 63) / 64;
-  const long nseg = (tile_faces(g, D) + TILE_FACES - 1) / TILE_FACES;
-  return (unsigned)((ncg * nseg + 7) / 8 * 8);
-}
-
 // Both edges of every prim of the zone at padded index c along the axis of
 // stride s: the left edges into left[], the right edges stored to
 // rows[v * 64] as they are formed.
@@ -610,26 +666,20 @@ __device__ __forceinline__ void zone_edges(const double* __restrict__ P, long nz
   }
 }
 
-// lb: this workgroup's place in the part (XCD-ordered); nb: workgroups in
-// the part; rows: the LDS right-edge buffers (TILE_NBUF x 4 x NVAR x 64).
+// Column group wg of the D-faces fs .. fs + most - 1; rows: the LDS
+// right-edge buffers (TILE_NBUF x 4 x NVAR x 64).
 template <int D, int RECON, typename R, typename FT, bool FACE>
-__device__ __forceinline__ void sweep_tile(const Dev& g, unsigned lb, const double* __restrict__ P,
+__device__ __forceinline__ void sweep_tile(const Dev& g, unsigned wg, int fs, int most, const double* __restrict__ P,
                                            const double* __restrict__ tab, FT* __restrict__ F,
                                            const double* __restrict__ ph, R* rows) {
   const int lane = (int)(threadIdx.x & 63u), w = (int)(threadIdx.x >> 6);
-  const long ncol = tile_columns(g, D);
-  const int nface = tile_faces(g, D);
-  const unsigned nseg = (unsigned)((nface + TILE_FACES - 1) / TILE_FACES);
-  const unsigned cg = lb / nseg, sg = lb - cg * nseg;
-  const long col = (long)cg * 64 + lane;
-  const bool colvalid = col < ncol;
-  const long cc = colvalid ? col : 0;
-  const int m1 = g.n1 + 2;
-  const int i = (int)(cc % m1) - 1, o = (int)(cc / m1) - 1;   // o: the other transverse index
-  const int fs = (int)sg * TILE_FACES;
-  const int fe = fs + TILE_FACES < nface ? fs + TILE_FACES : nface;
-  // a workgroup past the last segment (rounding) runs no step
-  const int nsteps = fs < nface ? (fe - fs + 1 + 3) / 4 : 0;
+  const unsigned m1 = (unsigned)g.n1 + 2u;
+  const unsigned col = wg * 64u + (unsigned)lane;
+  const bool colvalid = col < m1 * (unsigned)((D == 2 ? g.n3 : g.n2) + 2);
+  const unsigned cc = colvalid ? col : 0u, oo = cc / m1;
+  const int i = (int)(cc - oo * m1) - 1, o = (int)oo - 1;   // o: the other transverse index
+  const int nface = (D == 2 ? g.n2 : g.n3) + 1, fe = fs + most < nface ? fs + most : nface;
+  const int nsteps = (fe - fs + 1 + 3) / 4;
   const long s = D == 2 ? (long)g.s1 : g.plane;
   for (int t = 0; t < nsteps; t++) {
     const int r = fs - 1 + 4 * t + w;            // zone row along the face axis
@@ -1919,7 +1969,41 @@ int cell_b_from_faces(grmhd_ctx* c) {
   return hip_check();
 }
 
-inline unsigned round8(unsigned n) { return (n + 7u) & ~7u; }
+// The flux launch's plan: segments of TILE_FACES faces for the tiled sweeps of
+// WENO5 and blocks of as many planes, otherwise blocks of kg planes.  A turn
+// covers as many prims as one XCD's L2 holds: fewer turns read more from HBM
+// (128^3 WENO5, 10 steps: 1 turn 11.29 ms, 4 turns 11.09), more turns end in
+// more short pieces (16 turns 11.46 ms; 64^3 production, 5 steps: 1 turn
+// 1.47 ms, 4 turns 1.61).
+FluxPlan flux_plan(const Dev& g, int recon, int kg) {
+  const bool tiled = recon == GRMHD_RECON_WENO5 && FLUX_TILE;
+  const bool shared = recon == GRMHD_RECON_MC || recon == GRMHD_RECON_WENO5;
+  auto cut = [](long n, long size) { return (unsigned)((n + size - 1) / size); };
+  const long m1 = g.n1 + 2, m2 = g.n2 + 2, m3 = g.n3 + 2;
+  FluxPlan pl;
+  pl.kb = tiled ? TILE_FACES : (int)(kg < m3 ? kg : m3);
+  pl.lj = pl.lk = TILE_FACES;
+  pl.nj = (int)cut(m2 - 1, pl.lj);
+  pl.nk = (int)cut(m3 - 1, pl.lk);
+  pl.per1 = shared ? x1_sweep_blocks(m1 * m2) : cut((m1 - 1) * m2, BLOCK);
+  pl.n1 = pl.per1 * (unsigned)m3;
+  if (tiled) {
+    pl.per2 = cut(m1 * m3, 64);
+    pl.n2 = pl.per2 * (unsigned)pl.nj;
+    pl.per3 = cut(m1 * m2, 64);
+    pl.n3 = pl.per3 * (unsigned)pl.nk;
+  } else {
+    pl.per2 = cut(m1 * (m2 - 1), BLOCK);
+    pl.n2 = pl.per2 * (unsigned)m3;
+    pl.per3 = cut(m1 * m2, BLOCK);
+    pl.n3 = pl.per3 * (unsigned)(m3 - 1);
+  }
+  pl.rounds = cut(NVAR * 8 * g.nz, 8L * FLUX_TURN_BYTES);
+  pl.q1 = cut(cut(pl.n1, 8), pl.rounds);
+  pl.q2 = cut(cut(pl.n2, 8), pl.rounds);
+  pl.q3 = cut(cut(pl.n3, 8), pl.rounds);
+  return pl;
+}
 
 // Flux and EMF kernels of one stage, reading the (ghost-filled) prims P.
 // Edge EMFs of the stage from the fluxes: the Flux-CT average (also the
@@ -1944,22 +2028,15 @@ int stage_fluxes(grmhd_ctx* c, const double* P, unsigned long long* zero = nullp
   FT* F1 = (FT*)c->F[0];
   FT* F2 = (FT*)c->F[1];
   FT* F3 = (FT*)c->F[2];
-  Sched b1 = make_sched(make_box(0, g.n1, -1, g.n2, -1, g.n3), c->kg_flux);
-  Sched b2 = make_sched(make_box(-1, g.n1, 0, g.n2, -1, g.n3), c->kg_flux);
-  Sched b3 = make_sched(make_box(-1, g.n1, -1, g.n2, 0, g.n3), c->kg_flux);
-  const bool shared = c->params.recon == GRMHD_RECON_MC || c->params.recon == GRMHD_RECON_WENO5;
-  const unsigned n1 = shared ? x1_sweep_blocks((long)(g.n1 + 2) * (g.n2 + 2) * (g.n3 + 2))
-                             : round8(blocks_for(b1));
-  const bool tiled = c->params.recon == GRMHD_RECON_WENO5 && FLUX_TILE;
-  const unsigned n2 = tiled ? tile_blocks(g, 2) : round8(blocks_for(b2));
-  const unsigned n3 = tiled ? tile_blocks(g, 3) : blocks_for(b3);
+  const FluxPlan pl = flux_plan(g, c->params.recon, c->kg_flux);
+  const unsigned nb = flux_blocks(pl);
   const double* Pc = P;
   const double* p1 = ph ? ph[0] : nullptr;
   const double* p2 = ph ? ph[1] : nullptr;
   const double* p3 = ph ? ph[2] : nullptr;
   auto go = [&](auto kernel) {
-    return launch(c, T_FLUX, kernel, n1 + n2 + n3, g, b1, b2, b3, n1, n2, n3, Pc, (const double*)c->tabF1,
-                  (const double*)c->tabF2, (const double*)c->tabC, F1, F2, F3, p1, p2, p3);
+    return launch(c, T_FLUX, kernel, nb, g, pl, Pc, (const double*)c->tabF1, (const double*)c->tabF2,
+                  (const double*)c->tabC, F1, F2, F3, p1, p2, p3);
   };
   int rc;
   const bool face = ph != nullptr;
@@ -2142,6 +2219,7 @@ int emhd_stage(grmhd_ctx* c, const double* Pin, double* Xin, double* Pout, doubl
   Sched b1 = make_sched(make_box(0, g.n1, -1, g.n2, -1, g.n3), c->kg_flux);
   Sched b2 = make_sched(make_box(-1, g.n1, 0, g.n2, -1, g.n3), c->kg_flux);
   Sched b3 = make_sched(make_box(-1, g.n1, -1, g.n2, 0, g.n3), c->kg_flux);
+  auto round8 = [](unsigned n) { return (n + 7u) & ~7u; };
   const unsigned n1 = round8(blocks_for(b1)), n2 = round8(blocks_for(b2)), n3 = blocks_for(b3);
   double* F1 = (double*)c->F[0];
   double* F2 = (double*)c->F[1];

@@ -50,8 +50,7 @@ __host__ __device__ inline int tiles_of(const Box& b, int t1, int t2, int t3) {
 // t1 x t2 x t3 shape, tiles of faces.
 __host__ __device__ inline int x1_items(const BlockView& b) {
   if (b.t1 == 0) {
-    const long n1z = (long)(b.g.n1 + 2) * (b.g.n2 + 2) * (b.g.n3 + 2);
-    return (int)(((n1z + 62) / 63 + BLOCK / 64 - 1) / (BLOCK / 64));
+    return (int)x1_sweep_blocks((long)(b.g.n1 + 2) * (b.g.n2 + 2) * (b.g.n3 + 2));
   }
   return tiles_of(phase_box(b.g, PH_FLUX, 1), b.t1, b.t2, b.t3);
 }
@@ -102,7 +101,7 @@ __device__ __forceinline__ void pack_flux_item(const BlockView& b, const double*
   const int n1t = x1_items(b);
   if (lt < n1t) {
     if (LINEAR || t1 == 0) {  // every thread of the workgroup takes part (cross-lane shift)
-      sweep_x1<RECON, double, double, false>(g, (unsigned)lt, Pin, b.tabF1, b.F[0], nullptr);
+      sweep_x1<RECON, double, double, false>(g, (unsigned)lt, -1, g.n3 + 2, Pin, b.tabF1, b.F[0], nullptr);
       return;
     }
     if (tile_pos(phase_box(g, PH_FLUX, 1), t1, t2, t3, lt, i, j, k))
