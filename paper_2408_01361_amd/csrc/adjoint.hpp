@@ -176,7 +176,7 @@ k_adj_face(Dev g, Box box, const double* __restrict__ P,
   for (int v = 0; v < NVAR; v++) {
     double qs[St::W];
 #pragma unroll
-    for (int z = 0; z < St::W; z++) qs[z] = P[v * nz + c + (z - St::H) * s];
+    for (int z = 0; z < St::W; z++) qs[z] = P[vx(v, nz, c + (z - St::H) * s)];
     double dL[St::W], dR[St::W];
     if constexpr (RECON == GRMHD_RECON_WENO5) {
       // the left state is weno5(q0, .., q4), the right one weno5(q5, .., q1):
@@ -289,8 +289,7 @@ __global__ void __launch_bounds__(BLOCK) k_adj_zone(Dev g, Box box, const double
   // the local terms by one reverse sweep: the source (adjoint lambda_L of
   // the energy and momentum rows) and, in stage 1, the conserved variables
   double p[NVAR];
-#pragma unroll
-  for (int v = 0; v < NVAR; v++) p[v] = Pin[v * nz + c];
+  load8(Pin, nz, c, p);
   const double Sb[4] = {lL[UU], lL[U1], lL[U2], lL[U3]};
   double qb[NVAR], gz;
   zone_vjp(p, m, g.gam, cn, Sb, STAGE1 ? lU : nullptr, qb, gz);
@@ -370,8 +369,7 @@ __global__ void __launch_bounds__(BLOCK) k_adj_ift(Dev g, const double* __restri
   // so nothing held in registers is indexed by the pass counter.
   double Jh[5][NVAR + 1];
   double pv[NVAR];
-#pragma unroll
-  for (int v = 0; v < NVAR; v++) pv[v] = P[v * nz + t];
+  load8(P, nz, t, pv);
 #pragma unroll 1
   for (int sd = 0; sd <= NVAR; sd++) {
     Dual p[NVAR];

@@ -31,7 +31,7 @@
 //
 // Included inside the anonymous namespace of grmhd.hip.
 
-constexpr int NXV = 2;  // extra variables per zone
+constexpr int NXV = 2;  // extra variables per zone (stored as a pair per zone: index 2 c + n)
 
 // Physical heat flux q and anisotropy dP of the rescaled variables x.
 __device__ __forceinline__ void emhd_unscale(const Dev& g, const double p[NVAR], const double x[NXV], double& q,
@@ -99,24 +99,26 @@ __global__ void __launch_bounds__(BLOCK) k_bc_extra(Dev g, double* X) {
   const int sk = bc_map(k, g.n3, g.bc[4], g.bc[5], f3);
   if (si == i && sj == j && sk == k) return;  // frozen
   const long src = zid(g, si, sj, sk), dst = zid(g, i, j, k);
-#pragma unroll
-  for (int n = 0; n < NXV; n++) X[n * g.nz + dst] = X[n * g.nz + src];
+  Pair<double>* q = (Pair<double>*)X;
+  q[dst] = q[src];
 }
 
-// Face states of one variable at stride s around padded index c (the face
-// between c - s and c), as recon_pair forms them.
-template <int RECON>
-__device__ __forceinline__ void recon_one(const double* __restrict__ q, long s, double eps, double& l,
-                                          double& r) {
-  if (RECON == GRMHD_RECON_MC) {
-    const double m2 = q[-2 * s], m1 = q[-s], p0 = q[0], p1 = q[s];
-    l = mc_left(m2, m1, p0);
-    r = mc_right(m1, p0, p1);
-  } else {
-    const double m3 = q[-3 * s], m2 = q[-2 * s], m1 = q[-s], p0 = q[0], p1 = q[s], p2 = q[2 * s];
-    l = weno5(m3, m2, m1, p0, p1, eps);
-    r = weno5(p2, p1, p0, m1, m2, eps);
-  }
+// The caller's extra variables [2][padded] into the state and the stage
+// buffer (which carries the same frozen ghosts), and the state back out.
+__global__ void __launch_bounds__(BLOCK) k_load_extra(long nz, const double* __restrict__ src, double* __restrict__ X,
+                                                      double* __restrict__ X1) {
+  const long c = blockIdx.x * (long)BLOCK + threadIdx.x;
+  if (c >= nz) return;
+  const Pair<double> x{src[c], src[nz + c]};
+  ((Pair<double>*)X)[c] = x;
+  ((Pair<double>*)X1)[c] = x;
+}
+__global__ void __launch_bounds__(BLOCK) k_read_extra(long nz, const double* __restrict__ X, double* __restrict__ dst) {
+  const long c = blockIdx.x * (long)BLOCK + threadIdx.x;
+  if (c >= nz) return;
+  const Pair<double> x = ((const Pair<double>*)X)[c];
+  dst[c] = x.a;
+  dst[nz + c] = x.b;
 }
 
 // LLF flux of the ten variables through the lower D-face of zone (i, j, k),
@@ -130,17 +132,16 @@ __device__ __forceinline__ void emhd_face(const Dev& g, const double* __restrict
 #pragma clang fp contract(off)
   const long c = zid(g, i, j, k);
   if (pole_face<D>(g, j)) {
-#pragma unroll
-    for (int v = 0; v < NVAR; v++) F[v * g.nz + c] = 0.0;
-#pragma unroll
-    for (int n = 0; n < NXV; n++) FX[n * g.nz + c] = 0.0;
+    const double zero[NVAR] = {};
+    store_flux<D>(F, g.nz, c, zero);
+    ((Pair<double>*)FX)[c] = Pair<double>{0.0, 0.0};
     return;
   }
   const long s = D == 1 ? 1 : (D == 2 ? (long)g.s1 : g.plane);
   double qL[NVAR], qR[NVAR], xL[NXV], xR[NXV];
   recon_pair<RECON, double>(P, g.nz, c, s, g.weno_eps, qL, qR);
 #pragma unroll
-  for (int n = 0; n < NXV; n++) recon_one<RECON>(X + n * g.nz + c, s, g.weno_eps, xL[n], xR[n]);
+  for (int n = 0; n < NXV; n++) recon_face<RECON, double>(X + 2 * c + n, 2 * s, g.weno_eps, xL[n], xR[n]);
   PointMetric<double> m;
   load_metric<double>(tab, g.plane, pid(g, i, j), m);
   Fluid<double> fl, fr;
@@ -159,12 +160,12 @@ __device__ __forceinline__ void emhd_face(const Dev& g, const double* __restrict
   if (cpr > cmax) cmax = cpr;
   if (-cml > cmax) cmax = -cml;
   if (-cmr > cmax) cmax = -cmr;
+  double f[NVAR + NXV];
 #pragma unroll
-  for (int v = 0; v < NVAR; v++)
-    if (v != B1 + D - 1) F[v * g.nz + c] = 0.5 * (FL[v] + FR[v]) - 0.5 * cmax * (UR[v] - UL[v]);
-#pragma unroll
-  for (int n = 0; n < NXV; n++)
-    FX[n * g.nz + c] = 0.5 * (FL[NVAR + n] + FR[NVAR + n]) - 0.5 * cmax * (UR[NVAR + n] - UL[NVAR + n]);
+  for (int v = 0; v < NVAR + NXV; v++)
+    if (v != B1 + D - 1) f[v] = 0.5 * (FL[v] + FR[v]) - 0.5 * cmax * (UR[v] - UL[v]);
+  store_flux<D>(F, g.nz, c, f);
+  ((Pair<double>*)FX)[c] = Pair<double>{f[NVAR], f[NVAR + 1]};
 }
 
 // All three face directions in one launch, partitioned as k_flux_all.
@@ -210,11 +211,8 @@ __device__ __forceinline__ void emhd_targets(const Dev& g, const double* __restr
     const long s = a == 0 ? 1 : (a == 1 ? (long)g.s1 : g.plane);
     const long qs = a == 0 ? 1 : (a == 1 ? (long)g.s1 : 0);
     double pp[NVAR], pm[NVAR];
-#pragma unroll
-    for (int v = 0; v < NVAR; v++) {
-      pp[v] = P[v * g.nz + c + s];
-      pm[v] = P[v * g.nz + c - s];
-    }
+    load8(P, g.nz, c + s, pp);
+    load8(P, g.nz, c - s, pm);
     PointMetric<double> mp, mm;
     load_metric<double>(tabC, g.plane, q2 + qs, mp);
     load_metric<double>(tabC, g.plane, q2 - qs, mm);
@@ -280,16 +278,14 @@ k_targets_emhd(Dev g, Sched box, const double* __restrict__ Pin, const double* _
   if (!sched_index(box, blockIdx.x, gridDim.x, i, j, k)) return;
   const long c = zid(g, i, j, k);
   double p[NVAR];
-#pragma unroll
-  for (int v = 0; v < NVAR; v++) p[v] = Pin[v * g.nz + c];
+  load8(Pin, g.nz, c, p);
   PointMetric<double> m;
   load_metric<double>(tabC, g.plane, pid(g, i, j), m);
   Fluid<double> f;
   fluid_state(p, m, f);
   double Xt[NXV], dsp;
   emhd_targets(g, Pin, tabC, conn, i, j, k, p, f, m, Xt, dsp);
-#pragma unroll
-  for (int n = 0; n < NXV; n++) xt[n * g.nz + c] = Xt[n];
+  ((Pair<double>*)xt)[c] = Pair<double>{Xt[0], Xt[1]};
   divu[c] = dsp;
 }
 
@@ -316,10 +312,9 @@ k_update_emhd(Dev g, Sched box, const double* __restrict__ Pin, const double* __
   const long c = zid(g, i, j, k), nz = g.nz, si = 1, sj = g.s1, sk = g.plane;
   const long q2 = pid(g, i, j);
   double p[NVAR], x[NXV];
+  load8(Pin, nz, c, p);
 #pragma unroll
-  for (int v = 0; v < NVAR; v++) p[v] = Pin[v * nz + c];
-#pragma unroll
-  for (int n = 0; n < NXV; n++) x[n] = Xin[n * nz + c];
+  for (int n = 0; n < NXV; n++) x[n] = Xin[2 * c + n];
   PointMetric<double> m;
   load_metric<double>(tabC, g.plane, q2, m);
   Fluid<double> f;
@@ -340,42 +335,48 @@ k_update_emhd(Dev g, Sched box, const double* __restrict__ Pin, const double* __
 #pragma unroll
         for (int l = 0; l < 4; l++) s[nu] += Tk[l] * conn[(l * 10 + sidx(nu, kk)) * g.plane + q2];
     }
+    double lo[5], hi[5];
+    load_flux5(F1, nz, c, lo);
+    load_flux5(F1, nz, c + si, hi);
 #pragma unroll
-    for (int v = 0; v < 5; v++) {
-      const double d1 = (F1[v * nz + c + si] - F1[v * nz + c]) / g.dx1;
-      const double d2 = (F2[v * nz + c + sj] - F2[v * nz + c]) / g.dx2;
-      const double d3 = (F3[v * nz + c + sk] - F3[v * nz + c]) / g.dx3;
-      L[v] = -((d1 + d2) + d3) + (v == RHO ? 0.0 : m.gdet * s[v - 1]);
-    }
+    for (int v = 0; v < 5; v++) L[v] = (hi[v] - lo[v]) / g.dx1;
+    load_flux5(F2, nz, c, lo);
+    load_flux5(F2, nz, c + sj, hi);
+#pragma unroll
+    for (int v = 0; v < 5; v++) L[v] = L[v] + (hi[v] - lo[v]) / g.dx2;
+    load_flux5(F3, nz, c, lo);
+    load_flux5(F3, nz, c + sk, hi);
+#pragma unroll
+    for (int v = 0; v < 5; v++) L[v] = -(L[v] + (hi[v] - lo[v]) / g.dx3) + (v == RHO ? 0.0 : m.gdet * s[v - 1]);
     ct_field_rate(g, E1, E2, E3, c, L);
   }
   double LX[NXV];
 #pragma unroll
   for (int n = 0; n < NXV; n++) {
-    const double d1 = (FX1[n * nz + c + si] - FX1[n * nz + c]) / g.dx1;
-    const double d2 = (FX2[n * nz + c + sj] - FX2[n * nz + c]) / g.dx2;
-    const double d3 = (FX3[n * nz + c + sk] - FX3[n * nz + c]) / g.dx3;
-    LX[n] = -((d1 + d2) + d3) + m.gdet * xrhs[n * nz + c] / g.tau;
+    const long o = 2 * c + n;
+    const double d1 = (FX1[o + 2 * si] - FX1[o]) / g.dx1;
+    const double d2 = (FX2[o + 2 * sj] - FX2[o]) / g.dx2;
+    const double d3 = (FX3[o + 2 * sk] - FX3[o]) / g.dx3;
+    LX[n] = -((d1 + d2) + d3) + m.gdet * xrhs[o] / g.tau;
   }
   double U0[NVAR + NXV];
   if (STAGE == 1) {
     prim_to_flux_emhd(g, p, x, f, m, 0, U0);
+    store8(V, nz, c, U0);
 #pragma unroll
-    for (int v = 0; v < NVAR; v++) V[v * nz + c] = U0[v];
-#pragma unroll
-    for (int n = 0; n < NXV; n++) VX[n * nz + c] = U0[NVAR + n];
+    for (int n = 0; n < NXV; n++) VX[2 * c + n] = U0[NVAR + n];
     utn[c] = f.ucon[0];
   } else {
+    load8(V, nz, c, U0);
 #pragma unroll
-    for (int v = 0; v < NVAR; v++) U0[v] = V[v * nz + c];
-#pragma unroll
-    for (int n = 0; n < NXV; n++) U0[NVAR + n] = VX[n * nz + c];
+    for (int n = 0; n < NXV; n++) U0[NVAR + n] = VX[2 * c + n];
   }
   const double h = STAGE == 1 ? 0.5 * dt : dt;
 #pragma unroll
-  for (int v = 0; v < NVAR; v++) ustar[v * nz + c] = U0[v] + h * L[v];
+  for (int v = 0; v < NVAR; v++) L[v] = U0[v] + h * L[v];
+  store8(ustar, nz, c, L);
 #pragma unroll
-  for (int n = 0; n < NXV; n++) xrhs[n * nz + c] = U0[NVAR + n] + h * LX[n];
+  for (int n = 0; n < NXV; n++) xrhs[2 * c + n] = U0[NVAR + n] + h * LX[n];
 }
 
 // Implicit pass of a stage: per interior zone, the hydro prims and X whose
@@ -405,15 +406,12 @@ k_implicit_emhd(Dev g, Sched box, const double* __restrict__ Pin, const double* 
   if (in) {
     const long c = zid(g, i, j, k), nz = g.nz;
     double Us[NVAR], Ux[NXV], gs[NVAR], xg[NXV];
-#pragma unroll
-    for (int v = 0; v < NVAR; v++) {
-      Us[v] = ustar[v * nz + c];
-      gs[v] = Pin[v * nz + c];
-    }
+    load8(ustar, nz, c, Us);
+    load8(Pin, nz, c, gs);
 #pragma unroll
     for (int n = 0; n < NXV; n++) {
-      Ux[n] = xrhs[n * nz + c];
-      xg[n] = Xin[n * nz + c];
+      Ux[n] = xrhs[2 * c + n];
+      xg[n] = Xin[2 * c + n];
     }
     const double dsp = divu[c], ut_n = utn[c];
     const double h = STAGE == 1 ? 0.5 * dt : dt;
@@ -480,10 +478,9 @@ k_implicit_emhd(Dev g, Sched box, const double* __restrict__ Pin, const double* 
       for (int n = 0; n < NXV; n++) xo[n] = xg[n];
       atomicAdd(&fails[C_FAILS], 1ull);
     }
+    store8(Pout, nz, c, out);
 #pragma unroll
-    for (int v = 0; v < NVAR; v++) Pout[v * nz + c] = out[v];
-#pragma unroll
-    for (int n = 0; n < NXV; n++) Xout[n * nz + c] = xo[n];
+    for (int n = 0; n < NXV; n++) Xout[2 * c + n] = xo[n];
     if (RATE) r = zone_rate(g, out, m);
   }
   if (RATE) {

@@ -160,7 +160,7 @@ __device__ __forceinline__ bool sched_index(const Sched& s, unsigned bid, unsign
 
 // Tables over the padded (x1, x2) plane: metric at zone centres, x1 faces,
 // x2 faces; sqrt(-g) at (x1, x2) corners; connection and the geometric
-// source's metric-derivative rows at centres.  x3 faces share the centre
+// source's metric-derivative entries at centres.  x3 faces share the centre
 // values (nothing depends on x3).  Pole faces and corners are left zero:
 // nothing reads them.
 __global__ void k_geometry(Dev g, double* tabC, double* tabF1, double* tabF2, double* corner,
@@ -173,12 +173,11 @@ __global__ void k_geometry(Dev g, double* tabC, double* tabF1, double* tabF2, do
   bool pole = (g.pole_lo && j == 0) || (g.pole_hi && j == g.n2);
   double gcov[10], gcon[10], gdet, alpha;
   auto put = [&](double* tab) {
-    for (int f = 0; f < 10; f++) {
-      tab[(G_COV + f) * g.plane + t] = gcov[f];
-      tab[(G_CON + f) * g.plane + t] = gcon[f];
-    }
-    tab[G_DET * g.plane + t] = gdet;
-    tab[G_ALPHA * g.plane + t] = alpha;
+    const double f[G_NF] = {gcov[sidx(0, 0)], gcov[sidx(0, 1)], gcov[sidx(0, 3)], gcov[sidx(3, 3)],
+                            gcov[sidx(1, 1)], gcov[sidx(1, 3)], gcov[sidx(2, 2)], gcon[sidx(2, 2)],
+                            gcon[sidx(0, 0)], gcon[sidx(0, 1)], gdet, alpha,
+                            gcon[sidx(1, 1)], gcon[sidx(3, 3)], gcon[sidx(1, 3)], 0.0};
+    for (int n = 0; n < G_NF; n++) tab[gx(n, g.plane, t)] = f[n];
   };
   metric_point(g.st, xc1, xc2, gcov, gcon, gdet, alpha);
   put(tabC);
@@ -190,7 +189,7 @@ __global__ void k_geometry(Dev g, double* tabC, double* tabF1, double* tabF2, do
     metric_point(g.st, xf1, xf2, gcov, gcon, gdet, alpha);
     corner[t] = gdet;
   } else {
-    for (int f = 0; f < G_NF; f++) tabF2[f * g.plane + t] = 0.0;
+    for (int f = 0; f < G_NF; f++) tabF2[gx(f, g.plane, t)] = 0.0;
     corner[t] = 0.0;
   }
   if (conn) {  // (blocks of a pack have no connection table: nothing there reads it)
@@ -200,7 +199,11 @@ __global__ void k_geometry(Dev g, double* tabC, double* tabF1, double* tabF2, do
   }
   double D[NDG];
   source_metric_point(g.st, xc1, xc2, D);
-  for (int q = 0; q < NDG; q++) dgs[q * g.plane + t] = D[q];
+  for (int q = 0; q < 10; q++) {
+    if (x2_offdiag(q)) continue;
+    dgs[vx(2 * dgs_entry(q), g.plane, t)] = D[q];
+    dgs[vx(2 * dgs_entry(q) + 1, g.plane, t)] = D[10 + q];
+  }
 }
 
 // ------------------------------------------------------------ boundaries --
@@ -291,66 +294,71 @@ __global__ void __launch_bounds__(BLOCK) k_bc(Dev g, double* P) {
   int sk = bc_map(k, g.n3, g.bc[4], g.bc[5], f3);
   if (si == i && sj == j && sk == k) return;  // frozen
   const long src = zid(g, si, sj, sk), dst = zid(g, i, j, k);
-#pragma unroll
-  for (int v = 0; v < NVAR; v++) {
-    double x = P[v * g.nz + src];
-    if (f2 && (v == U2 || v == B2)) x = -x;
-    P[v * g.nz + dst] = x;
+  double p[NVAR];
+  load8(P, g.nz, src, p);
+  if (f2) {
+    p[U2] = -p[U2];
+    p[B2] = -p[B2];
   }
+  store8(P, g.nz, dst, p);
 }
 
 // ----------------------------------------------------------------- fluxes --
 
+// Left and right state of one variable at the face between q[-s] and q[0].
+template <int RECON, typename R>
+__device__ __forceinline__ void recon_face(const double* __restrict__ q, long s, R eps, R& l, R& r) {
+  if (RECON == GRMHD_RECON_DONOR) {
+    l = (R)q[-s];
+    r = (R)q[0];
+  } else if (RECON == GRMHD_RECON_MC) {
+    R m2 = (R)q[-2 * s], m1 = (R)q[-s], p0 = (R)q[0], p1 = (R)q[s];
+    l = mc_left(m2, m1, p0);
+    r = mc_right(m1, p0, p1);
+  } else if (RECON == GRMHD_RECON_VL) {
+    R m2 = (R)q[-2 * s], m1 = (R)q[-s], p0 = (R)q[0], p1 = (R)q[s];
+    l = vl_left(m2, m1, p0);
+    r = vl_right(m1, p0, p1);
+  } else if (RECON == GRMHD_RECON_WENOZ) {
+    R m3 = (R)q[-3 * s], m2 = (R)q[-2 * s], m1 = (R)q[-s], p0 = (R)q[0], p1 = (R)q[s],
+      p2 = (R)q[2 * s];
+    l = wenoz(m3, m2, m1, p0, p1, eps);
+    r = wenoz(p2, p1, p0, m1, m2, eps);
+  } else if (RECON == GRMHD_RECON_MP5) {
+    R m3 = (R)q[-3 * s], m2 = (R)q[-2 * s], m1 = (R)q[-s], p0 = (R)q[0], p1 = (R)q[s],
+      p2 = (R)q[2 * s];
+    l = mp5(m3, m2, m1, p0, p1);
+    r = mp5(p2, p1, p0, m1, m2);
+  } else if (RECON == GRMHD_RECON_PPM) {
+    R m3 = (R)q[-3 * s], m2 = (R)q[-2 * s], m1 = (R)q[-s], p0 = (R)q[0], p1 = (R)q[s],
+      p2 = (R)q[2 * s];
+    R lo, hi;
+    ppm_edges(m3, m2, m1, p0, p1, lo, hi);  // zone i-1: its right edge
+    l = hi;
+    ppm_edges(m2, m1, p0, p1, p2, lo, hi);  // zone i: its left edge
+    r = lo;
+  } else if (RECON == GRMHD_RECON_PPMX) {
+    R m3 = (R)q[-3 * s], m2 = (R)q[-2 * s], m1 = (R)q[-s], p0 = (R)q[0], p1 = (R)q[s],
+      p2 = (R)q[2 * s];
+    R lo, hi;
+    ppmx_edges(m3, m2, m1, p0, p1, lo, hi);  // zone i-1: its right edge
+    l = hi;
+    ppmx_edges(m2, m1, p0, p1, p2, lo, hi);  // zone i: its left edge
+    r = lo;
+  } else {
+    R m3 = (R)q[-3 * s], m2 = (R)q[-2 * s], m1 = (R)q[-s], p0 = (R)q[0], p1 = (R)q[s],
+      p2 = (R)q[2 * s];
+    l = weno5(m3, m2, m1, p0, p1, eps);
+    r = weno5(p2, p1, p0, m1, m2, eps);
+  }
+}
+
+// Left and right states at the face between zones c - s and c.
 template <int RECON, typename R>
 __device__ __forceinline__ void recon_pair(const double* __restrict__ P, long nz, long c, long s,
                                            R eps, R qL[NVAR], R qR[NVAR]) {
 #pragma unroll
-  for (int v = 0; v < NVAR; v++) {
-    const double* q = P + v * nz + c;
-    if (RECON == GRMHD_RECON_DONOR) {
-      qL[v] = (R)q[-s];
-      qR[v] = (R)q[0];
-    } else if (RECON == GRMHD_RECON_MC) {
-      R m2 = (R)q[-2 * s], m1 = (R)q[-s], p0 = (R)q[0], p1 = (R)q[s];
-      qL[v] = mc_left(m2, m1, p0);
-      qR[v] = mc_right(m1, p0, p1);
-    } else if (RECON == GRMHD_RECON_VL) {
-      R m2 = (R)q[-2 * s], m1 = (R)q[-s], p0 = (R)q[0], p1 = (R)q[s];
-      qL[v] = vl_left(m2, m1, p0);
-      qR[v] = vl_right(m1, p0, p1);
-    } else if (RECON == GRMHD_RECON_WENOZ) {
-      R m3 = (R)q[-3 * s], m2 = (R)q[-2 * s], m1 = (R)q[-s], p0 = (R)q[0], p1 = (R)q[s],
-        p2 = (R)q[2 * s];
-      qL[v] = wenoz(m3, m2, m1, p0, p1, eps);
-      qR[v] = wenoz(p2, p1, p0, m1, m2, eps);
-    } else if (RECON == GRMHD_RECON_MP5) {
-      R m3 = (R)q[-3 * s], m2 = (R)q[-2 * s], m1 = (R)q[-s], p0 = (R)q[0], p1 = (R)q[s],
-        p2 = (R)q[2 * s];
-      qL[v] = mp5(m3, m2, m1, p0, p1);
-      qR[v] = mp5(p2, p1, p0, m1, m2);
-    } else if (RECON == GRMHD_RECON_PPM) {
-      R m3 = (R)q[-3 * s], m2 = (R)q[-2 * s], m1 = (R)q[-s], p0 = (R)q[0], p1 = (R)q[s],
-        p2 = (R)q[2 * s];
-      R l, r;
-      ppm_edges(m3, m2, m1, p0, p1, l, r);  // zone i-1: its right edge
-      qL[v] = r;
-      ppm_edges(m2, m1, p0, p1, p2, l, r);  // zone i: its left edge
-      qR[v] = l;
-    } else if (RECON == GRMHD_RECON_PPMX) {
-      R m3 = (R)q[-3 * s], m2 = (R)q[-2 * s], m1 = (R)q[-s], p0 = (R)q[0], p1 = (R)q[s],
-        p2 = (R)q[2 * s];
-      R l, r;
-      ppmx_edges(m3, m2, m1, p0, p1, l, r);  // zone i-1: its right edge
-      qL[v] = r;
-      ppmx_edges(m2, m1, p0, p1, p2, l, r);  // zone i: its left edge
-      qR[v] = l;
-    } else {
-      R m3 = (R)q[-3 * s], m2 = (R)q[-2 * s], m1 = (R)q[-s], p0 = (R)q[0], p1 = (R)q[s],
-        p2 = (R)q[2 * s];
-      qL[v] = weno5(m3, m2, m1, p0, p1, eps);
-      qR[v] = weno5(p2, p1, p0, m1, m2, eps);
-    }
-  }
+  for (int v = 0; v < NVAR; v++) recon_face<RECON, R>(P + vx(v, nz, c), 2 * s, eps, qL[v], qR[v]);
 }
 
 // sqrt(-g) ((FL + FR)/2 - cmax (UR - UL)/2) from the sum of the fluxes and the
@@ -379,9 +387,11 @@ __device__ __forceinline__ void face_llf(const Dev& g, const R qL[NVAR], const R
   const R cmax = fmax(fmax(cl, cr), (R)0);
   // the normal field component's flux is not stored: Flux-CT replaces it by
   // zero and nothing reads it
+  FT f[NVAR];
 #pragma unroll
   for (int v = 0; v < NVAR; v++)
-    if (v != B1 + D - 1) F[v * g.nz + c] = (FT)llf_dens(m.gdet, cmax, FL[v] + FR[v], UR[v] - UL[v]);
+    if (v != B1 + D - 1) f[v] = (FT)llf_dens(m.gdet, cmax, FL[v] + FR[v], UR[v] - UL[v]);
+  store_flux<D>(F, g.nz, c, f);
 }
 
 template <int D>
@@ -399,8 +409,8 @@ __device__ __forceinline__ void flux_face(const Dev& g, const double* __restrict
                                           int j, int k, const double* __restrict__ phi = nullptr) {
   long c = zid(g, i, j, k);
   if (pole_face<D>(g, j)) {
-#pragma unroll
-    for (int v = 0; v < NVAR; v++) F[v * g.nz + c] = (FT)0;
+    const FT zero[NVAR] = {};
+    store_flux<D>(F, g.nz, c, zero);
     return;
   }
   const long s = D == 1 ? 1 : (D == 2 ? (long)g.s1 : g.plane);
@@ -408,7 +418,7 @@ __device__ __forceinline__ void flux_face(const Dev& g, const double* __restrict
   recon_pair<RECON, R>(P, g.nz, c, s, (R)g.weno_eps, qL, qR);
   const long q2 = pid(g, i, j);
   if (phi) {
-    const R bn = (R)(phi[c] / tab[G_DET * g.plane + q2]);
+    const R bn = (R)(phi[c] / tab[gx(G_DET, g.plane, q2)]);
     qL[B1 + D - 1] = bn;
     qR[B1 + D - 1] = bn;
   }
@@ -584,12 +594,12 @@ template <int RECON, typename R>
 __device__ __forceinline__ void zone_edges_x1(const double* __restrict__ P, long nz, long c, R eps,
                                               R left[NVAR], R right[NVAR]) {
 #pragma unroll
-  for (int v = 0; v < NVAR; v++) {
-    const double* q = P + v * nz + c;
-    const R m1 = (R)q[-1], p0 = (R)q[0], p1 = (R)q[1];
-    const R m2 = RECON == GRMHD_RECON_MC ? p0 : (R)q[-2];
-    const R p2 = RECON == GRMHD_RECON_MC ? p0 : (R)q[2];
-    edge_pair<RECON>(m2, m1, p0, p1, p2, eps, left[v], right[v]);
+  for (int a = 0; a < NVAR / 2; a++) {
+    const Pair<double>* q = (const Pair<double>*)P + a * nz + c;
+    const Pair<double> m1 = q[-1], p0 = q[0], p1 = q[1];
+    const Pair<double> m2 = RECON == GRMHD_RECON_MC ? p0 : q[-2], p2 = RECON == GRMHD_RECON_MC ? p0 : q[2];
+    edge_pair<RECON>((R)m2.a, (R)m1.a, (R)p0.a, (R)p1.a, (R)p2.a, eps, left[2 * a], right[2 * a]);
+    edge_pair<RECON>((R)m2.b, (R)m1.b, (R)p0.b, (R)p1.b, (R)p2.b, eps, left[2 * a + 1], right[2 * a + 1]);
   }
 }
 
@@ -625,7 +635,7 @@ __device__ __forceinline__ void sweep_x1(const Dev& g, unsigned wg, int k0, int 
   if (!valid || lane == 0 || i < 0) return;
   const long q2 = pid(g, i, j);
   if (FACE) {
-    const R bn = (R)(ph1[c] / tabF1[G_DET * g.plane + q2]);
+    const R bn = (R)(ph1[c] / tabF1[gx(G_DET, g.plane, q2)]);
     qL[B1] = bn;
     left[B1] = bn;
   }
@@ -655,14 +665,15 @@ template <int RECON, typename R>
 __device__ __forceinline__ void zone_edges(const double* __restrict__ P, long nz, long c, long s, R eps,
                                            R left[NVAR], R* rows) {
 #pragma unroll
-  for (int v = 0; v < NVAR; v++) {
-    const double* q = P + v * nz + c;
-    const R m1 = (R)q[-s], p0 = (R)q[0], p1 = (R)q[s];
-    const R m2 = RECON == GRMHD_RECON_MC ? p0 : (R)q[-2 * s];
-    const R p2 = RECON == GRMHD_RECON_MC ? p0 : (R)q[2 * s];
+  for (int a = 0; a < NVAR / 2; a++) {
+    const Pair<double>* q = (const Pair<double>*)P + a * nz + c;
+    const Pair<double> m1 = q[-s], p0 = q[0], p1 = q[s];
+    const Pair<double> m2 = RECON == GRMHD_RECON_MC ? p0 : q[-2 * s], p2 = RECON == GRMHD_RECON_MC ? p0 : q[2 * s];
     R right;
-    edge_pair<RECON>(m2, m1, p0, p1, p2, eps, left[v], right);
-    rows[v * 64] = right;
+    edge_pair<RECON>((R)m2.a, (R)m1.a, (R)p0.a, (R)p1.a, (R)p2.a, eps, left[2 * a], right);
+    rows[2 * a * 64] = right;
+    edge_pair<RECON>((R)m2.b, (R)m1.b, (R)p0.b, (R)p1.b, (R)p2.b, eps, left[2 * a + 1], right);
+    rows[(2 * a + 1) * 64] = right;
   }
 }
 
@@ -698,8 +709,8 @@ __device__ __forceinline__ void sweep_tile(const Dev& g, unsigned wg, int fs, in
 #pragma unroll
     for (int v = 0; v < NVAR; v++) qL[v] = rd[v * 64 + lane];
     if (pole_face<D>(g, r)) {
-#pragma unroll
-      for (int v = 0; v < NVAR; v++) F[v * g.nz + c] = (FT)0;
+      const FT zero[NVAR] = {};
+      store_flux<D>(F, g.nz, c, zero);
       continue;
     }
     long q2 = D == 2 ? pid(g, i, r) : pid(g, i, o);
@@ -708,7 +719,7 @@ __device__ __forceinline__ void sweep_tile(const Dev& g, unsigned wg, int fs, in
     // the reconstruction and spilled)
     if (D == 3) asm volatile("" : "+v"(q2));
     if (FACE) {
-      const R bn = (R)(ph[c] / tab[G_DET * g.plane + q2]);
+      const R bn = (R)(ph[c] / tab[gx(G_DET, g.plane, q2)]);
       qL[B1 + D - 1] = bn;
       left[B1 + D - 1] = bn;
     }
@@ -729,9 +740,11 @@ __device__ __forceinline__ void emf_edge(const Dev& g, const FT* __restrict__ F1
   const long nz = g.nz, si = 1, sj = g.s1, sk = g.plane;
   bool pole = (g.pole_lo && j == 0) || (g.pole_hi && j == g.n2);
   const FT q = (FT)0.25;
-  FT e3 = q * (F1[B2 * nz + c] + F1[B2 * nz + c - sj] - F2[B1 * nz + c] - F2[B1 * nz + c - si]);
-  FT e2 = q * (F3[B1 * nz + c] + F3[B1 * nz + c - si] - F1[B3 * nz + c] - F1[B3 * nz + c - sk]);
-  FT e1 = q * (F2[B3 * nz + c] + F2[B3 * nz + c - sk] - F3[B2 * nz + c] - F3[B2 * nz + c - sj]);
+  // F1 (B2, B3), F2 (B1, B3), F3 (B1, B2)
+  const Pair<FT> f1 = flux_field(F1, nz, c), f2 = flux_field(F2, nz, c), f3 = flux_field(F3, nz, c);
+  FT e3 = q * (f1.a + flux_field(F1, nz, c - sj).a - f2.a - flux_field(F2, nz, c - si).a);
+  FT e2 = q * (f3.a + flux_field(F3, nz, c - si).a - f1.b - flux_field(F1, nz, c - sk).b);
+  FT e1 = q * (f2.b + flux_field(F2, nz, c - sk).b - f3.b - flux_field(F3, nz, c - sj).b);
   E1[c] = pole ? (FT)0 : e1;
   E2[c] = e2;
   E3[c] = pole ? (FT)0 : e3;
@@ -878,8 +891,7 @@ __global__ void __launch_bounds__(BLOCK) k_cell_emf(Dev g, Box box, const double
   if (!box_index(box, t, i, j, k)) return;
   const long c = zid(g, i, j, k);
   R p[NVAR];
-#pragma unroll
-  for (int v = 0; v < NVAR; v++) p[v] = (R)P[v * g.nz + c];
+  load8(P, g.nz, c, p);
   PointMetric<R> m;
   load_metric<R>(tabC, g.plane, pid(g, i, j), m);
   Fluid<R> f;
@@ -936,14 +948,14 @@ __global__ void __launch_bounds__(BLOCK) k_emf_gs(Dev g, Sched box, const FT* __
     const FT* C = Cd[e];
     const long sa = st[a], sb = st[b];
     const long p00 = c, p10 = c - sa, p01 = c - sb, p11 = c - sa - sb;
-    const FT ea0 = Fa[(B1 + b) * nz + p00], ea1 = Fa[(B1 + b) * nz + p01];
-    const FT eb0 = -Fb[(B1 + a) * nz + p00], eb1 = -Fb[(B1 + a) * nz + p10];
+    const FT ea0 = Fa[fx(a + 1, B1 + b, nz, p00)], ea1 = Fa[fx(a + 1, B1 + b, nz, p01)];
+    const FT eb0 = -Fb[fx(b + 1, B1 + a, nz, p00)], eb1 = -Fb[fx(b + 1, B1 + a, nz, p10)];
     FT ed = (FT)0.25 * (((ea0 + ea1) + eb0) + eb1);
-    const FT fa0 = Fa[RHO * nz + p00], fa1 = Fa[RHO * nz + p01];
+    const FT fa0 = Fa[vx(RHO, nz, p00)], fa1 = Fa[vx(RHO, nz, p01)];
     const FT sa0 = S[p10] + S[p00], sa1 = S[p11] + S[p01];
     const FT dbp = up(fa0, sa0, C[p10] - eb1, C[p00] - eb0);
     const FT dbm = up(fa1, sa1, eb1 - C[p11], eb0 - C[p01]);
-    const FT fb0 = Fb[RHO * nz + p00], fb1 = Fb[RHO * nz + p10];
+    const FT fb0 = Fb[vx(RHO, nz, p00)], fb1 = Fb[vx(RHO, nz, p10)];
     const FT sb0 = S[p01] + S[p00], sb1 = S[p11] + S[p10];
     const FT dap = up(fb0, sb0, C[p01] - ea1, C[p00] - ea0);
     const FT dam = up(fb1, sb1, ea1 - C[p11], ea0 - C[p10]);
@@ -1004,38 +1016,55 @@ __global__ void __launch_bounds__(BLOCK) k_cell_b(Dev g, Box box, const double* 
   int i, j, k;
   if (!box_index(box, t, i, j, k)) return;
   const long c = zid(g, i, j, k);
-  const double gd = tabC[G_DET * g.plane + pid(g, i, j)];
-  P[B1 * g.nz + c] = 0.5 * (ph1[c] + ph1[c + 1]) / gd;
-  P[B2 * g.nz + c] = 0.5 * (ph2[c] + ph2[c + g.s1]) / gd;
-  P[B3 * g.nz + c] = 0.5 * (ph3[c] + ph3[c + g.plane]) / gd;
+  const double gd = tabC[gx(G_DET, g.plane, pid(g, i, j))];
+  P[vx(B1, g.nz, c)] = 0.5 * (ph1[c] + ph1[c + 1]) / gd;
+  P[vx(B2, g.nz, c)] = 0.5 * (ph2[c] + ph2[c + g.s1]) / gd;
+  P[vx(B3, g.nz, c)] = 0.5 * (ph3[c] + ph3[c + g.plane]) / gd;
 }
 
-// Rebuild the B components of interior-face fluxes from the EMFs (as the
-// update does on the fly); used by the flux inspection entry point only.
-template <typename FT>
-__global__ void k_ct_fluxes(Dev g, Box box, FT* F1, FT* F2, FT* F3, const FT* E1, const FT* E2,
-                            const FT* E3) {
+// The fluxes of interior faces as the caller's array [3][8][padded], their B
+// components rebuilt from the EMFs (as the update does on the fly); used by
+// the flux inspection entry point only.
+__global__ void k_export_fluxes(Dev g, Box box, const double* F1, const double* F2, const double* F3, const double* E1,
+                                const double* E2, const double* E3, double* out) {
   long t = blockIdx.x * (long)blockDim.x + threadIdx.x;
   int i, j, k;
   if (!box_index(box, t, i, j, k)) return;
   long c = zid(g, i, j, k);
   const long nz = g.nz, si = 1, sj = g.s1, sk = g.plane;
-  const FT h = (FT)0.5;
-  if (j < g.n2 && k < g.n3) {
-    F1[B1 * nz + c] = (FT)0;
-    F1[B2 * nz + c] = h * (E3[c] + E3[c + sj]);
-    F1[B3 * nz + c] = -h * (E2[c] + E2[c + sk]);
-  }
-  if (i < g.n1 && k < g.n3) {
-    F2[B1 * nz + c] = -h * (E3[c] + E3[c + si]);
-    F2[B2 * nz + c] = (FT)0;
-    F2[B3 * nz + c] = h * (E1[c] + E1[c + sk]);
-  }
-  if (i < g.n1 && j < g.n2) {
-    F3[B1 * nz + c] = h * (E2[c] + E2[c + si]);
-    F3[B2 * nz + c] = -h * (E1[c] + E1[c + sj]);
-    F3[B3 * nz + c] = (FT)0;
-  }
+  double f[5];
+  auto put = [&](int d, const double* F, double b1, double b2, double b3) {
+    double* o = out + (d - 1) * NVAR * nz + c;
+    load_flux5(F, nz, c, f);
+    for (int v = 0; v < 5; v++) o[v * nz] = f[v];
+    o[B1 * nz] = b1;
+    o[B2 * nz] = b2;
+    o[B3 * nz] = b3;
+  };
+  if (j < g.n2 && k < g.n3) put(1, F1, 0.0, 0.5 * (E3[c] + E3[c + sj]), -0.5 * (E2[c] + E2[c + sk]));
+  if (i < g.n1 && k < g.n3) put(2, F2, -0.5 * (E3[c] + E3[c + si]), 0.0, 0.5 * (E1[c] + E1[c + sk]));
+  if (i < g.n1 && j < g.n2) put(3, F3, 0.5 * (E2[c] + E2[c + si]), -0.5 * (E1[c] + E1[c + sj]), 0.0);
+}
+
+// The caller's prims [8][padded] into the state (and, where given, the stage
+// buffer, which carries the same frozen ghosts), and the state back out.
+__global__ void __launch_bounds__(BLOCK) k_load_state(long nz, const double* __restrict__ src, double* __restrict__ P,
+                                                      double* __restrict__ P1) {
+  const long c = blockIdx.x * (long)BLOCK + threadIdx.x;
+  if (c >= nz) return;
+  double p[NVAR];
+#pragma unroll
+  for (int v = 0; v < NVAR; v++) p[v] = src[v * nz + c];
+  store8(P, nz, c, p);
+  if (P1) store8(P1, nz, c, p);
+}
+__global__ void __launch_bounds__(BLOCK) k_read_state(long nz, const double* __restrict__ P, double* __restrict__ dst) {
+  const long c = blockIdx.x * (long)BLOCK + threadIdx.x;
+  if (c >= nz) return;
+  double p[NVAR];
+  load8(P, nz, c, p);
+#pragma unroll
+  for (int v = 0; v < NVAR; v++) dst[v * nz + c] = p[v];
 }
 
 #include "inversion.hpp"
@@ -1223,7 +1252,12 @@ __device__ __forceinline__ void geometric_source(const double p[NVAR], const Flu
                                                  double gam, double S[2]) {
   double D[NDG];
 #pragma unroll
-  for (int r = 0; r < NDG; r++) D[r] = x2_offdiag(r % 10) ? 0.0 : dgs[r * plane + q];
+  for (int r = 0; r < 10; r++) {
+    Pair<double> x{0.0, 0.0};
+    if (!x2_offdiag(r)) x = ((const Pair<double>*)dgs)[dgs_entry(r) * plane + q];
+    D[r] = x.a;
+    D[10 + r] = x.b;
+  }
   metric_source(p, f, m, gam, D, S);
 }
 
@@ -1292,8 +1326,7 @@ __device__ __forceinline__ void update_zone(const Dev& g, const double* __restri
   const long c = zid(g, i, j, k), nz = g.nz, si = 1, sj = g.s1, sk = g.plane;
   const long q2 = pid(g, i, j);
   double p[NVAR];
-#pragma unroll
-  for (int v = 0; v < NVAR; v++) p[v] = Pin[v * nz + c];
+  load8(Pin, nz, c, p);
   PointMetric<double> m;
   load_metric<double>(tabC, g.plane, q2, m);
   Fluid<double> f;
@@ -1303,12 +1336,20 @@ __device__ __forceinline__ void update_zone(const Dev& g, const double* __restri
   {
     double S[2];
     geometric_source(p, f, m, dgs, g.plane, q2, g.gam, S);
+    double lo[5], hi[5];
+    load_flux5(F1, nz, c, lo);
+    load_flux5(F1, nz, c + si, hi);
+#pragma unroll
+    for (int v = 0; v < 5; v++) L[v] = (hi[v] - lo[v]) * g.idx1;
+    load_flux5(F2, nz, c, lo);
+    load_flux5(F2, nz, c + sj, hi);
+#pragma unroll
+    for (int v = 0; v < 5; v++) L[v] = L[v] + (hi[v] - lo[v]) * g.idx2;
+    load_flux5(F3, nz, c, lo);
+    load_flux5(F3, nz, c + sk, hi);
 #pragma unroll
     for (int v = 0; v < 5; v++) {
-      double d1 = ((double)F1[v * nz + c + si] - (double)F1[v * nz + c]) * g.idx1;
-      double d2 = ((double)F2[v * nz + c + sj] - (double)F2[v * nz + c]) * g.idx2;
-      double d3 = ((double)F3[v * nz + c + sk] - (double)F3[v * nz + c]) * g.idx3;
-      L[v] = -((d1 + d2) + d3);
+      L[v] = -(L[v] + (hi[v] - lo[v]) * g.idx3);
       if (v == U1 || v == U2) L[v] += S[v - U1];
     }
     if constexpr (!FACE) {
@@ -1339,7 +1380,7 @@ __device__ __forceinline__ void update_zone(const Dev& g, const double* __restri
 #pragma unroll
     for (int v = 0; v < NVAR; v++) {
       const double dtl = dt * L[v];
-      const long o = v * nz + c;
+      const long o = vx(v, nz, c);
       if constexpr (STAGE == 1) {
         U[v] = U0[v] + SSP54_C1 * dtl;
         R0[o] = U0[v];
@@ -1363,16 +1404,18 @@ __device__ __forceinline__ void update_zone(const Dev& g, const double* __restri
     double U0[NVAR];
     prim_to_flux(p, f, m, g.gam, 0, U0);
     const double h = INTEG == GRMHD_INTEG_PC ? 0.5 * dt : dt;
+    double reg[NVAR];
 #pragma unroll
     for (int v = 0; v < NVAR; v++) {
       U[v] = U0[v] + h * L[v];
-      if (INTEG == GRMHD_INTEG_SSPRK2) V[v * nz + c] = 0.5 * (U0[v] + U[v]);
-      if (INTEG == GRMHD_INTEG_PC) V[v * nz + c] = U0[v];
+      reg[v] = INTEG == GRMHD_INTEG_PC ? U0[v] : 0.5 * (U0[v] + U[v]);
     }
+    if (INTEG == GRMHD_INTEG_SSPRK2 || INTEG == GRMHD_INTEG_PC) store8(V, nz, c, reg);
   } else {
+    double reg[NVAR];
+    load8(V, nz, c, reg);
 #pragma unroll
-    for (int v = 0; v < NVAR; v++)
-      U[v] = INTEG == GRMHD_INTEG_PC ? V[v * nz + c] + dt * L[v] : V[v * nz + c] + 0.5 * (dt * L[v]);
+    for (int v = 0; v < NVAR; v++) U[v] = reg[v] + (INTEG == GRMHD_INTEG_PC ? dt * L[v] : 0.5 * (dt * L[v]));
   }
   if constexpr (FACE) {  // face-centred CT: the zone's field is the mean of its new faces
     U[B1] = 0.5 * (ph1[c] + ph1[c + si]);
@@ -1380,14 +1423,12 @@ __device__ __forceinline__ void update_zone(const Dev& g, const double* __restri
     U[B3] = 0.5 * (ph3[c] + ph3[c + sk]);
   }
   if constexpr (MODE == U_STORE) {  // the implicit solver recovers the prims in its own pass
-#pragma unroll
-    for (int v = 0; v < NVAR; v++) ustar[v * nz + c] = U[v];
+    store8(ustar, nz, c, U);
     return;
   }
   double out[NVAR];
   int bad = invert(g, m, U, p, out);
-#pragma unroll
-  for (int v = 0; v < NVAR; v++) Pout[v * nz + c] = out[v];
+  store8(Pout, nz, c, out);
   if (flags) flags[c] = (unsigned char)bad;
   if (MODE == U_PROVISIONAL) {
     mark[c] = (unsigned char)bad;
@@ -1461,25 +1502,23 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(3, 8
   if (in) {
     const long c = zid(g, i, j, k), nz = g.nz;
     double out[NVAR];
-#pragma unroll
-    for (int v = 0; v < NVAR; v++) out[v] = Pout[v * nz + c];
+    load8(Pout, nz, c, out);
     PointMetric<double> m;
     load_metric<double>(tabC, g.plane, pid(g, i, j), m);
     const int fl = apply_floors(g, m, g.x1min + (i + 0.5) * g.dx1, out);
     if (fl) {
-#pragma unroll
-      for (int v = 0; v < NVAR; v++) Pout[v * nz + c] = out[v];
+      store8(Pout, nz, c, out);
       if (STAGE == 1) {
         double p[NVAR], U0[NVAR], U1[NVAR];
-#pragma unroll
-        for (int v = 0; v < NVAR; v++) p[v] = Pin[v * nz + c];
+        load8(Pin, nz, c, p);
         Fluid<double> f0, f1;
         fluid_state(p, m, f0);
         prim_to_flux(p, f0, m, g.gam, 0, U0);
         fluid_state(out, m, f1);
         prim_to_flux(out, f1, m, g.gam, 0, U1);
 #pragma unroll
-        for (int v = 0; v < NVAR; v++) V[v * nz + c] = 0.5 * (U0[v] + U1[v]);
+        for (int v = 0; v < NVAR; v++) U1[v] = 0.5 * (U0[v] + U1[v]);
+        store8(V, nz, c, U1);
       }
       if (MODE == U_PROVISIONAL) {
         if (mark[c] == 0) {
@@ -1518,16 +1557,12 @@ k_implicit(Dev g, Sched box, const double* __restrict__ Pin, const double* __res
   if (in) {
     const long c = zid(g, i, j, k), nz = g.nz;
     double U[NVAR], p[NVAR], out[NVAR];
-#pragma unroll
-    for (int v = 0; v < NVAR; v++) {
-      U[v] = ustar[v * nz + c];
-      p[v] = Pin[v * nz + c];
-    }
+    load8(ustar, nz, c, U);
+    load8(Pin, nz, c, p);
     PointMetric<double> m;
     load_metric<double>(tabC, g.plane, pid(g, i, j), m);
     const int bad = invert_implicit(g, m, U, p, out, jac + threadIdx.x);
-#pragma unroll
-    for (int v = 0; v < NVAR; v++) Pout[v * nz + c] = out[v];
+    store8(Pout, nz, c, out);
     if (flags) flags[c] = (unsigned char)bad;
     if (bad) atomicAdd(&fails[C_FAILS], 1ull);
     if (RATE) r = zone_rate(g, out, m);
@@ -1554,8 +1589,7 @@ __global__ void __launch_bounds__(BLOCK) k_dt_partial(Dev g, Box box, const doub
     box_index(box, t, i, j, k);
     long c = zid(g, i, j, k);
     double p[NVAR];
-#pragma unroll
-    for (int v = 0; v < NVAR; v++) p[v] = P[v * g.nz + c];
+    load8(P, g.nz, c, p);
     PointMetric<double> m;
     load_metric<double>(tabC, g.plane, pid(g, i, j), m);
     s = fmax(s, zone_rate(g, p, m));
@@ -1602,7 +1636,7 @@ __global__ void __launch_bounds__(BLOCK) k_divb_partial(Dev g, Box box, const do
     box_index(box, t, i, j, k);
     const long nz = g.nz;
     auto ub = [&](int d, int a, int b, int cc) {
-      return tabC[G_DET * g.plane + pid(g, a, b)] * P[(B1 + d) * nz + zid(g, a, b, cc)];
+      return tabC[gx(G_DET, g.plane, pid(g, a, b))] * P[vx(B1 + d, nz, zid(g, a, b, cc))];
     };
     double d1 = (ub(0, i, j, k) + ub(0, i, j - 1, k) + ub(0, i, j, k - 1) + ub(0, i, j - 1, k - 1)) -
                 (ub(0, i - 1, j, k) + ub(0, i - 1, j - 1, k) + ub(0, i - 1, j, k - 1) +
@@ -1844,7 +1878,7 @@ size_t carve(grmhd_ctx* c, char* base, const grmhd_grid* g, const grmhd_params* 
   double* tabF2 = cv.take<double>(base, G_NF * plane);
   double* corner = cv.take<double>(base, plane);
   double* conn = cv.take<double>(base, NCONN * plane);
-  double* dgs = cv.take<double>(base, NDG * plane);
+  double* dgs = cv.take<double>(base, NDGT * plane);
   double* pmax = cv.take<double>(base, MAX_PARTIALS);
   double* psum = cv.take<double>(base, MAX_PARTIALS);
   double* result = cv.take<double>(base, 8);
@@ -2491,12 +2525,9 @@ int grmhd_load_prims(grmhd_ctx* c, const double* d_prims) {
   if (!c || !d_prims) return GRMHD_E_ARG;
   c->rate_ready = false;
   c->ghosts_valid = false;
-  size_t bytes = sizeof(double) * NVAR * c->dev.nz;
-  if (hipMemcpyAsync(c->P, d_prims, bytes, hipMemcpyDeviceToDevice, c->stream) != hipSuccess)
-    return GRMHD_E_HIP;
-  // the stage buffer carries the same (frozen) ghosts
-  if (hipMemcpyAsync(c->P1, d_prims, bytes, hipMemcpyDeviceToDevice, c->stream) != hipSuccess)
-    return GRMHD_E_HIP;
+  k_load_state<<<blocks_for(c->dev.nz), BLOCK, 0, c->stream>>>(c->dev.nz, d_prims, c->P, c->P1);
+  int rc = hip_check();
+  if (rc) return rc;
   // face-centred CT: the zones' field is their faces' mean
   if (c->faces_loaded) return cell_b_from_faces(c);
   return GRMHD_OK;
@@ -2505,12 +2536,8 @@ int grmhd_load_prims(grmhd_ctx* c, const double* d_prims) {
 int grmhd_load_extended(grmhd_ctx* c, const double* d_extra) {
   if (!c || !d_extra) return GRMHD_E_ARG;
   if (!c->params.egrmhd) return GRMHD_E_STATE;
-  const size_t bytes = sizeof(double) * NXV * c->dev.nz;
-  // the stage buffer carries the same (frozen) ghosts
-  if (hipMemcpyAsync(c->X, d_extra, bytes, hipMemcpyDeviceToDevice, c->stream) != hipSuccess ||
-      hipMemcpyAsync(c->X1, d_extra, bytes, hipMemcpyDeviceToDevice, c->stream) != hipSuccess)
-    return GRMHD_E_HIP;
-  return GRMHD_OK;
+  k_load_extra<<<blocks_for(c->dev.nz), BLOCK, 0, c->stream>>>(c->dev.nz, d_extra, c->X, c->X1);
+  return hip_check();
 }
 
 int grmhd_get_extended(grmhd_ctx* c, double* d_extra) {
@@ -2518,10 +2545,8 @@ int grmhd_get_extended(grmhd_ctx* c, double* d_extra) {
   if (!c->params.egrmhd) return GRMHD_E_STATE;
   int rc;
   if ((rc = launch(c, T_BC, k_bc_extra, blocks_for(ghost_count(c->dev)), c->dev, c->X))) return rc;
-  if (hipMemcpyAsync(d_extra, c->X, sizeof(double) * NXV * c->dev.nz, hipMemcpyDeviceToDevice, c->stream) !=
-      hipSuccess)
-    return GRMHD_E_HIP;
-  return GRMHD_OK;
+  k_read_extra<<<blocks_for(c->dev.nz), BLOCK, 0, c->stream>>>(c->dev.nz, (const double*)c->X, d_extra);
+  return hip_check();
 }
 
 int grmhd_load_faces(grmhd_ctx* c, const double* d_faces) {
@@ -2618,10 +2643,8 @@ int grmhd_get_prims(grmhd_ctx* c, double* d_out) {
   if (!c || !d_out) return GRMHD_E_ARG;
   int rc;
   if ((rc = ensure_ghosts(c))) return rc;
-  if (hipMemcpyAsync(d_out, c->P, sizeof(double) * NVAR * c->dev.nz, hipMemcpyDeviceToDevice,
-                     c->stream) != hipSuccess)
-    return GRMHD_E_HIP;
-  return GRMHD_OK;
+  k_read_state<<<blocks_for(c->dev.nz), BLOCK, 0, c->stream>>>(c->dev.nz, (const double*)c->P, d_out);
+  return hip_check();
 }
 
 int grmhd_divb(grmhd_ctx* c, double* d_divb, double* max_out, double* mean_out) {
@@ -2719,16 +2742,10 @@ int grmhd_fluxes(grmhd_ctx* c, const double* d_prims, double* d_flux) {
   if ((rc = stage_fluxes<double, double>(c, c->P))) return rc;
   const Dev& g = c->dev;
   Box be = make_box(0, g.n1, 0, g.n2, 0, g.n3);
-  k_ct_fluxes<double><<<blocks_for(be.count()), BLOCK, 0, c->stream>>>(
-      g, be, (double*)c->F[0], (double*)c->F[1], (double*)c->F[2], (const double*)c->E[0],
-      (const double*)c->E[1], (const double*)c->E[2]);
-  if ((rc = hip_check())) return rc;
-  size_t bytes = sizeof(double) * NVAR * g.nz;
-  for (int d = 0; d < 3; d++)
-    if (hipMemcpyAsync(d_flux + d * NVAR * g.nz, c->F[d], bytes, hipMemcpyDeviceToDevice, c->stream) !=
-        hipSuccess)
-      return GRMHD_E_HIP;
-  return GRMHD_OK;
+  k_export_fluxes<<<blocks_for(be.count()), BLOCK, 0, c->stream>>>(
+      g, be, (const double*)c->F[0], (const double*)c->F[1], (const double*)c->F[2], (const double*)c->E[0],
+      (const double*)c->E[1], (const double*)c->E[2], d_flux);
+  return hip_check();
 }
 
 const char* grmhd_strerror(int code) {
@@ -2816,9 +2833,8 @@ int step_vjp(grmhd_ctx* c, const VjpCarve& w, const double* d_in, double dt, con
   // interior zones only (the inversion's adjoint).
   bool frozen = false;
   for (int f = 0; f < 6; f++) frozen = frozen || c->grid.bc[f] == GRMHD_BC_FROZEN;
-  if (hipMemcpyAsync(w.A, d_in, bytes, hipMemcpyDeviceToDevice, c->stream) != hipSuccess ||
-      (frozen && hipMemcpyAsync(w.B, d_in, bytes, hipMemcpyDeviceToDevice, c->stream) != hipSuccess) ||
-      hipMemsetAsync(w.GZ, 0, sizeof(double) * nz, c->stream) != hipSuccess ||
+  k_load_state<<<blocks_for(nz), BLOCK, 0, c->stream>>>(nz, d_in, w.A, frozen ? w.B : nullptr);
+  if (hip_check() != GRMHD_OK || hipMemsetAsync(w.GZ, 0, sizeof(double) * nz, c->stream) != hipSuccess ||
       hipMemsetAsync(d_gin, 0, bytes, c->stream) != hipSuccess)
     return GRMHD_E_HIP;
   for (int d = 0; d < 3; d++)
@@ -2937,7 +2953,6 @@ struct grmhd_pack {
   hipStream_t stream;
   int nb;
   std::vector<BlockView> views;
-  std::vector<long> prim_off;  // offset (doubles) of each block in the packed prims
   long prim_total;
   BlockView* d_views;
   int* d_pre;
@@ -2967,11 +2982,9 @@ size_t pack_carve(int nb, const int* n, char* base, grmhd_pack* pk) {
     v.tabF1 = cv.take<double>(base, G_NF * plane);
     v.tabF2 = cv.take<double>(base, G_NF * plane);
     v.corner = cv.take<double>(base, plane);
-    v.dgs = cv.take<double>(base, NDG * plane);
-    if (pk) {
-      pk->views.push_back(v);
-      pk->prim_off.push_back(prim_total);
-    }
+    v.dgs = cv.take<double>(base, NDGT * plane);
+    v.off = prim_total;
+    if (pk) pk->views.push_back(v);
     prim_total += NVAR * nz;
   }
   BlockView* dv = cv.take<BlockView>(base, nb);
@@ -3009,6 +3022,12 @@ int pack_upload(grmhd_pack* pk) {
       hipMemcpy(pk->d_pre, pre.data(), sizeof(int) * pre.size(), hipMemcpyHostToDevice) != hipSuccess)
     return GRMHD_E_HIP;
   return GRMHD_OK;
+}
+
+// Blocks by chunks of the largest block's padded zones.
+dim3 pack_zone_grid(const grmhd_pack* pk) {
+  const unsigned chunks = ((unsigned)pk->max_nz + BLOCK - 1) / BLOCK;
+  return dim3((unsigned)pk->nb, chunks < 65535u ? chunks : 65535u);
 }
 
 template <int RECON>
@@ -3155,14 +3174,9 @@ int grmhd_pack_set_tiles(grmhd_pack* pk, int n, int t1, int t2, int t3) {
 
 int grmhd_pack_load_prims(grmhd_pack* pk, const double* d_prims) {
   if (!pk || !d_prims) return GRMHD_E_ARG;
-  for (int b = 0; b < pk->nb; b++) {
-    size_t bytes = sizeof(double) * NVAR * pk->views[b].g.nz;
-    const double* src = d_prims + pk->prim_off[b];
-    if (hipMemcpyAsync(pk->views[b].P, src, bytes, hipMemcpyDeviceToDevice, pk->stream) != hipSuccess ||
-        hipMemcpyAsync(pk->views[b].P1, src, bytes, hipMemcpyDeviceToDevice, pk->stream) != hipSuccess)
-      return GRMHD_E_HIP;
-  }
-  return GRMHD_OK;
+  const dim3 grid = pack_zone_grid(pk);
+  k_pack_load<<<grid, BLOCK, 0, pk->stream>>>(pk->d_views, d_prims);
+  return hip_check();
 }
 
 int grmhd_pack_step(grmhd_pack* pk, double dt) {
@@ -3178,13 +3192,9 @@ int grmhd_pack_step(grmhd_pack* pk, double dt) {
 
 int grmhd_pack_get_prims(grmhd_pack* pk, double* d_out) {
   if (!pk || !d_out) return GRMHD_E_ARG;
-  for (int b = 0; b < pk->nb; b++) {
-    size_t bytes = sizeof(double) * NVAR * pk->views[b].g.nz;
-    if (hipMemcpyAsync(d_out + pk->prim_off[b], pk->views[b].P, bytes, hipMemcpyDeviceToDevice, pk->stream) !=
-        hipSuccess)
-      return GRMHD_E_HIP;
-  }
-  return GRMHD_OK;
+  const dim3 grid = pack_zone_grid(pk);
+  k_pack_read<<<grid, BLOCK, 0, pk->stream>>>(pk->d_views, d_out);
+  return hip_check();
 }
 
 int grmhd_pack_get_status(grmhd_pack* pk, long long* n_inv_fail) {

@@ -21,6 +21,7 @@ struct BlockView {
   double *tabC, *tabF1, *tabF2, *corner, *dgs;
   int t1, t2, t3;  // tile shape
   int o1, o2, o3;  // offset of the block's first interior zone in the global grid
+  long off;        // offset (doubles) of the block in the packed prims
 };
 
 enum { PH_FLUX = 0, PH_EMF = 1, PH_UPDATE = 2, PH_N = 3 };
@@ -206,10 +207,37 @@ __global__ void __launch_bounds__(BLOCK) k_pack_exchange(const BlockView* __rest
   const long sidx = zid(src.g, gi - src.o1, gj - src.o2, gk - src.o3), didx = zid(b.g, i, j, k);
   const double* Ps = stage == 1 ? src.P : src.P1;
   double* Pd = stage == 1 ? b.P : b.P1;
+  double p[NVAR];
+  load8(Ps, src.g.nz, sidx, p);
+  if (f2) {
+    p[U2] = -p[U2];
+    p[B2] = -p[B2];
+  }
+  store8(Pd, b.g.nz, didx, p);
+}
+
+// The caller's packed prims (each block [8][padded], at its offset) into the
+// blocks' states and stage buffers, and back.  Grid: x over blocks, y over the
+// padded zones of the largest block.
+__global__ void __launch_bounds__(BLOCK) k_pack_load(const BlockView* __restrict__ views,
+                                                     const double* __restrict__ packed) {
+  const BlockView& b = views[blockIdx.x];
+  const long nz = b.g.nz;
+  for (long c = blockIdx.y * (long)BLOCK + threadIdx.x; c < nz; c += gridDim.y * (long)BLOCK) {
+    double p[NVAR];
 #pragma unroll
-  for (int v = 0; v < NVAR; v++) {
-    double x = Ps[v * src.g.nz + sidx];
-    if (f2 && (v == U2 || v == B2)) x = -x;
-    Pd[v * b.g.nz + didx] = x;
+    for (int v = 0; v < NVAR; v++) p[v] = packed[b.off + v * nz + c];
+    store8(b.P, nz, c, p);
+    store8(b.P1, nz, c, p);
+  }
+}
+__global__ void __launch_bounds__(BLOCK) k_pack_read(const BlockView* __restrict__ views, double* __restrict__ packed) {
+  const BlockView& b = views[blockIdx.x];
+  const long nz = b.g.nz;
+  for (long c = blockIdx.y * (long)BLOCK + threadIdx.x; c < nz; c += gridDim.y * (long)BLOCK) {
+    double p[NVAR];
+    load8(b.P, nz, c, p);
+#pragma unroll
+    for (int v = 0; v < NVAR; v++) packed[b.off + v * nz + c] = p[v];
   }
 }

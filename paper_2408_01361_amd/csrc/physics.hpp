@@ -35,35 +35,128 @@ struct PointMetric {
   R alpha;
 };
 
-// Layout of a per-location geometry table: field-major over the padded
-// (x1, x2) plane, so consecutive x1 columns are consecutive addresses.
-enum { G_COV = 0, G_CON = 10, G_DET = 20, G_ALPHA = 21, G_NF = 22 };
+// Two neighbouring values, loaded and stored as one.  A vector memory
+// instruction takes a CU 16 cycles for its 64 lanes whether they move 4, 8 or
+// 16 bytes each (measured: 31 B per cycle with 8 bytes a lane, 63 with 16),
+// and the flux kernel issued 60 of them per face row, more cycles than its
+// arithmetic; so everything the kernels read together is stored in pairs.
+template <typename T>
+struct alignas(2 * sizeof(T)) Pair {
+  T a, b;
+};
+
+// State arrays (prims, stage registers, targets): variables 2q and 2q+1 of a
+// zone next to each other, the pairs of one q over all nz padded zones.
+__host__ __device__ constexpr long vx(int v, long nz, long c) { return ((long)(v >> 1) * nz + c) * 2 + (v & 1); }
+
+template <typename R>
+__device__ __forceinline__ void load8(const double* __restrict__ P, long nz, long c, R p[NVAR]) {
+  const Pair<double>* q = (const Pair<double>*)P;
+#pragma unroll
+  for (int a = 0; a < NVAR / 2; a++) {
+    const Pair<double> x = q[a * nz + c];
+    p[2 * a] = (R)x.a;
+    p[2 * a + 1] = (R)x.b;
+  }
+}
+__device__ __forceinline__ void store8(double* __restrict__ P, long nz, long c, const double p[NVAR]) {
+  Pair<double>* q = (Pair<double>*)P;
+#pragma unroll
+  for (int a = 0; a < NVAR / 2; a++) q[a * nz + c] = Pair<double>{p[2 * a], p[2 * a + 1]};
+}
+
+// Flux arrays of direction d = 1..3: the pairs (rho, u) and (u1, u2), then the
+// two transverse field components, then u3 alone (the normal field has no
+// flux).
+__host__ __device__ constexpr int fslot(int d, int v) { return v - B1 < d - 1 ? v - B1 : v - B1 - 1; }
+__host__ __device__ constexpr long fx(int d, int v, long nz, long c) {
+  return v < U3 ? vx(v, nz, c) : (v == U3 ? 6 * nz + c : 4 * nz + 2 * c + fslot(d, v));
+}
+template <int D, typename FT>
+__device__ __forceinline__ void store_flux(FT* __restrict__ F, long nz, long c, const FT f[NVAR]) {
+  Pair<FT>* q = (Pair<FT>*)F;
+  q[c] = Pair<FT>{f[RHO], f[UU]};
+  q[nz + c] = Pair<FT>{f[U1], f[U2]};
+  q[2 * nz + c] = Pair<FT>{f[D == 1 ? B2 : B1], f[D == 3 ? B2 : B3]};
+  F[6 * nz + c] = f[U3];
+}
+// The five hydro components; the field pair.
+template <typename FT>
+__device__ __forceinline__ void load_flux5(const FT* __restrict__ F, long nz, long c, double f[5]) {
+  const Pair<FT>* q = (const Pair<FT>*)F;
+  const Pair<FT> x = q[c], y = q[nz + c];
+  f[RHO] = (double)x.a;
+  f[UU] = (double)x.b;
+  f[U1] = (double)y.a;
+  f[U2] = (double)y.b;
+  f[U3] = (double)F[6 * nz + c];
+}
+template <typename FT>
+__device__ __forceinline__ Pair<FT> flux_field(const FT* __restrict__ F, long nz, long c) {
+  return ((const Pair<FT>*)F)[2 * nz + c];
+}
+
+// Fields of a per-location geometry table: the entries that are not zero in
+// the library's two spacetimes (below), ordered so that what is read together
+// is paired; pairs over the padded (x1, x2) plane, so consecutive x1 columns
+// are consecutive addresses.
+enum {
+  G_GTT, G_GT1, G_GT3, G_G33, G_G11, G_G13, G_G22, G_C22, G_CTT, G_CT1, G_DET, G_ALPHA, G_C11, G_C33, G_C13, G_SPARE,
+  G_NF
+};
+__host__ __device__ constexpr long gx(int f, long plane, long q) { return vx(f, plane, q); }
 enum { NCONN = 40 };  // Gamma^l_{mn}, m <= n
 // Metric-derivative table of the geometric source: for nu = 1, 2 (row nu - 1)
 // and each symmetric index s = (k, l), d_nu g_kl / 2 if k = l and d_nu g_kl if
 // k < l (the pair (l, k) folded in), so that sum_s T^s D[s] = T^{kl} d_nu g_kl / 2.
-enum { NDG = 20 };
+// In the table the two derivatives of each of the seven entries that are not
+// identically zero are a pair (dgs_entry gives its index).
+enum { NDG = 20, NDGT = 14 };
 
 // Both spacetimes of the library (flat space, and Kerr in modified
-// Kerr-Schild coordinates) have g_{2 mu} = g^{2 mu} = 0 for mu != 2: x2 is
-// orthogonal to the other coordinates, and the tables hold exact zeros
-// there.  Those six entries are set to the constant zero rather than loaded,
-// which gives the same values (and the same rounding of every expression
-// that reads them) while keeping them out of registers.
+// Kerr-Schild coordinates) have g_{2 mu} = g^{2 mu} = 0 for mu != 2 -- x2 is
+// orthogonal to the other coordinates -- and g^{t3} = 0.  Those seven entries
+// are the constant zero rather than table fields, which gives the same values
+// (and the same rounding of every expression that reads them) while keeping
+// them out of registers.
 __host__ __device__ constexpr bool x2_offdiag(int f) {
   return f == sidx(0, 2) || f == sidx(1, 2) || f == sidx(2, 3);
+}
+
+__host__ __device__ constexpr int dgs_entry(int s) {
+  return s == sidx(0, 0) ? 0 : s == sidx(0, 1) ? 1 : s == sidx(0, 3) ? 2 : s == sidx(1, 1) ? 3
+         : s == sidx(1, 3) ? 4 : s == sidx(2, 2) ? 5 : 6;
 }
 
 template <typename R>
 __device__ __forceinline__ void load_metric(const double* __restrict__ tab, long plane, long q,
                                    PointMetric<R>& m) {
+  const Pair<double>* t = (const Pair<double>*)tab;
+  auto at = [&](int f) { return t[(f >> 1) * plane + q]; };
 #pragma unroll
-  for (int f = 0; f < 10; f++) {
-    m.gcov[f] = x2_offdiag(f) ? (R)0 : (R)tab[(G_COV + f) * plane + q];
-    m.gcon[f] = x2_offdiag(f) ? (R)0 : (R)tab[(G_CON + f) * plane + q];
-  }
-  m.gdet = (R)tab[G_DET * plane + q];
-  m.alpha = (R)tab[G_ALPHA * plane + q];
+  for (int f = 0; f < 10; f++) m.gcov[f] = m.gcon[f] = (R)0;
+  Pair<double> x = at(G_GTT);
+  m.gcov[sidx(0, 0)] = (R)x.a;
+  m.gcov[sidx(0, 1)] = (R)x.b;
+  x = at(G_GT3);
+  m.gcov[sidx(0, 3)] = (R)x.a;
+  m.gcov[sidx(3, 3)] = (R)x.b;
+  x = at(G_G11);
+  m.gcov[sidx(1, 1)] = (R)x.a;
+  m.gcov[sidx(1, 3)] = (R)x.b;
+  x = at(G_G22);
+  m.gcov[sidx(2, 2)] = (R)x.a;
+  m.gcon[sidx(2, 2)] = (R)x.b;
+  x = at(G_CTT);
+  m.gcon[sidx(0, 0)] = (R)x.a;
+  m.gcon[sidx(0, 1)] = (R)x.b;
+  x = at(G_DET);
+  m.gdet = (R)x.a;
+  m.alpha = (R)x.b;
+  x = at(G_C11);
+  m.gcon[sidx(1, 1)] = (R)x.a;
+  m.gcon[sidx(3, 3)] = (R)x.b;
+  m.gcon[sidx(1, 3)] = (R)tab[gx(G_C13, plane, q)];
 }
 
 template <typename R>
@@ -450,8 +543,7 @@ __device__ __forceinline__ void mc_right_grad(double l, double c, double r, doub
 //   * the face metric holds only the entries that are not identically zero
 //     in the library's two spacetimes: flat space and Kerr in modified
 //     Kerr-Schild coordinates both have g_{2 mu} = g^{2 mu} = 0 for mu != 2
-//     (x2 is orthogonal to the other coordinates), so those table entries,
-//     exactly zero, are never read and their products never formed;
+//     and g^{t3} = 0, so those products are never formed;
 //   * FP64: the speeds' quadratic times w (b^2 + w), which leaves its roots
 //     unchanged, needs neither the sound nor the Alfven speed: with
 //     n = gam p + b^2 and m = (b^2 + w) - n = rho + gam (2 - gam) u (w = rho +
@@ -502,7 +594,7 @@ __device__ __forceinline__ double unit_scale(double x) {
 template <typename R>
 struct FaceMetric {
   R gtt, gt1, gt3, g11, g13, g22, g33;   // covariant
-  R ctt, ct1, ct3, c11, c13, c22, c33;   // contravariant
+  R ctt, ct1, c11, c22, c33;             // contravariant
   R gdet, alpha, ialpha;
 };
 
@@ -513,23 +605,24 @@ __device__ __forceinline__ float inverse_lapse(float alpha, float) { return __bu
 template <typename R>
 __device__ __forceinline__ void load_face_metric(const double* __restrict__ tab, long plane, long q,
                                                  FaceMetric<R>& m) {
-  auto at = [&](int f) { return (R)tab[f * plane + q]; };
-  m.gtt = at(G_COV + sidx(0, 0));
-  m.gt1 = at(G_COV + sidx(0, 1));
-  m.gt3 = at(G_COV + sidx(0, 3));
-  m.g11 = at(G_COV + sidx(1, 1));
-  m.g13 = at(G_COV + sidx(1, 3));
-  m.g22 = at(G_COV + sidx(2, 2));
-  m.g33 = at(G_COV + sidx(3, 3));
-  m.ctt = at(G_CON + sidx(0, 0));
-  m.ct1 = at(G_CON + sidx(0, 1));
-  m.ct3 = at(G_CON + sidx(0, 3));
-  m.c11 = at(G_CON + sidx(1, 1));
-  m.c13 = at(G_CON + sidx(1, 3));
-  m.c22 = at(G_CON + sidx(2, 2));
-  m.c33 = at(G_CON + sidx(3, 3));
-  m.gdet = at(G_DET);
-  m.alpha = at(G_ALPHA);
+  const Pair<double>* t = (const Pair<double>*)tab;
+  auto at = [&](int f) { return t[(f >> 1) * plane + q]; };
+  const Pair<double> x0 = at(G_GTT), x1 = at(G_GT3), x2 = at(G_G11), x3 = at(G_G22), x4 = at(G_CTT), x5 = at(G_DET),
+                     x6 = at(G_C11);
+  m.gtt = (R)x0.a;
+  m.gt1 = (R)x0.b;
+  m.gt3 = (R)x1.a;
+  m.g33 = (R)x1.b;
+  m.g11 = (R)x2.a;
+  m.g13 = (R)x2.b;
+  m.g22 = (R)x3.a;
+  m.c22 = (R)x3.b;
+  m.ctt = (R)x4.a;
+  m.ct1 = (R)x4.b;
+  m.gdet = (R)x5.a;
+  m.alpha = (R)x5.b;
+  m.c11 = (R)x6.a;
+  m.c33 = (R)x6.b;
   m.ialpha = inverse_lapse(m.alpha, m.ctt);
 }
 
@@ -599,7 +692,7 @@ __device__ __forceinline__ R face_side(const R p[NVAR], const FaceMetric<R>& m, 
   const R gamma = lorentz((R)1 + qsq, m.alpha, iut);
   const R ga = gamma * m.alpha;
   const R ut = gamma * m.ialpha;
-  const R u1 = fma(-ga, m.ct1, v1), u2 = v2, u3 = fma(-ga, m.ct3, v3);
+  const R u1 = fma(-ga, m.ct1, v1), u2 = v2, u3 = v3;
   const R l0 = fma(m.gtt, ut, fma(m.gt1, u1, m.gt3 * u3));
   const R l1 = fma(m.gt1, ut, fma(m.g11, u1, m.g13 * u3));
   const R l2 = m.g22 * u2;
@@ -644,7 +737,7 @@ __device__ __forceinline__ R face_side(const R p[NVAR], const FaceMetric<R>& m, 
     F[B3] = fma(b3, ud, -bd * u3);
   }
   const R cdd = D == 1 ? m.c11 : (D == 2 ? m.c22 : m.c33);
-  const R ctd = D == 1 ? m.ct1 : (D == 2 ? (R)0 : m.ct3);
+  const R ctd = D == 1 ? m.ct1 : (R)0;
   return fast_speed(rho, uu, pg, bsq, gam, ut, ud, m.ctt, ctd, cdd);
 }
 
