@@ -133,7 +133,7 @@ __device__ __forceinline__ void emhd_face(const Dev& g, const double* __restrict
   const long c = zid(g, i, j, k);
   if (pole_face<D>(g, j)) {
     const double zero[NVAR] = {};
-    store_flux<D>(F, g.nz, c, zero);
+    store_flux<D>(F, g.nz, c, zero, g.stream);
     ((Pair<double>*)FX)[c] = Pair<double>{0.0, 0.0};
     return;
   }
@@ -164,7 +164,7 @@ __device__ __forceinline__ void emhd_face(const Dev& g, const double* __restrict
 #pragma unroll
   for (int v = 0; v < NVAR + NXV; v++)
     if (v != B1 + D - 1) f[v] = 0.5 * (FL[v] + FR[v]) - 0.5 * cmax * (UR[v] - UL[v]);
-  store_flux<D>(F, g.nz, c, f);
+  store_flux<D>(F, g.nz, c, f, g.stream);
   ((Pair<double>*)FX)[c] = Pair<double>{f[NVAR], f[NVAR + 1]};
 }
 

@@ -7,8 +7,8 @@
 //           variables and characteristic speeds for both sides, and form the
 //           local Lax-Friedrichs flux (the paper keeps speeds, P->U and the
 //           Riemann solve in one kernel, Solvers section)
-//   emf     Flux-CT edge EMFs from the transverse B fluxes
-//   update  per zone: flux divergence (B fluxes rebuilt from edge EMFs),
+//   update  per zone: flux divergence (the field's from the Flux-CT edge
+//           EMFs, averages of transverse B fluxes formed in place),
 //           geometric source, SSPRK2 combination and the 1D_W inversion;
 //           stage 2 also reduces the next step's CFL rate per workgroup
 // with every intermediate resident in the caller's HBM workspace, and a
@@ -19,8 +19,8 @@
 // Options selected per context add passes to a stage: the Kastaun recovery
 // replaces 1D_W inside the update; the implicit solver's recovery runs as a
 // pass of its own after an update that stores U*; floors run after each
-// update pass; the first-order flux correction repeats the EMF and update
-// passes after a donor-cell fix of the marked zones' faces (launches that
+// update pass; the first-order flux correction repeats the update
+// pass after a donor-cell fix of the marked zones' faces (launches that
 // exit at once when nothing was marked); face-centred CT fills ghost faces,
 // reads the face field in the flux pass, forms edge EMFs (averaged, or
 // upwinded from zone-centre EMFs) and advances the faces before the update.
@@ -29,6 +29,7 @@
 
 #include <math.h>
 #include <mutex>
+#include <type_traits>
 #include <vector>
 #include <new>
 #include <stdint.h>
@@ -46,6 +47,7 @@ namespace {
 constexpr int NG = 3;
 constexpr int BLOCK = 256;
 constexpr int MAX_PARTIALS = 65536;
+constexpr long LAST_LEVEL_CACHE = 256L << 20;  // bytes
 
 // Waves per SIMD the update kernel is compiled for (its register budget):
 // without and with the CFL-rate evaluation of the new state.
@@ -73,6 +75,7 @@ struct Dev {
   double vmax2;       // 1 - 1/W_max^2, the Kastaun recovery's speed cap
   int ct;             // GRMHD_CT_*: Flux-CT, or face-centred CT (averaged / upwinded EMFs)
   int floors;         // floors and ceilings after every inversion of a stage
+  int stream;         // the fluxes of a launch exceed the last-level cache (store_flux)
   double rho_min_geom, u_min_geom, bsq_over_rho_max, bsq_over_u_max, u_over_rho_max, gamma_max;
   double tau, chi, nu;  // Extended GRMHD closure constants
   SpaceTime st;
@@ -391,7 +394,7 @@ __device__ __forceinline__ void face_llf(const Dev& g, const R qL[NVAR], const R
 #pragma unroll
   for (int v = 0; v < NVAR; v++)
     if (v != B1 + D - 1) f[v] = (FT)llf_dens(m.gdet, cmax, FL[v] + FR[v], UR[v] - UL[v]);
-  store_flux<D>(F, g.nz, c, f);
+  store_flux<D>(F, g.nz, c, f, g.stream);
 }
 
 template <int D>
@@ -410,7 +413,7 @@ __device__ __forceinline__ void flux_face(const Dev& g, const double* __restrict
   long c = zid(g, i, j, k);
   if (pole_face<D>(g, j)) {
     const FT zero[NVAR] = {};
-    store_flux<D>(F, g.nz, c, zero);
+    store_flux<D>(F, g.nz, c, zero, g.stream);
     return;
   }
   const long s = D == 1 ? 1 : (D == 2 ? (long)g.s1 : g.plane);
@@ -450,8 +453,8 @@ __device__ __forceinline__ bool plane_index(int m1, int lo1, int m2, int lo2, un
 #define FLUX_TILE 1
 #endif
 constexpr int TILE_FACES = 4 * TILE_STEPS - 1;
-constexpr int TILE_NBUF = 3;
-constexpr long FLUX_TURN_BYTES = 4L << 20;  // (the L2 of an XCD)
+constexpr int TILE_ROWS = 9;   // right-edge rows in LDS: two each of the first three wavefronts, three of the last
+constexpr long FLUX_TURN_BYTES = 4L << 20;  // (the L2 of an XCD)  // (the L2 of an XCD)
 
 // Work order of the flux launch.  Each direction has a list of workgroups
 // that goes through the grid in blocks of kb x3 planes and, inside a block,
@@ -501,7 +504,9 @@ __device__ __forceinline__ void tile2_item(const FluxPlan& pl, int n1, unsigned 
   cg = blk * most + (r - seg * n);
 }
 
-// All three face directions in one launch, in the order of FluxPlan.
+// All three face directions in one launch, in the order of FluxPlan.  With
+// zero, its first workgroup clears *zero (the flux correction's mark count of
+// the stage about to be taken).
 // For MC and WENO5 the x1 part is the shared-edge sweep, for WENO5 the x2
 // and x3 parts are the LDS-tiled sweeps (below); other schemes and parts
 // evaluate face by face.
@@ -510,12 +515,13 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(FACE
 k_flux_all(Dev g, FluxPlan pl, const double* __restrict__ P, const double* __restrict__ tabF1,
            const double* __restrict__ tabF2, const double* __restrict__ tabC, FT* __restrict__ F1,
            FT* __restrict__ F2, FT* __restrict__ F3, const double* __restrict__ ph1,
-           const double* __restrict__ ph2, const double* __restrict__ ph3) {
+           const double* __restrict__ ph2, const double* __restrict__ ph3, unsigned long long* zero) {
+  if (zero && blockIdx.x == 0 && threadIdx.x == 0) *zero = 0;
   constexpr bool shared = RECON == GRMHD_RECON_MC || RECON == GRMHD_RECON_WENO5;
   // (WENO5 only: for MC the pair saves little arithmetic and the tile's
   // registers and LDS cost a wave per SIMD)
   constexpr bool tiled = RECON == GRMHD_RECON_WENO5 && FLUX_TILE;
-  __shared__ R rows[tiled ? TILE_NBUF * 4 * NVAR * 64 : 1];
+  __shared__ R rows[tiled ? TILE_ROWS * NVAR * 64 : 1];
   int d;
   unsigned t;
   if (!flux_item(pl, blockIdx.x, d, t)) return;
@@ -653,9 +659,12 @@ __device__ __forceinline__ void sweep_x1(const Dev& g, unsigned wg, int k0, int 
 // LDS to the wavefront of the row above, and every wavefront forms the lower
 // face of its row from that left state and its own left edge.  The first row
 // of a segment is the zone below its first face (reconstructed, no face).
-// The right-edge rows are triple-buffered, so one barrier per step orders
-// everything: the buffer a step writes was last read in the step before the
-// previous one, and every wavefront has passed the barrier in between.
+// One barrier per step orders everything: a wavefront's right-edge row is
+// read in the step that wrote it (by the wavefront above) and, the last
+// wavefront's, in the next step (by the first); a row written in step t is
+// written again in step t + 2 (t + 3 for the last wavefront's), after a
+// barrier that every reader has passed once it had read.  Nine rows, 36 KB,
+// against 48 KB for three of each.
 // The face values are those of the per-face evaluation bit for bit.
 
 // Both edges of every prim of the zone at padded index c along the axis of
@@ -677,8 +686,11 @@ __device__ __forceinline__ void zone_edges(const double* __restrict__ P, long nz
   }
 }
 
+// LDS row of the right edges wavefront w forms in step t.
+__device__ __forceinline__ int tile_row(int t, int w) { return w < 3 ? (t & 1) * 3 + w : 6 + (t + 3) % 3; }
+
 // Column group wg of the D-faces fs .. fs + most - 1; rows: the LDS
-// right-edge buffers (TILE_NBUF x 4 x NVAR x 64).
+// right-edge buffers (TILE_ROWS x NVAR x 64).
 template <int D, int RECON, typename R, typename FT, bool FACE>
 __device__ __forceinline__ void sweep_tile(const Dev& g, unsigned wg, int fs, int most, const double* __restrict__ P,
                                            const double* __restrict__ tab, FT* __restrict__ F,
@@ -698,19 +710,18 @@ __device__ __forceinline__ void sweep_tile(const Dev& g, unsigned wg, int fs, in
     const int rr = rowvalid ? r : fe - 1;        // rows past the segment load an in-range stencil
     const long c = D == 2 ? zid(g, i, rr, o) : zid(g, i, o, rr);
     R left[NVAR];
-    zone_edges<RECON, R>(P, g.nz, c, s, (R)g.weno_eps, left, rows + ((t % TILE_NBUF) * 4 + w) * NVAR * 64 + lane);
+    zone_edges<RECON, R>(P, g.nz, c, s, (R)g.weno_eps, left, rows + tile_row(t, w) * NVAR * 64 + lane);
     __syncthreads();
     if (!colvalid || !rowvalid || r < fs) continue;
     // left state: the right edge of the row below (for the first wavefront,
     // the last row of the previous step)
-    const R* rd = w > 0 ? rows + ((t % TILE_NBUF) * 4 + (w - 1)) * NVAR * 64
-                        : rows + (((t + TILE_NBUF - 1) % TILE_NBUF) * 4 + 3) * NVAR * 64;
+    const R* rd = rows + (w > 0 ? tile_row(t, w - 1) : tile_row(t - 1, 3)) * NVAR * 64;
     R qL[NVAR];
 #pragma unroll
     for (int v = 0; v < NVAR; v++) qL[v] = rd[v * 64 + lane];
     if (pole_face<D>(g, r)) {
       const FT zero[NVAR] = {};
-      store_flux<D>(F, g.nz, c, zero);
+      store_flux<D>(F, g.nz, c, zero, g.stream);
       continue;
     }
     long q2 = D == 2 ? pid(g, i, r) : pid(g, i, o);
@@ -727,43 +738,52 @@ __device__ __forceinline__ void sweep_tile(const Dev& g, unsigned wg, int fs, in
   }
 }
 
-// Flux-CT edge EMFs at the lower (x1, x2, x3) corner of zone (i, j, k):
+// Flux-CT edge EMFs at the lower (x1, x2, x3) corner of the zone at padded
+// index c:
 //   E3 = [F1(B2) + F1(B2)_{j-1} - F2(B1) - F2(B1)_{i-1}]/4
 //   E2 = [F3(B1) + F3(B1)_{i-1} - F1(B3) - F1(B3)_{k-1}]/4
 //   E1 = [F2(B3) + F2(B3)_{k-1} - F3(B2) - F3(B2)_{j-1}]/4
-// E1 and E3 vanish on polar edges (sqrt(-g) = 0 there).
+// (the field pairs are F1 (B2, B3), F2 (B1, B3), F3 (B1, B2)).  E1 and E3
+// vanish on polar edges (sqrt(-g) = 0 there).
 template <typename FT>
-__device__ __forceinline__ void emf_edge(const Dev& g, const FT* __restrict__ F1, const FT* __restrict__ F2,
-                                         const FT* __restrict__ F3, FT* __restrict__ E1,
-                                         FT* __restrict__ E2, FT* __restrict__ E3, int i, int j, int k) {
-  long c = zid(g, i, j, k);
-  const long nz = g.nz, si = 1, sj = g.s1, sk = g.plane;
-  bool pole = (g.pole_lo && j == 0) || (g.pole_hi && j == g.n2);
-  const FT q = (FT)0.25;
-  // F1 (B2, B3), F2 (B1, B3), F3 (B1, B2)
-  const Pair<FT> f1 = flux_field(F1, nz, c), f2 = flux_field(F2, nz, c), f3 = flux_field(F3, nz, c);
-  FT e3 = q * (f1.a + flux_field(F1, nz, c - sj).a - f2.a - flux_field(F2, nz, c - si).a);
-  FT e2 = q * (f3.a + flux_field(F3, nz, c - si).a - f1.b - flux_field(F1, nz, c - sk).b);
-  FT e1 = q * (f2.b + flux_field(F2, nz, c - sk).b - f3.b - flux_field(F3, nz, c - sj).b);
-  E1[c] = pole ? (FT)0 : e1;
-  E2[c] = e2;
-  E3[c] = pole ? (FT)0 : e3;
+__device__ __forceinline__ FT edge_e3(const Dev& g, const FT* __restrict__ F1, const FT* __restrict__ F2, long c) {
+  const long nz = g.nz;
+  return (FT)0.25 * (flux_field(F1, nz, c).a + flux_field(F1, nz, c - g.s1).a - flux_field(F2, nz, c).a -
+                     flux_field(F2, nz, c - 1).a);
+}
+template <typename FT>
+__device__ __forceinline__ FT edge_e2(const Dev& g, const FT* __restrict__ F1, const FT* __restrict__ F3, long c) {
+  const long nz = g.nz;
+  return (FT)0.25 * (flux_field(F3, nz, c).a + flux_field(F3, nz, c - 1).a - flux_field(F1, nz, c).b -
+                     flux_field(F1, nz, c - g.plane).b);
+}
+template <typename FT>
+__device__ __forceinline__ FT edge_e1(const Dev& g, const FT* __restrict__ F2, const FT* __restrict__ F3, long c) {
+  const long nz = g.nz;
+  return (FT)0.25 * (flux_field(F2, nz, c).b + flux_field(F2, nz, c - g.plane).b - flux_field(F3, nz, c).b -
+                     flux_field(F3, nz, c - g.s1).b);
+}
+__device__ __forceinline__ bool polar_edge(const Dev& g, int j) {
+  return (g.pole_lo && j == 0) || (g.pole_hi && j == g.n2);
 }
 
+// The EMFs as arrays (face-centred CT with averaged EMFs, Extended GRMHD, the
+// flux inspection, and where the update reads them: FIELD_EMFS below).
 // With gate, runs only when *gate is non-zero (the flux correction's second
-// EMF pass); with zero, its first workgroup clears *zero (the mark count of
-// the stage about to be taken).
+// EMF pass).
 template <typename FT>
 __global__ void __launch_bounds__(BLOCK) k_emf(Dev g, Sched box, const FT* __restrict__ F1,
                                                const FT* __restrict__ F2, const FT* __restrict__ F3,
                                                FT* __restrict__ E1, FT* __restrict__ E2,
-                                               FT* __restrict__ E3, const unsigned long long* gate,
-                                               unsigned long long* zero) {
+                                               FT* __restrict__ E3, const unsigned long long* gate) {
   if (gate && *gate == 0) return;
-  if (zero && blockIdx.x == 0 && threadIdx.x == 0) *zero = 0;
   int i, j, k;
   if (!sched_index(box, blockIdx.x, gridDim.x, i, j, k)) return;
-  emf_edge<FT>(g, F1, F2, F3, E1, E2, E3, i, j, k);
+  const long c = zid(g, i, j, k);
+  const bool pole = polar_edge(g, j);
+  E1[c] = pole ? (FT)0 : edge_e1(g, F2, F3, c);
+  E2[c] = edge_e2(g, F1, F3, c);
+  E3[c] = pole ? (FT)0 : edge_e3(g, F1, F2, c);
 }
 
 // Mark of the zone at (i, j, k) for the flux correction: interior zones
@@ -910,7 +930,7 @@ __global__ void __launch_bounds__(BLOCK) k_cell_emf(Dev g, Box box, const double
 }
 
 // Upwinded (Gardiner & Stone) edge EMFs at the lower corner of zone (i, j,
-// k), edges 0..n; gate/zero as in k_emf.  Same operation order as the CPU
+// k), edges 0..n; gate as in k_emf.  Same operation order as the CPU
 // reference of the scheme.
 template <typename FT>
 __global__ void __launch_bounds__(BLOCK) k_emf_gs(Dev g, Sched box, const FT* __restrict__ F1,
@@ -919,10 +939,9 @@ __global__ void __launch_bounds__(BLOCK) k_emf_gs(Dev g, Sched box, const FT* __
                                                   const FT* __restrict__ C3, const FT* __restrict__ S,
                                                   FT* __restrict__ E1,
                                                   FT* __restrict__ E2, FT* __restrict__ E3,
-                                                  const unsigned long long* gate, unsigned long long* zero) {
+                                                  const unsigned long long* gate) {
 #pragma clang fp contract(off)
   if (gate && *gate == 0) return;
-  if (zero && blockIdx.x == 0 && threadIdx.x == 0) *zero = 0;
   int i, j, k;
   if (!sched_index(box, blockIdx.x, gridDim.x, i, j, k)) return;
   const long c = zid(g, i, j, k), nz = g.nz;
@@ -1263,7 +1282,7 @@ __device__ __forceinline__ void geometric_source(const double p[NVAR], const Flu
 
 // One stage for every interior zone.  STAGE 1: V = (Un + U1)/2 with
 // Un = U(Pin), U1 = Un + dt L(Pin); STAGE 2: U = V + dt L(Pin)/2.  Then
-// Pout = U_to_P(U; guess Pin).  B fluxes come from the edge EMFs.
+// Pout = U_to_P(U; guess Pin).  The field's rate comes from the edge EMFs.
 // Update modes: PLAIN, and the two passes of a stage under the first-order
 // flux correction: PROVISIONAL (marks zones whose inversion fails, counts
 // nothing else) and FINAL (the same update from the corrected fluxes,
@@ -1273,25 +1292,68 @@ enum { U_PLAIN = 0, U_PROVISIONAL = 2, U_FINAL = 3, U_STORE = 4 };
 // Counter slots of the context's counter array.
 enum { C_FAILS = 0, C_C2P = 1, C_FLOORS = 2, C_FOFC = 3, C_FLUID = 4, C_MARKS = 5 };
 
-// Rate of the zone field at padded index c from the edge EMFs (Flux-CT):
+// Rate of the zone field from its twelve edge EMFs (Flux-CT), e3[di][dj],
+// e2[di][dk], e1[dj][dk] at the edges offset by 0 or 1:
 // F1(B2) = (E3 + E3_{j+1})/2, F1(B3) = -(E2 + E2_{k+1})/2,
 // F2(B1) = -(E3 + E3_{i+1})/2, F2(B3) = (E1 + E1_{k+1})/2,
 // F3(B1) = (E2 + E2_{i+1})/2, F3(B2) = -(E1 + E1_{j+1})/2; normal ones zero.
-template <typename FT>
-__device__ __forceinline__ void ct_field_rate(const Dev& g, const FT* __restrict__ E1, const FT* __restrict__ E2,
-                                              const FT* __restrict__ E3, long c, double L[NVAR]) {
+__device__ __forceinline__ void field_rate(const Dev& g, const double e1[2][2], const double e2[2][2],
+                                           const double e3[2][2], double L[NVAR]) {
 #pragma clang fp contract(off)
-  const long si = 1, sj = g.s1, sk = g.plane;
-  auto e = [&](const FT* E, long o) { return (double)E[c + o]; };
-  double f1b2_p = 0.5 * (e(E3, si) + e(E3, si + sj)), f1b2_m = 0.5 * (e(E3, 0) + e(E3, sj));
-  double f1b3_p = -0.5 * (e(E2, si) + e(E2, si + sk)), f1b3_m = -0.5 * (e(E2, 0) + e(E2, sk));
-  double f2b1_p = -0.5 * (e(E3, sj) + e(E3, sj + si)), f2b1_m = -0.5 * (e(E3, 0) + e(E3, si));
-  double f2b3_p = 0.5 * (e(E1, sj) + e(E1, sj + sk)), f2b3_m = 0.5 * (e(E1, 0) + e(E1, sk));
-  double f3b1_p = 0.5 * (e(E2, sk) + e(E2, sk + si)), f3b1_m = 0.5 * (e(E2, 0) + e(E2, si));
-  double f3b2_p = -0.5 * (e(E1, sk) + e(E1, sk + sj)), f3b2_m = -0.5 * (e(E1, 0) + e(E1, sj));
+  double f1b2_p = 0.5 * (e3[1][0] + e3[1][1]), f1b2_m = 0.5 * (e3[0][0] + e3[0][1]);
+  double f1b3_p = -0.5 * (e2[1][0] + e2[1][1]), f1b3_m = -0.5 * (e2[0][0] + e2[0][1]);
+  double f2b1_p = -0.5 * (e3[0][1] + e3[1][1]), f2b1_m = -0.5 * (e3[0][0] + e3[1][0]);
+  double f2b3_p = 0.5 * (e1[1][0] + e1[1][1]), f2b3_m = 0.5 * (e1[0][0] + e1[0][1]);
+  double f3b1_p = 0.5 * (e2[0][1] + e2[1][1]), f3b1_m = 0.5 * (e2[0][0] + e2[1][0]);
+  double f3b2_p = -0.5 * (e1[0][1] + e1[1][1]), f3b2_m = -0.5 * (e1[0][0] + e1[1][0]);
   L[B1] = -((f2b1_p - f2b1_m) * g.idx2 + (f3b1_p - f3b1_m) * g.idx3);
   L[B2] = -((f1b2_p - f1b2_m) * g.idx1 + (f3b2_p - f3b2_m) * g.idx3);
   L[B3] = -((f1b3_p - f1b3_m) * g.idx1 + (f2b3_p - f2b3_m) * g.idx2);
+}
+// Where the update takes the field from: the EMF arrays of the EMF pass, the
+// face fluxes (forming the EMFs itself), or the faces of face-centred CT.
+// From the fluxes it makes 30 loads of field pairs that neighbouring zones
+// share instead of 12 of EMFs, but there is no EMF pass.  That pays while the
+// launch counts or the fluxes are still cached (32^3 MC, 10 steps: 536 -> 469
+// us, 64^3 production, 5 steps: 1.38 -> 1.36 ms); beyond the last-level cache
+// the longer chain of loads costs more than the pass (256^3 MC, 3 steps: 21.4
+// -> 22.1 ms, 192^3 mixed, 4 steps: 10.6 -> 11.1), so the rule is Dev::stream.
+enum { FIELD_EMFS = 0, FIELD_FLUXES = 1, FIELD_FACES = 2 };
+template <typename FT>
+struct Emfs {
+  const FT *e1, *e2, *e3;
+};
+// The rate from EMF arrays.
+template <typename FT>
+__device__ __forceinline__ void ct_field_rate(const Dev& g, const FT* __restrict__ E1, const FT* __restrict__ E2,
+                                              const FT* __restrict__ E3, long c, double L[NVAR]) {
+  const long si = 1, sj = g.s1, sk = g.plane;
+  auto e = [&](const FT* E, long o) { return (double)E[c + o]; };
+  const double e1[2][2] = {{e(E1, 0), e(E1, sk)}, {e(E1, sj), e(E1, sj + sk)}};
+  const double e2[2][2] = {{e(E2, 0), e(E2, sk)}, {e(E2, si), e(E2, si + sk)}};
+  const double e3[2][2] = {{e(E3, 0), e(E3, sj)}, {e(E3, si), e(E3, si + sj)}};
+  field_rate(g, e1, e2, e3, L);
+}
+// The rate from the face fluxes.
+template <typename FT>
+__device__ __forceinline__ void ct_field_rate(const Dev& g, const FT* __restrict__ F1, const FT* __restrict__ F2,
+                                              const FT* __restrict__ F3, long c, int j, double L[NVAR]) {
+  const long si = 1, sj = g.s1, sk = g.plane;
+  const bool lo = polar_edge(g, j), hi = polar_edge(g, j + 1);
+  double e1[2][2], e2[2][2], e3[2][2];
+#pragma unroll
+  for (int a = 0; a < 2; a++) {
+    e3[a][0] = lo ? 0.0 : (double)edge_e3(g, F1, F2, c + a * si);
+    e3[a][1] = hi ? 0.0 : (double)edge_e3(g, F1, F2, c + a * si + sj);
+    e2[a][0] = (double)edge_e2(g, F1, F3, c + a * si);
+    e2[a][1] = (double)edge_e2(g, F1, F3, c + a * si + sk);
+    e1[0][a] = lo ? 0.0 : (double)edge_e1(g, F2, F3, c + a * sk);
+    e1[1][a] = hi ? 0.0 : (double)edge_e1(g, F2, F3, c + a * sk + sj);
+  }
+  field_rate(g, e1, e2, e3, L);
+  // keep the zone's other loads behind these: all in flight together they
+  // take more registers than there are (124-204 B of spills per lane)
+  asm volatile("" : "+v"(L[B1]), "+v"(L[B2]), "+v"(L[B3]) :: "memory");
 }
 
 // SSPRK(5,4) of Spiteri & Ruuth (2002), Shu-Osher form, coefficients as
@@ -1305,15 +1367,13 @@ constexpr double SSP54_A4 = 0.178079954393132, SSP54_B4 = 0.821920045606868, SSP
 constexpr double SSP54_D2 = 0.517231671970585, SSP54_D3 = 0.096059710526147, SSP54_E3 = 0.063692468666290,
                  SSP54_D4 = 0.386708617503269, SSP54_E4 = 0.226007483236906;
 
-template <int STAGE, typename FT, bool RATE = false, int MODE = U_PLAIN, bool FACE = false,
+template <int STAGE, typename FT, bool RATE = false, int MODE = U_PLAIN, int FIELD = FIELD_FLUXES,
           int INTEG = GRMHD_INTEG_SSPRK2>
 __device__ __forceinline__ void update_zone(const Dev& g, const double* __restrict__ Pin,
                                             double* __restrict__ Pout, double* __restrict__ V,
                                             const FT* __restrict__ F1, const FT* __restrict__ F2,
-                                            const FT* __restrict__ F3, const FT* __restrict__ E1,
-                                            const FT* __restrict__ E2, const FT* __restrict__ E3,
-                                            const double* __restrict__ tabC,
-                                            const double* __restrict__ dgs, double dt,
+                                            const FT* __restrict__ F3, const Emfs<FT>& em,
+                                            const double* __restrict__ tabC, const double* __restrict__ dgs, double dt,
                                             unsigned long long* fails, unsigned char* __restrict__ flags,
                                             int i, int j, int k, double* rate = nullptr,
                                             unsigned char* __restrict__ mark = nullptr,
@@ -1326,13 +1386,14 @@ __device__ __forceinline__ void update_zone(const Dev& g, const double* __restri
   const long c = zid(g, i, j, k), nz = g.nz, si = 1, sj = g.s1, sk = g.plane;
   const long q2 = pid(g, i, j);
   double p[NVAR];
+  double L[NVAR];
+  if constexpr (FIELD == FIELD_FLUXES) ct_field_rate(g, F1, F2, F3, c, j, L);
   load8(Pin, nz, c, p);
   PointMetric<double> m;
   load_metric<double>(tabC, g.plane, q2, m);
   Fluid<double> f;
   fluid_state(p, m, f);
 
-  double L[NVAR];
   {
     double S[2];
     geometric_source(p, f, m, dgs, g.plane, q2, g.gam, S);
@@ -1352,11 +1413,8 @@ __device__ __forceinline__ void update_zone(const Dev& g, const double* __restri
       L[v] = -(L[v] + (hi[v] - lo[v]) * g.idx3);
       if (v == U1 || v == U2) L[v] += S[v - U1];
     }
-    if constexpr (!FACE) {
-      ct_field_rate(g, E1, E2, E3, c, L);
-    } else {
-      L[B1] = L[B2] = L[B3] = 0.0;
-    }
+    if constexpr (FIELD == FIELD_EMFS) ct_field_rate(g, em.e1, em.e2, em.e3, c, L);
+    if constexpr (FIELD == FIELD_FACES) L[B1] = L[B2] = L[B3] = 0.0;
   }
 
   // SSPRK2: U1 = U^n + dt L(P^n), V = (U^n + U1)/2, U^{n+1} = V + dt L(P1)/2;
@@ -1417,7 +1475,7 @@ __device__ __forceinline__ void update_zone(const Dev& g, const double* __restri
 #pragma unroll
     for (int v = 0; v < NVAR; v++) U[v] = reg[v] + (INTEG == GRMHD_INTEG_PC ? dt * L[v] : 0.5 * (dt * L[v]));
   }
-  if constexpr (FACE) {  // face-centred CT: the zone's field is the mean of its new faces
+  if constexpr (FIELD == FIELD_FACES) {  // face-centred CT: the zone's field is the mean of its new faces
     U[B1] = 0.5 * (ph1[c] + ph1[c + si]);
     U[B2] = 0.5 * (ph2[c] + ph2[c + sj]);
     U[B3] = 0.5 * (ph3[c] + ph3[c + sk]);
@@ -1446,13 +1504,12 @@ __device__ __forceinline__ void update_zone(const Dev& g, const double* __restri
 // flux correction runs only when the PROVISIONAL pass marked a zone (a
 // grid-uniform test of the mark count), and then adds that count to the
 // correction's running total.
-template <int STAGE, typename FT, bool RATE, int MODE, bool FACE, int INTEG = GRMHD_INTEG_SSPRK2>
+template <int STAGE, typename FT, bool RATE, int MODE, int FIELD, int INTEG = GRMHD_INTEG_SSPRK2>
 __global__ void __launch_bounds__(BLOCK)
 __attribute__((amdgpu_waves_per_eu(RATE ? UPDATE_WAVES_RATE : UPDATE_WAVES, 8)))
 k_update(Dev g, Sched box, const double* __restrict__ Pin, double* __restrict__ Pout,
          double* __restrict__ V, const FT* __restrict__ F1, const FT* __restrict__ F2,
-         const FT* __restrict__ F3, const FT* __restrict__ E1, const FT* __restrict__ E2,
-         const FT* __restrict__ E3, const double* __restrict__ tabC, const double* __restrict__ dgs,
+         const FT* __restrict__ F3, Emfs<FT> em, const double* __restrict__ tabC, const double* __restrict__ dgs,
          double dt, const double* __restrict__ dt_dev, unsigned long long* fails,
          unsigned char* __restrict__ flags, double* __restrict__ rate_partial,
          unsigned char* __restrict__ mark, const double* __restrict__ ph1,
@@ -1467,14 +1524,14 @@ k_update(Dev g, Sched box, const double* __restrict__ Pin, double* __restrict__ 
   if (dt_dev) dt = *dt_dev;
   if (!RATE) {
     if (in)
-      update_zone<STAGE, FT, false, MODE, FACE, INTEG>(g, Pin, Pout, V, F1, F2, F3, E1, E2, E3, tabC, dgs,
+      update_zone<STAGE, FT, false, MODE, FIELD, INTEG>(g, Pin, Pout, V, F1, F2, F3, em, tabC, dgs,
                                                        dt, fails, flags, i, j, k, nullptr, mark, ph1, ph2,
                                                        ph3, ustar);
     return;
   }
   double r = 0.0, sm = 0.0;
   if (in)
-    update_zone<STAGE, FT, true, MODE, FACE, INTEG>(g, Pin, Pout, V, F1, F2, F3, E1, E2, E3, tabC, dgs, dt,
+    update_zone<STAGE, FT, true, MODE, FIELD, INTEG>(g, Pin, Pout, V, F1, F2, F3, em, tabC, dgs, dt,
                                                     fails, flags, i, j, k, &r, mark, ph1, ph2, ph3, ustar);
   block_reduce(r, sm);
   if (threadIdx.x == 0) rate_partial[blockIdx.x] = r;
@@ -2039,22 +2096,27 @@ FluxPlan flux_plan(const Dev& g, int recon, int kg) {
   return pl;
 }
 
-// Flux and EMF kernels of one stage, reading the (ghost-filled) prims P.
-// Edge EMFs of the stage from the fluxes: the Flux-CT average (also the
+// Edge EMF arrays of the stage from the fluxes: the Flux-CT average (also the
 // averaged face-centred scheme), or the upwinded scheme from the zone-centre
-// EMFs (computed once per stage, from P).  gate/zero as in k_emf.
+// EMFs (computed once per stage, from P).  gate as in k_emf.
 template <typename FT>
-int stage_emfs(grmhd_ctx* c, const unsigned long long* gate, unsigned long long* zero) {
+int stage_emfs(grmhd_ctx* c, const unsigned long long* gate) {
   const Dev& g = c->dev;
   Sched be = make_sched(make_box(0, g.n1, 0, g.n2, 0, g.n3), c->kg_flux);
   if (c->params.ct == GRMHD_CT_FACE_GS)
     return launch(c, T_EMF, k_emf_gs<FT>, blocks_for(be), g, be, (const FT*)c->F[0], (const FT*)c->F[1],
                   (const FT*)c->F[2], (const FT*)c->Ec[0], (const FT*)c->Ec[1], (const FT*)c->Ec[2],
-                  (const FT*)c->Ec[3], (FT*)c->E[0], (FT*)c->E[1], (FT*)c->E[2], gate, zero);
+                  (const FT*)c->Ec[3], (FT*)c->E[0], (FT*)c->E[1], (FT*)c->E[2], gate);
   return launch(c, T_EMF, k_emf<FT>, blocks_for(be), g, be, (const FT*)c->F[0], (const FT*)c->F[1],
-                (const FT*)c->F[2], (FT*)c->E[0], (FT*)c->E[1], (FT*)c->E[2], gate, zero);
+                (const FT*)c->F[2], (FT*)c->E[0], (FT*)c->E[1], (FT*)c->E[2], gate);
 }
 
+// Whether a stage has an EMF pass: for face-centred CT, and where the update
+// reads the EMFs (FIELD_EMFS).
+bool emf_pass(const grmhd_ctx* c) { return c->params.ct != GRMHD_CT_FLUX || c->dev.stream; }
+
+// Flux kernel of one stage, reading the (ghost-filled) prims P, then its EMF
+// pass if it has one.  zero as in k_flux_all.
 template <typename R, typename FT>
 int stage_fluxes(grmhd_ctx* c, const double* P, unsigned long long* zero = nullptr,
                  double* const* ph = nullptr) {
@@ -2070,7 +2132,7 @@ int stage_fluxes(grmhd_ctx* c, const double* P, unsigned long long* zero = nullp
   const double* p3 = ph ? ph[2] : nullptr;
   auto go = [&](auto kernel) {
     return launch(c, T_FLUX, kernel, nb, g, pl, Pc, (const double*)c->tabF1, (const double*)c->tabF2,
-                  (const double*)c->tabC, F1, F2, F3, p1, p2, p3);
+                  (const double*)c->tabC, F1, F2, F3, p1, p2, p3, zero);
   };
   int rc;
   const bool face = ph != nullptr;
@@ -2097,7 +2159,7 @@ int stage_fluxes(grmhd_ctx* c, const double* P, unsigned long long* zero = nullp
                      (FT*)c->Ec[0], (FT*)c->Ec[1], (FT*)c->Ec[2], (FT*)c->Ec[3])))
       return rc;
   }
-  return stage_emfs<FT>(c, (const unsigned long long*)nullptr, zero);
+  return emf_pass(c) ? stage_emfs<FT>(c, (const unsigned long long*)nullptr) : GRMHD_OK;
 }
 
 // Face fields of one stage from the edge EMFs: stage 1 phi1 = phi + dt R (and
@@ -2131,24 +2193,29 @@ int stage_update(grmhd_ctx* c, const double* Pin, double* Pout, double dt,
   const unsigned nb = blocks_for(bz);
   auto go = [&](auto kernel, double* partial) {
     return launch(c, cls, kernel, nb, g, bz, Pin, Pout, c->V, (const FT*)c->F[0], (const FT*)c->F[1],
-                  (const FT*)c->F[2], (const FT*)c->E[0], (const FT*)c->E[1], (const FT*)c->E[2],
-                  (const double*)c->tabC, (const double*)c->dgs, dt, dt_dev, fails ? fails : c->fails, flags,
+                  (const FT*)c->F[2], Emfs<FT>{(const FT*)c->E[0], (const FT*)c->E[1], (const FT*)c->E[2]},
+                  (const double*)c->tabC, (const double*)c->dgs, dt, dt_dev,
+                  fails ? fails : c->fails, flags,
                   partial, c->mark, p1, p2, p3, c->ustar);
   };
-  if constexpr (INTEG != GRMHD_INTEG_SSPRK2) {  // the plain Flux-CT path only
-    if constexpr (INTEG != GRMHD_INTEG_SSPRK54 || STAGE == 5) {  // the stage that ends a step
-      if (rate && nb <= (unsigned)MAX_PARTIALS) return go(k_update<STAGE, FT, true, MODE, false, INTEG>, c->pdt);
+  const bool partials = rate && nb <= (unsigned)MAX_PARTIALS;
+  auto plain = [&](auto field) {  // Flux-CT
+    constexpr int FIELD = decltype(field)::value;
+    // (only the stage that ends a step is asked for its rate)
+    if constexpr (STAGE == (INTEG == GRMHD_INTEG_SSPRK54 ? 5 : 2) || INTEG == GRMHD_INTEG_RK1) {
+      if (partials) return go(k_update<STAGE, FT, true, MODE, FIELD, INTEG>, c->pdt);
     }
-    return go(k_update<STAGE, FT, false, MODE, false, INTEG>, (double*)nullptr);
-  } else {
-    if constexpr (STAGE == 2) {
-      if (rate && nb <= (unsigned)MAX_PARTIALS)
-        return ph ? go(k_update<STAGE, FT, true, MODE, true>, c->pdt)
-                  : go(k_update<STAGE, FT, true, MODE, false>, c->pdt);
+    return go(k_update<STAGE, FT, false, MODE, FIELD, INTEG>, (double*)nullptr);
+  };
+  if constexpr (INTEG == GRMHD_INTEG_SSPRK2) {
+    if (ph) {
+      if constexpr (STAGE == 2) {
+        if (partials) return go(k_update<STAGE, FT, true, MODE, FIELD_FACES>, c->pdt);
+      }
+      return go(k_update<STAGE, FT, false, MODE, FIELD_FACES>, (double*)nullptr);
     }
-    return ph ? go(k_update<STAGE, FT, false, MODE, true>, (double*)nullptr)
-              : go(k_update<STAGE, FT, false, MODE, false>, (double*)nullptr);
   }
+  return emf_pass(c) ? plain(std::integral_constant<int, FIELD_EMFS>()) : plain(std::integral_constant<int, FIELD_FLUXES>());
 }
 
 // The floors pass after an update pass (same schedule as the update, so the
@@ -2234,7 +2301,7 @@ int stage(grmhd_ctx* c, const double* Pin, double* Pout, double dt, const double
                    (const double*)(phin ? phin[0] : nullptr), (const double*)(phin ? phin[1] : nullptr),
                    (const double*)(phin ? phin[2] : nullptr))))
     return rc;
-  if ((rc = stage_emfs<FT>(c, (const unsigned long long*)nmark, (unsigned long long*)nullptr))) return rc;
+  if (emf_pass(c) && (rc = stage_emfs<FT>(c, (const unsigned long long*)nmark))) return rc;
   if (faces && (rc = stage_faces<STAGE, FT>(c, dt, dt_dev, (const unsigned long long*)nmark))) return rc;
   if ((rc = stage_update<STAGE, FT, U_FINAL>(c, Pin, Pout, dt, nullptr, nullptr, dt_dev, urate))) return rc;
   return floors ? stage_floors<STAGE, U_FINAL>(c, Pin, Pout, rate) : GRMHD_OK;
@@ -2265,7 +2332,7 @@ int emhd_stage(grmhd_ctx* c, const double* Pin, double* Xin, double* Pout, doubl
   };
   rc = c->params.recon == GRMHD_RECON_MC ? flux(k_flux_emhd<GRMHD_RECON_MC>) : flux(k_flux_emhd<GRMHD_RECON_WENO5>);
   if (rc) return rc;
-  if ((rc = stage_emfs<double>(c, (const unsigned long long*)nullptr, (unsigned long long*)nullptr))) return rc;
+  if ((rc = stage_emfs<double>(c, (const unsigned long long*)nullptr))) return rc;
   Sched bz = make_sched(make_box(0, g.n1 - 1, 0, g.n2 - 1, 0, g.n3 - 1), c->kg_update);
   const unsigned nb = blocks_for(bz);
   const int cls = STAGE == 1 ? T_UPDATE1 : T_UPDATE2;
@@ -2394,6 +2461,7 @@ Dev make_dev(const grmhd_grid* grid, const grmhd_metric* metric, const grmhd_par
   g.chi = params->chi_emhd;
   g.nu = params->nu_emhd;
   g.st = SpaceTime{kerr ? 1 : 0, metric->a, metric->hslope};
+  g.stream = 21L * (params->precision == GRMHD_PREC_FP64 ? 8 : 4) * g.nz > LAST_LEVEL_CACHE;
   return g;
 }
 
@@ -2740,6 +2808,7 @@ int grmhd_fluxes(grmhd_ctx* c, const double* d_prims, double* d_flux) {
   if ((rc = grmhd_load_prims(c, d_prims))) return rc;
   if ((rc = ensure_ghosts(c))) return rc;
   if ((rc = stage_fluxes<double, double>(c, c->P))) return rc;
+  if (!emf_pass(c) && (rc = stage_emfs<double>(c, (const unsigned long long*)nullptr))) return rc;
   const Dev& g = c->dev;
   Box be = make_box(0, g.n1, 0, g.n2, 0, g.n3);
   k_export_fluxes<<<blocks_for(be.count()), BLOCK, 0, c->stream>>>(
@@ -2977,7 +3046,6 @@ size_t pack_carve(int nb, const int* n, char* base, grmhd_pack* pk) {
     v.P1 = cv.take<double>(base, NVAR * nz);
     v.V = cv.take<double>(base, NVAR * nz);
     for (int d = 0; d < 3; d++) v.F[d] = cv.take<double>(base, NVAR * nz);
-    for (int d = 0; d < 3; d++) v.E[d] = cv.take<double>(base, nz);
     v.tabC = cv.take<double>(base, G_NF * plane);
     v.tabF1 = cv.take<double>(base, G_NF * plane);
     v.tabF2 = cv.take<double>(base, G_NF * plane);
@@ -3049,14 +3117,12 @@ int pack_launch(grmhd_pack* pk, int stage, double dt) {
       flux(k_pack_flux<1, RECON, true>);
     else
       flux(k_pack_flux<1, RECON, false>);
-    k_pack_emf<<<pk->items[PH_EMF], BLOCK, 0, pk->stream>>>(views, nb, pre);
     k_pack_update<1><<<pk->items[PH_UPDATE], BLOCK, 0, pk->stream>>>(views, nb, pre, dt, pk->d_fails);
   } else {
     if (linear)
       flux(k_pack_flux<2, RECON, true>);
     else
       flux(k_pack_flux<2, RECON, false>);
-    k_pack_emf<<<pk->items[PH_EMF], BLOCK, 0, pk->stream>>>(views, nb, pre);
     k_pack_update<2><<<pk->items[PH_UPDATE], BLOCK, 0, pk->stream>>>(views, nb, pre, dt, pk->d_fails);
   }
   return hip_check();
@@ -3141,6 +3207,7 @@ int grmhd_pack_create(grmhd_pack** out, int nblocks, const int* n, const int* of
     g.u_over_rho_max = params->u_over_rho_max;
     g.gamma_max = params->gamma_max;
     g.st = SpaceTime{kerr ? 1 : 0, metric->a, metric->hslope};
+    g.stream = 21L * pk->prim_total > LAST_LEVEL_CACHE;  // (prim_total = 8 doubles a zone)
     BlockView& v = pk->views[b];
     v.o1 = o[0];
     v.o2 = o[1];
@@ -3209,7 +3276,7 @@ int grmhd_pack_get_status(grmhd_pack* pk, long long* n_inv_fail) {
 
 int grmhd_pack_info(grmhd_pack* pk, int* grid_blocks, long long* prim_doubles) {
   if (!pk || !grid_blocks || !prim_doubles) return GRMHD_E_ARG;
-  *grid_blocks = pk->items[PH_FLUX] + pk->items[PH_EMF] + pk->items[PH_UPDATE];
+  *grid_blocks = pk->items[PH_FLUX] + pk->items[PH_UPDATE];
   *prim_doubles = pk->prim_total;
   return GRMHD_OK;
 }

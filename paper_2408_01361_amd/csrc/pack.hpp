@@ -1,11 +1,11 @@
-// Batched uneven meshblock packs: three launches per RK2 stage advance every
-// block of a pack -- face fluxes of every block along x1..x3, edge EMFs,
-// then the zone update with the inversion -- each launch covering the work
+// Batched uneven meshblock packs: two launches per RK2 stage advance every
+// block of a pack -- face fluxes of every block along x1..x3, then the zone
+// update with the edge EMFs and the inversion -- each launch covering the work
 // items of all blocks (one workgroup per item, in XCD order), so uneven
 // block sizes fill the whole GPU together and every phase keeps the
 // register budget of its own single-grid kernel.  Tile shapes (T1 x T2 x T3
 // <= BLOCK threads, or linear runs of BLOCK positions) are chosen per block
-// size (an autotuner picks them); the per-face, per-edge and per-zone work
+// size (an autotuner picks them); the per-face and per-zone work
 // is the same device code as the single-block kernels, so a block advanced
 // in a pack matches the same block advanced alone bit for bit (with the
 // linear tile shape the x1 faces come from the same shared-edge sweep as the
@@ -17,23 +17,22 @@
 struct BlockView {
   Dev g;
   double *P, *P1, *V;
-  double *F[3], *E[3];
+  double* F[3];
   double *tabC, *tabF1, *tabF2, *corner, *dgs;
   int t1, t2, t3;  // tile shape
   int o1, o2, o3;  // offset of the block's first interior zone in the global grid
   long off;        // offset (doubles) of the block in the packed prims
 };
 
-enum { PH_FLUX = 0, PH_EMF = 1, PH_UPDATE = 2, PH_N = 3 };
+enum { PH_FLUX = 0, PH_UPDATE = 1, PH_N = 2 };
 
-// Boxes of the three phases of a block (flux boxes per direction).
+// Boxes of the two phases of a block (flux boxes per direction).
 __host__ __device__ inline Box phase_box(const Dev& g, int ph, int d) {
   if (ph == PH_FLUX) {
     if (d == 1) return Box{0, -1, -1, g.n1 + 1, g.n2 + 2, g.n3 + 2};
     if (d == 2) return Box{-1, 0, -1, g.n1 + 2, g.n2 + 1, g.n3 + 2};
     return Box{-1, -1, 0, g.n1 + 2, g.n2 + 2, g.n3 + 1};
   }
-  if (ph == PH_EMF) return Box{0, 0, 0, g.n1 + 1, g.n2 + 1, g.n3 + 1};
   return Box{0, 0, 0, g.n1, g.n2, g.n3};
 }
 
@@ -153,14 +152,6 @@ k_pack_flux(const BlockView* __restrict__ bv, int nb, const int* __restrict__ pr
   pack_flux_item<RECON, LINEAR>(b, STAGE == 1 ? b.P : b.P1, lt);
 }
 
-__global__ void __launch_bounds__(BLOCK) k_pack_emf(const BlockView* __restrict__ bv, int nb,
-                                                    const int* __restrict__ pre) {
-  int lt, i, j, k;
-  const BlockView& b = bv[pack_item(nb, pre, PH_EMF, lt)];
-  if (tile_pos(phase_box(b.g, PH_EMF, 0), b.t1, b.t2, b.t3, lt, i, j, k))
-    emf_edge<double>(b.g, b.F[0], b.F[1], b.F[2], b.E[0], b.E[1], b.E[2], i, j, k);
-}
-
 template <int STAGE>
 __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(UPDATE_WAVES, 8)))
 k_pack_update(const BlockView* __restrict__ bv, int nb, const int* __restrict__ pre, double dt,
@@ -169,7 +160,7 @@ k_pack_update(const BlockView* __restrict__ bv, int nb, const int* __restrict__ 
   const BlockView& b = bv[pack_item(nb, pre, PH_UPDATE, lt)];
   if (tile_pos(phase_box(b.g, PH_UPDATE, 0), b.t1, b.t2, b.t3, lt, i, j, k))
     update_zone<STAGE, double>(b.g, STAGE == 1 ? b.P : b.P1, STAGE == 1 ? b.P1 : b.P, b.V, b.F[0], b.F[1],
-                               b.F[2], b.E[0], b.E[1], b.E[2], b.tabC, b.dgs, dt, fails, nullptr, i, j, k);
+                               b.F[2], Emfs<double>{}, b.tabC, b.dgs, dt, fails, nullptr, i, j, k);
 }
 
 // Ghost exchange between the blocks of a pack (the blocks tile part or all

@@ -72,12 +72,29 @@ __host__ __device__ constexpr int fslot(int d, int v) { return v - B1 < d - 1 ? 
 __host__ __device__ constexpr long fx(int d, int v, long nz, long c) {
   return v < U3 ? vx(v, nz, c) : (v == U3 ? 6 * nz + c : 4 * nz + 2 * c + fslot(d, v));
 }
+// stream: the launch's fluxes exceed the last-level cache (256 MB), so nothing
+// of them is still there when the update reads them; stored past the L2 they
+// leave it to the prims (128^3 WENO5, 10 steps: 10.17 -> 9.77 ms, 256^3 MC, 3
+// steps: 22.6 -> 21.4; below that size they would be missed: 64^3
+// production, 5 steps: 1.43 -> 1.45).
 template <int D, typename FT>
-__device__ __forceinline__ void store_flux(FT* __restrict__ F, long nz, long c, const FT f[NVAR]) {
+__device__ __forceinline__ void store_flux(FT* __restrict__ F, long nz, long c, const FT f[NVAR], bool stream) {
+  const FT ba = f[D == 1 ? B2 : B1], bb = f[D == 3 ? B2 : B3];
+#ifdef __AMDGCN__
+  if (stream) {
+    typedef FT Vec2 __attribute__((ext_vector_type(2)));
+    Vec2* q = (Vec2*)F;
+    __builtin_nontemporal_store((Vec2){f[RHO], f[UU]}, q + c);
+    __builtin_nontemporal_store((Vec2){f[U1], f[U2]}, q + nz + c);
+    __builtin_nontemporal_store((Vec2){ba, bb}, q + 2 * nz + c);
+    __builtin_nontemporal_store(f[U3], F + 6 * nz + c);
+    return;
+  }
+#endif
   Pair<FT>* q = (Pair<FT>*)F;
   q[c] = Pair<FT>{f[RHO], f[UU]};
   q[nz + c] = Pair<FT>{f[U1], f[U2]};
-  q[2 * nz + c] = Pair<FT>{f[D == 1 ? B2 : B1], f[D == 3 ? B2 : B3]};
+  q[2 * nz + c] = Pair<FT>{ba, bb};
   F[6 * nz + c] = f[U3];
 }
 // The five hydro components; the field pair.
