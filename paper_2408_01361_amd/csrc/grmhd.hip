@@ -64,6 +64,8 @@ struct Dev {
   int s1, s2, s3;     // padded extents
   long nz;            // padded zones per variable
   long plane;         // s1 * s2
+  long sk;            // x3 stride of the step's kernels: plane, or 0 for a flat grid
+  int flat;           // one zone along a periodic x3: every plane is the same, only plane 0 is computed
   double dx1, dx2, dx3;
   double idx1, idx2, idx3;  // 1 / dx_d (the update's differences multiply by them)
   double x1min, x2min;
@@ -286,8 +288,10 @@ __device__ __forceinline__ void ghost_index(const Dev& g, long t, int& i, int& j
 // One thread per ghost zone; ghost zones of non-frozen axes copy from the
 // zone their per-axis maps point to (always interior along those axes, so
 // nothing read here is written here).  Polar mirrors flip u~2 and B2.
+// For a flat grid only the ghosts of plane 0 (the step reads no others).
 __global__ void __launch_bounds__(BLOCK) k_bc(Dev g, double* P) {
   long t = blockIdx.x * (long)blockDim.x + threadIdx.x;
+  if (g.flat) t += 6L * g.plane;
   if (t >= ghost_count(g)) return;
   int i, j, k;
   ghost_index(g, t, i, j, k);
@@ -416,7 +420,7 @@ __device__ __forceinline__ void flux_face(const Dev& g, const double* __restrict
     store_flux<D>(F, g.nz, c, zero, g.stream);
     return;
   }
-  const long s = D == 1 ? 1 : (D == 2 ? (long)g.s1 : g.plane);
+  const long s = D == 1 ? 1 : (D == 2 ? (long)g.s1 : g.sk);
   R qL[NVAR], qR[NVAR];
   recon_pair<RECON, R>(P, g.nz, c, s, (R)g.weno_eps, qL, qR);
   const long q2 = pid(g, i, j);
@@ -504,13 +508,14 @@ __device__ __forceinline__ void tile2_item(const FluxPlan& pl, int n1, unsigned 
   cg = blk * most + (r - seg * n);
 }
 
-// All three face directions in one launch, in the order of FluxPlan.  With
+// All three face directions in one launch, in the order of FluxPlan; FLAT: of
+// a flat grid's plane 0.  With
 // zero, its first workgroup clears *zero (the flux correction's mark count of
 // the stage about to be taken).
 // For MC and WENO5 the x1 part is the shared-edge sweep, for WENO5 the x2
 // and x3 parts are the LDS-tiled sweeps (below); other schemes and parts
 // evaluate face by face.
-template <int RECON, typename R, typename FT, bool FACE>
+template <int RECON, typename R, typename FT, bool FACE, bool FLAT>
 __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(FACE ? 3 : FLUX_WAVES, 8)))
 k_flux_all(Dev g, FluxPlan pl, const double* __restrict__ P, const double* __restrict__ tabF1,
            const double* __restrict__ tabF2, const double* __restrict__ tabC, FT* __restrict__ F1,
@@ -527,30 +532,35 @@ k_flux_all(Dev g, FluxPlan pl, const double* __restrict__ P, const double* __res
   if (!flux_item(pl, blockIdx.x, d, t)) return;
   unsigned wg, seg;
   int i, j, k;
+  const int planes = FLAT ? 1 : g.n3 + 2, k0 = FLAT ? 0 : -1;  // x3 planes of the x1 and x2 faces
   if (d == 2) {
     if (tiled) {
       tile2_item(pl, g.n1, t, wg, seg);
-      sweep_tile<2, RECON, R, FT, FACE>(g, wg, (int)seg * pl.lj, pl.lj, P, tabF2, F2, ph2, rows);
+      sweep_tile<2, RECON, R, FT, FACE, FLAT>(g, wg, (int)seg * pl.lj, pl.lj, P, tabF2, F2, ph2, rows);
       return;
     }
-    plane_item(pl, pl.per2, g.n3 + 2, t, wg, k);
+    plane_item(pl, pl.per2, planes, t, wg, k);
     if (plane_index(g.n1 + 2, -1, g.n2 + 1, 0, wg, i, j))
-      flux_face<2, RECON, R, FT>(g, P, tabF2, F2, i, j, k - 1, FACE ? ph2 : nullptr);
+      flux_face<2, RECON, R, FT>(g, P, tabF2, F2, i, j, k + k0, FACE ? ph2 : nullptr);
   } else if (d == 3) {
+    if (FLAT) {  // (the one face of each column; g.sk is 0, so its stencil is the zone)
+      if (plane_index(g.n1 + 2, -1, g.n2 + 2, -1, t, i, j)) flux_face<3, RECON, R, FT>(g, P, tabC, F3, i, j, 0);
+      return;
+    }
     if (tiled) {
       seg = t / pl.per3;
-      sweep_tile<3, RECON, R, FT, FACE>(g, t - seg * pl.per3, (int)seg * pl.lk, pl.lk, P, tabC, F3, ph3, rows);
+      sweep_tile<3, RECON, R, FT, FACE, false>(g, t - seg * pl.per3, (int)seg * pl.lk, pl.lk, P, tabC, F3, ph3, rows);
       return;
     }
     plane_item(pl, pl.per3, g.n3 + 1, t, wg, k);
     if (plane_index(g.n1 + 2, -1, g.n2 + 2, -1, wg, i, j))
       flux_face<3, RECON, R, FT>(g, P, tabC, F3, i, j, k, FACE ? ph3 : nullptr);
   } else {
-    plane_item(pl, pl.per1, g.n3 + 2, t, wg, k);
+    plane_item(pl, pl.per1, planes, t, wg, k);
     if (shared)
-      sweep_x1<RECON, R, FT, FACE>(g, wg, k - 1, 1, P, tabF1, F1, ph1);
+      sweep_x1<RECON, R, FT, FACE>(g, wg, k + k0, 1, P, tabF1, F1, ph1);
     else if (plane_index(g.n1 + 1, 0, g.n2 + 2, -1, wg, i, j))
-      flux_face<1, RECON, R, FT>(g, P, tabF1, F1, i, j, k - 1, FACE ? ph1 : nullptr);
+      flux_face<1, RECON, R, FT>(g, P, tabF1, F1, i, j, k + k0, FACE ? ph1 : nullptr);
   }
 }
 
@@ -691,16 +701,16 @@ __device__ __forceinline__ int tile_row(int t, int w) { return w < 3 ? (t & 1) *
 
 // Column group wg of the D-faces fs .. fs + most - 1; rows: the LDS
 // right-edge buffers (TILE_ROWS x NVAR x 64).
-template <int D, int RECON, typename R, typename FT, bool FACE>
+template <int D, int RECON, typename R, typename FT, bool FACE, bool FLAT>
 __device__ __forceinline__ void sweep_tile(const Dev& g, unsigned wg, int fs, int most, const double* __restrict__ P,
                                            const double* __restrict__ tab, FT* __restrict__ F,
                                            const double* __restrict__ ph, R* rows) {
   const int lane = (int)(threadIdx.x & 63u), w = (int)(threadIdx.x >> 6);
   const unsigned m1 = (unsigned)g.n1 + 2u;
   const unsigned col = wg * 64u + (unsigned)lane;
-  const bool colvalid = col < m1 * (unsigned)((D == 2 ? g.n3 : g.n2) + 2);
+  const bool colvalid = col < m1 * (FLAT ? 1u : (unsigned)((D == 2 ? g.n3 : g.n2) + 2));
   const unsigned cc = colvalid ? col : 0u, oo = cc / m1;
-  const int i = (int)(cc - oo * m1) - 1, o = (int)oo - 1;   // o: the other transverse index
+  const int i = (int)(cc - oo * m1) - 1, o = FLAT ? 0 : (int)oo - 1;   // o: the other transverse index
   const int nface = (D == 2 ? g.n2 : g.n3) + 1, fe = fs + most < nface ? fs + most : nface;
   const int nsteps = (fe - fs + 1 + 3) / 4;
   const long s = D == 2 ? (long)g.s1 : g.plane;
@@ -755,12 +765,12 @@ template <typename FT>
 __device__ __forceinline__ FT edge_e2(const Dev& g, const FT* __restrict__ F1, const FT* __restrict__ F3, long c) {
   const long nz = g.nz;
   return (FT)0.25 * (flux_field(F3, nz, c).a + flux_field(F3, nz, c - 1).a - flux_field(F1, nz, c).b -
-                     flux_field(F1, nz, c - g.plane).b);
+                     flux_field(F1, nz, c - g.sk).b);
 }
 template <typename FT>
 __device__ __forceinline__ FT edge_e1(const Dev& g, const FT* __restrict__ F2, const FT* __restrict__ F3, long c) {
   const long nz = g.nz;
-  return (FT)0.25 * (flux_field(F2, nz, c).b + flux_field(F2, nz, c - g.plane).b - flux_field(F3, nz, c).b -
+  return (FT)0.25 * (flux_field(F2, nz, c).b + flux_field(F2, nz, c - g.sk).b - flux_field(F3, nz, c).b -
                      flux_field(F3, nz, c - g.s1).b);
 }
 __device__ __forceinline__ bool polar_edge(const Dev& g, int j) {
@@ -1327,7 +1337,7 @@ struct Emfs {
 template <typename FT>
 __device__ __forceinline__ void ct_field_rate(const Dev& g, const FT* __restrict__ E1, const FT* __restrict__ E2,
                                               const FT* __restrict__ E3, long c, double L[NVAR]) {
-  const long si = 1, sj = g.s1, sk = g.plane;
+  const long si = 1, sj = g.s1, sk = g.sk;
   auto e = [&](const FT* E, long o) { return (double)E[c + o]; };
   const double e1[2][2] = {{e(E1, 0), e(E1, sk)}, {e(E1, sj), e(E1, sj + sk)}};
   const double e2[2][2] = {{e(E2, 0), e(E2, sk)}, {e(E2, si), e(E2, si + sk)}};
@@ -1338,7 +1348,7 @@ __device__ __forceinline__ void ct_field_rate(const Dev& g, const FT* __restrict
 template <typename FT>
 __device__ __forceinline__ void ct_field_rate(const Dev& g, const FT* __restrict__ F1, const FT* __restrict__ F2,
                                               const FT* __restrict__ F3, long c, int j, double L[NVAR]) {
-  const long si = 1, sj = g.s1, sk = g.plane;
+  const long si = 1, sj = g.s1, sk = g.sk;
   const bool lo = polar_edge(g, j), hi = polar_edge(g, j + 1);
   double e1[2][2], e2[2][2], e3[2][2];
 #pragma unroll
@@ -1383,7 +1393,7 @@ __device__ __forceinline__ void update_zone(const Dev& g, const double* __restri
                                             double* __restrict__ ustar = nullptr) {
   // the FP64 update is rounded operation by operation, in the order written
 #pragma clang fp contract(off)
-  const long c = zid(g, i, j, k), nz = g.nz, si = 1, sj = g.s1, sk = g.plane;
+  const long c = zid(g, i, j, k), nz = g.nz, si = 1, sj = g.s1, sk = g.sk;
   const long q2 = pid(g, i, j);
   double p[NVAR];
   double L[NVAR];
@@ -1820,6 +1830,8 @@ struct grmhd_ctx {
   grmhd_params params;
   hipStream_t stream;
   Dev dev;
+  Dev flat;            // dev with its flat flag, where a step may use it
+  const Dev* cur;      // the one the stage functions use: &flat within a step, else &dev
   // workspace carve (device)
   double *P, *P1, *V;
   void *F[3], *E[3];
@@ -1842,6 +1854,7 @@ struct grmhd_ctx {
   double* pdt;              // CFL-rate partials left by the last stage-2 update
   bool rate_ready = false;  // pdt describes the current state (rate_n partials)
   bool ghosts_valid = false;  // the ghost zones of P hold the boundary conditions of its interior
+  bool plane_valid = false;   // those of plane 0 do (flat grids)
   int rate_n = 0;
   // x3 planes per chunk run of the flux/EMF and update schedules
   int kg_flux = 8, kg_update = 8;
@@ -2039,15 +2052,17 @@ int fill_ghosts(grmhd_ctx* c, double* P, double* const* ph = nullptr) {
     int rc = launch(c, T_BC, k_bc_faces, blocks_for(3 * c->dev.nz), c->dev, ph[0], ph[1], ph[2]);
     if (rc) return rc;
   }
-  return launch(c, T_BC, k_bc, blocks_for(ghost_count(c->dev)), c->dev, P);
+  const Dev& g = *c->cur;
+  return launch(c, T_BC, k_bc, blocks_for(ghost_count(g) - (g.flat ? 6L * g.plane : 0)), g, P);
 }
 
-// Ghost zones (and faces) of the state, filled unless they already hold its
-// boundary conditions (filled since the state last changed).
+// Ghost zones (and faces) of the state (of its plane 0 within a flat grid's
+// step), filled unless they already hold its boundary conditions (filled
+// since the state last changed).
 int ensure_ghosts(grmhd_ctx* c) {
-  if (c->ghosts_valid) return GRMHD_OK;
+  if (c->ghosts_valid || (c->cur->flat && c->plane_valid)) return GRMHD_OK;
   int rc = fill_ghosts(c, c->P, c->phi);
-  if (rc == GRMHD_OK) c->ghosts_valid = true;
+  if (rc == GRMHD_OK) (c->cur->flat ? c->plane_valid : c->ghosts_valid) = true;
   return rc;
 }
 
@@ -2070,12 +2085,12 @@ FluxPlan flux_plan(const Dev& g, int recon, int kg) {
   const bool tiled = recon == GRMHD_RECON_WENO5 && FLUX_TILE;
   const bool shared = recon == GRMHD_RECON_MC || recon == GRMHD_RECON_WENO5;
   auto cut = [](long n, long size) { return (unsigned)((n + size - 1) / size); };
-  const long m1 = g.n1 + 2, m2 = g.n2 + 2, m3 = g.n3 + 2;
+  const long m1 = g.n1 + 2, m2 = g.n2 + 2, m3 = g.flat ? 1 : g.n3 + 2;
   FluxPlan pl;
   pl.kb = tiled ? TILE_FACES : (int)(kg < m3 ? kg : m3);
   pl.lj = pl.lk = TILE_FACES;
   pl.nj = (int)cut(m2 - 1, pl.lj);
-  pl.nk = (int)cut(m3 - 1, pl.lk);
+  pl.nk = (int)cut(g.n3 + 1, pl.lk);
   pl.per1 = shared ? x1_sweep_blocks(m1 * m2) : cut((m1 - 1) * m2, BLOCK);
   pl.n1 = pl.per1 * (unsigned)m3;
   if (tiled) {
@@ -2087,9 +2102,10 @@ FluxPlan flux_plan(const Dev& g, int recon, int kg) {
     pl.per2 = cut(m1 * (m2 - 1), BLOCK);
     pl.n2 = pl.per2 * (unsigned)m3;
     pl.per3 = cut(m1 * m2, BLOCK);
-    pl.n3 = pl.per3 * (unsigned)(m3 - 1);
+    pl.n3 = pl.per3 * (unsigned)(g.n3 + 1);
   }
-  pl.rounds = cut(NVAR * 8 * g.nz, 8L * FLUX_TURN_BYTES);
+  if (g.flat) pl.n3 = cut(m1 * m2, BLOCK);
+  pl.rounds = cut(NVAR * 8 * (g.flat ? g.plane : g.nz), 8L * FLUX_TURN_BYTES);
   pl.q1 = cut(cut(pl.n1, 8), pl.rounds);
   pl.q2 = cut(cut(pl.n2, 8), pl.rounds);
   pl.q3 = cut(cut(pl.n3, 8), pl.rounds);
@@ -2101,8 +2117,8 @@ FluxPlan flux_plan(const Dev& g, int recon, int kg) {
 // EMFs (computed once per stage, from P).  gate as in k_emf.
 template <typename FT>
 int stage_emfs(grmhd_ctx* c, const unsigned long long* gate) {
-  const Dev& g = c->dev;
-  Sched be = make_sched(make_box(0, g.n1, 0, g.n2, 0, g.n3), c->kg_flux);
+  const Dev& g = *c->cur;
+  Sched be = make_sched(make_box(0, g.n1, 0, g.n2, 0, g.flat ? 0 : g.n3), c->kg_flux);
   if (c->params.ct == GRMHD_CT_FACE_GS)
     return launch(c, T_EMF, k_emf_gs<FT>, blocks_for(be), g, be, (const FT*)c->F[0], (const FT*)c->F[1],
                   (const FT*)c->F[2], (const FT*)c->Ec[0], (const FT*)c->Ec[1], (const FT*)c->Ec[2],
@@ -2113,14 +2129,14 @@ int stage_emfs(grmhd_ctx* c, const unsigned long long* gate) {
 
 // Whether a stage has an EMF pass: for face-centred CT, and where the update
 // reads the EMFs (FIELD_EMFS).
-bool emf_pass(const grmhd_ctx* c) { return c->params.ct != GRMHD_CT_FLUX || c->dev.stream; }
+bool emf_pass(const grmhd_ctx* c) { return c->params.ct != GRMHD_CT_FLUX || c->cur->stream; }
 
 // Flux kernel of one stage, reading the (ghost-filled) prims P, then its EMF
 // pass if it has one.  zero as in k_flux_all.
 template <typename R, typename FT>
 int stage_fluxes(grmhd_ctx* c, const double* P, unsigned long long* zero = nullptr,
                  double* const* ph = nullptr) {
-  const Dev& g = c->dev;
+  const Dev& g = *c->cur;
   FT* F1 = (FT*)c->F[0];
   FT* F2 = (FT*)c->F[1];
   FT* F3 = (FT*)c->F[2];
@@ -2134,24 +2150,28 @@ int stage_fluxes(grmhd_ctx* c, const double* P, unsigned long long* zero = nullp
     return launch(c, T_FLUX, kernel, nb, g, pl, Pc, (const double*)c->tabF1, (const double*)c->tabF2,
                   (const double*)c->tabC, F1, F2, F3, p1, p2, p3, zero);
   };
+  auto scheme = [&](auto recon) {
+    constexpr int RECON = decltype(recon)::value;
+    if (ph) return go(k_flux_all<RECON, R, FT, true, false>);
+    return g.flat ? go(k_flux_all<RECON, R, FT, false, true>) : go(k_flux_all<RECON, R, FT, false, false>);
+  };
   int rc;
-  const bool face = ph != nullptr;
   if (c->params.recon == GRMHD_RECON_MC)
-    rc = face ? go(k_flux_all<GRMHD_RECON_MC, R, FT, true>) : go(k_flux_all<GRMHD_RECON_MC, R, FT, false>);
+    rc = scheme(std::integral_constant<int, GRMHD_RECON_MC>());
   else if (c->params.recon == GRMHD_RECON_DONOR)
-    rc = face ? go(k_flux_all<GRMHD_RECON_DONOR, R, FT, true>) : go(k_flux_all<GRMHD_RECON_DONOR, R, FT, false>);
+    rc = scheme(std::integral_constant<int, GRMHD_RECON_DONOR>());
   else if (c->params.recon == GRMHD_RECON_VL)
-    rc = face ? go(k_flux_all<GRMHD_RECON_VL, R, FT, true>) : go(k_flux_all<GRMHD_RECON_VL, R, FT, false>);
+    rc = scheme(std::integral_constant<int, GRMHD_RECON_VL>());
   else if (c->params.recon == GRMHD_RECON_WENOZ)
-    rc = face ? go(k_flux_all<GRMHD_RECON_WENOZ, R, FT, true>) : go(k_flux_all<GRMHD_RECON_WENOZ, R, FT, false>);
+    rc = scheme(std::integral_constant<int, GRMHD_RECON_WENOZ>());
   else if (c->params.recon == GRMHD_RECON_MP5)
-    rc = face ? go(k_flux_all<GRMHD_RECON_MP5, R, FT, true>) : go(k_flux_all<GRMHD_RECON_MP5, R, FT, false>);
+    rc = scheme(std::integral_constant<int, GRMHD_RECON_MP5>());
   else if (c->params.recon == GRMHD_RECON_PPM)
-    rc = face ? go(k_flux_all<GRMHD_RECON_PPM, R, FT, true>) : go(k_flux_all<GRMHD_RECON_PPM, R, FT, false>);
+    rc = scheme(std::integral_constant<int, GRMHD_RECON_PPM>());
   else if (c->params.recon == GRMHD_RECON_PPMX)
-    rc = face ? go(k_flux_all<GRMHD_RECON_PPMX, R, FT, true>) : go(k_flux_all<GRMHD_RECON_PPMX, R, FT, false>);
+    rc = scheme(std::integral_constant<int, GRMHD_RECON_PPMX>());
   else
-    rc = face ? go(k_flux_all<GRMHD_RECON_WENO5, R, FT, true>) : go(k_flux_all<GRMHD_RECON_WENO5, R, FT, false>);
+    rc = scheme(std::integral_constant<int, GRMHD_RECON_WENO5>());
   if (rc) return rc;
   if (c->params.ct == GRMHD_CT_FACE_GS) {
     Box bc = make_box(-1, g.n1, -1, g.n2, -1, g.n3);
@@ -2182,7 +2202,7 @@ template <int STAGE, typename FT, int MODE = U_PLAIN, int INTEG = GRMHD_INTEG_SS
 int stage_update(grmhd_ctx* c, const double* Pin, double* Pout, double dt,
                  unsigned long long* fails = nullptr, unsigned char* flags = nullptr,
                  const double* dt_dev = nullptr, bool rate = false) {
-  const Dev& g = c->dev;
+  const Dev& g = *c->cur;
   // face-centred CT: the zones' field from the stage's new faces
   double* const* ph = c->params.ct == GRMHD_CT_FLUX ? nullptr : (STAGE == 1 ? c->phi1 : c->phi);
   const double* p1 = ph ? ph[0] : nullptr;
@@ -2289,9 +2309,10 @@ int stage(grmhd_ctx* c, const double* Pin, double* Pout, double dt, const double
   if ((rc = stage_update<STAGE, FT, U_PROVISIONAL>(c, Pin, Pout, dt, nullptr, nullptr, dt_dev, urate)))
     return rc;
   if (floors && (rc = stage_floors<STAGE, U_PROVISIONAL>(c, Pin, Pout, rate))) return rc;
-  const Dev& g = c->dev;
-  Box b1 = make_box(0, g.n1, -1, g.n2, -1, g.n3), b2 = make_box(-1, g.n1, 0, g.n2, -1, g.n3),
-      b3 = make_box(-1, g.n1, -1, g.n2, 0, g.n3);
+  const Dev& g = *c->cur;
+  const int k0 = g.flat ? 0 : -1, k1 = g.flat ? 0 : g.n3;
+  Box b1 = make_box(0, g.n1, -1, g.n2, k0, k1), b2 = make_box(-1, g.n1, 0, g.n2, k0, k1),
+      b3 = make_box(-1, g.n1, -1, g.n2, 0, k1);
   FT* F1 = (FT*)c->F[0];
   FT* F2 = (FT*)c->F[1];
   FT* F3 = (FT*)c->F[2];
@@ -2362,9 +2383,14 @@ template <typename R, typename FT>
 int do_step(grmhd_ctx* c, double dt, const double* dt_dev = nullptr) {
   int rc;
   if (c->params.ct != GRMHD_CT_FLUX && !c->faces_loaded) return GRMHD_E_STATE;
+  struct Use {  // the step's grid description, until the step returns
+    grmhd_ctx* c;
+    explicit Use(grmhd_ctx* x) : c(x) { c->cur = &c->flat; }
+    ~Use() { c->cur = &c->dev; }
+  } use(c);
   c->rate_ready = false;
   if ((rc = ensure_ghosts(c))) return rc;
-  c->ghosts_valid = false;
+  c->ghosts_valid = c->plane_valid = false;
   const Dev& g = c->dev;
   if (c->params.egrmhd) {  // Extended GRMHD: the predictor-corrector with implicit stages
     if ((rc = emhd_stage<1>(c, c->P, c->X, c->P1, c->X1, dt, dt_dev, false))) return rc;
@@ -2424,6 +2450,12 @@ int launch_dt(grmhd_ctx* c) {
   return hip_check();
 }
 
+// Whether the fluxes of a launch over that many zones (21 components each)
+// exceed the last-level cache.
+bool streams(long zones, const grmhd_params* p) {
+  return 21L * (p->precision == GRMHD_PREC_FP64 ? 8 : 4) * zones > LAST_LEVEL_CACHE;
+}
+
 // Kernel-side description of a grid, its metric and parameters.
 Dev make_dev(const grmhd_grid* grid, const grmhd_metric* metric, const grmhd_params* params) {
   Dev g;
@@ -2431,6 +2463,8 @@ Dev make_dev(const grmhd_grid* grid, const grmhd_metric* metric, const grmhd_par
   g.s1 = g.n1 + 2 * NG; g.s2 = g.n2 + 2 * NG; g.s3 = g.n3 + 2 * NG;
   g.nz = (long)g.s1 * g.s2 * g.s3;
   g.plane = (long)g.s1 * g.s2;
+  g.sk = g.plane;
+  g.flat = 0;
   g.dx1 = (grid->x1max - grid->x1min) / g.n1;
   g.dx2 = (grid->x2max - grid->x2min) / g.n2;
   g.dx3 = (grid->x3max - grid->x3min) / g.n3;
@@ -2461,7 +2495,7 @@ Dev make_dev(const grmhd_grid* grid, const grmhd_metric* metric, const grmhd_par
   g.chi = params->chi_emhd;
   g.nu = params->nu_emhd;
   g.st = SpaceTime{kerr ? 1 : 0, metric->a, metric->hslope};
-  g.stream = 21L * (params->precision == GRMHD_PREC_FP64 ? 8 : 4) * g.nz > LAST_LEVEL_CACHE;
+  g.stream = streams(g.nz, params);
   return g;
 }
 
@@ -2570,7 +2604,15 @@ int grmhd_create(grmhd_ctx** out, const grmhd_grid* grid, const grmhd_metric* me
   c->params = *params;
   c->stream = (hipStream_t)hip_stream;
   carve(c, (char*)d_workspace, grid, params);
-  c->dev = make_dev(grid, metric, params);
+  c->dev = c->flat = make_dev(grid, metric, params);
+  c->cur = &c->dev;
+  // a flat grid's step: x3 periodic with one zone, so all its planes are equal
+  // and differences along x3 vanish (zone fields only)
+  if (grid->n3 == 1 && grid->bc[4] == GRMHD_BC_PERIODIC && params->ct == GRMHD_CT_FLUX && !params->egrmhd) {
+    c->flat.flat = 1;
+    c->flat.sk = 0;
+    c->flat.stream = streams(c->flat.plane, params);
+  }
   Dev& g = c->dev;
   k_geometry<<<blocks_for(g.plane), BLOCK, 0, c->stream>>>(g, c->tabC, c->tabF1, c->tabF2, c->corner,
                                                            c->conn, c->dgs);
@@ -2592,7 +2634,7 @@ int grmhd_create(grmhd_ctx** out, const grmhd_grid* grid, const grmhd_metric* me
 int grmhd_load_prims(grmhd_ctx* c, const double* d_prims) {
   if (!c || !d_prims) return GRMHD_E_ARG;
   c->rate_ready = false;
-  c->ghosts_valid = false;
+  c->ghosts_valid = c->plane_valid = false;
   k_load_state<<<blocks_for(c->dev.nz), BLOCK, 0, c->stream>>>(c->dev.nz, d_prims, c->P, c->P1);
   int rc = hip_check();
   if (rc) return rc;
@@ -2631,7 +2673,7 @@ int grmhd_load_faces(grmhd_ctx* c, const double* d_faces) {
   }
   c->faces_loaded = true;
   c->rate_ready = false;
-  c->ghosts_valid = false;
+  c->ghosts_valid = c->plane_valid = false;
   return cell_b_from_faces(c);
 }
 
@@ -3178,6 +3220,8 @@ int grmhd_pack_create(grmhd_pack** out, int nblocks, const int* n, const int* of
     g.s1 = g.s2 = g.s3 = n[b] + 2 * NG;
     g.nz = (long)g.s1 * g.s2 * g.s3;
     g.plane = (long)g.s1 * g.s2;
+    g.sk = g.plane;
+    g.flat = 0;
     double x1lo = global->x1min + o[0] * gd1, x2lo = global->x2min + o[1] * gd2;
     double x1hi = global->x1min + (o[0] + n[b]) * gd1, x2hi = global->x2min + (o[1] + n[b]) * gd2;
     double x3lo = global->x3min + o[2] * gd3, x3hi = global->x3min + (o[2] + n[b]) * gd3;
