@@ -48,6 +48,10 @@ constexpr int NG = 3;
 constexpr int BLOCK = 256;
 constexpr int MAX_PARTIALS = 65536;
 constexpr long LAST_LEVEL_CACHE = 256L << 20;  // bytes
+// Largest padded grid whose updates write their zones' ghost images instead of
+// a ghost fill per stage (32^3 MC, 10 steps: 458 -> 399 us, 48^3 WENO5, 5
+// steps: 514 -> 484, 64^3: no difference any more).
+constexpr long IMAGE_ZONES = 1000000;
 
 // Waves per SIMD the update kernel is compiled for (its register budget):
 // without and with the CFL-rate evaluation of the new state.
@@ -65,6 +69,7 @@ struct Dev {
   long nz;            // padded zones per variable
   long plane;         // s1 * s2
   long sk;            // x3 stride of the step's kernels: plane, or 0 for a flat grid
+  int images;         // the update writes its zones' ghost images (below)
   int flat;           // one zone along a periodic x3: every plane is the same, only plane 0 is computed
   double dx1, dx2, dx3;
   double idx1, idx2, idx3;  // 1 / dx_d (the update's differences multiply by them)
@@ -308,6 +313,47 @@ __global__ void __launch_bounds__(BLOCK) k_bc(Dev g, double* P) {
     p[B2] = -p[B2];
   }
   store8(P, g.nz, dst, p);
+}
+
+// Ghost positions along one axis that copy interior x (n >= 6 zones, so those
+// of the two ends do not meet): m of them from y0, with the polar sign.
+__device__ __forceinline__ void axis_images(int x, int n, int lo, int hi, int& y0, int& m, bool& flip) {
+  m = 0;
+  y0 = 0;
+  flip = false;
+  const int d = x < NG ? x : n - 1 - x;   // distance from the nearer end
+  if (d >= NG) return;
+  const int bc = x < NG ? lo : hi;
+  if (bc == GRMHD_BC_PERIODIC) {
+    y0 = x < NG ? x + n : x - n;
+    m = 1;
+  } else if (bc == GRMHD_BC_POLAR) {
+    y0 = x < NG ? -1 - x : 2 * n - 1 - x;
+    m = 1;
+    flip = true;
+  } else if (bc == GRMHD_BC_OUTFLOW && d == 0) {
+    y0 = x == 0 ? -NG : n;
+    m = NG;
+  }
+}
+// The ghost fill from the side of the zone (i, j, k) with new prims p: stores
+// to every ghost zone that copies it.
+__device__ __forceinline__ void store_images(const Dev& g, double* __restrict__ P, int i, int j, int k,
+                                             const double p[NVAR]) {
+  int y1, y2, y3, m1, m2, m3;
+  bool f1, f2, f3;
+  axis_images(i, g.n1, g.bc[0], g.bc[1], y1, m1, f1);
+  axis_images(j, g.n2, g.bc[2], g.bc[3], y2, m2, f2);
+  axis_images(k, g.n3, g.bc[4], g.bc[5], y3, m3, f3);
+  if (g.flat) m3 = 0;
+  for (int c = 0; c <= m3; c++)
+    for (int b = 0; b <= m2; b++)
+      for (int a = (b | c) == 0 ? 1 : 0; a <= m1; a++) {
+        double q[NVAR];
+#pragma unroll
+        for (int v = 0; v < NVAR; v++) q[v] = f2 && b > 0 && (v == U2 || v == B2) ? -p[v] : p[v];
+        store8(P, g.nz, zid(g, a ? y1 + a - 1 : i, b ? y2 + b - 1 : j, c ? y3 + c - 1 : k), q);
+      }
 }
 
 // ----------------------------------------------------------------- fluxes --
@@ -1497,6 +1543,9 @@ __device__ __forceinline__ void update_zone(const Dev& g, const double* __restri
   double out[NVAR];
   int bad = invert(g, m, U, p, out);
   store8(Pout, nz, c, out);
+  if constexpr (MODE == U_PLAIN && FIELD == FIELD_FLUXES) {
+    if (g.images) store_images(g, Pout, i, j, k, out);
+  }
   if (flags) flags[c] = (unsigned char)bad;
   if (MODE == U_PROVISIONAL) {
     mark[c] = (unsigned char)bad;
@@ -1505,6 +1554,32 @@ __device__ __forceinline__ void update_zone(const Dev& g, const double* __restri
     atomicAdd(&fails[C_FAILS], 1ull);
   }
   if (RATE) *rate = zone_rate(g, out, m);
+}
+
+// The dt reduction's final pass inside the kernel that needs its dt, for few
+// partials (a launch less per step): every wavefront takes their maximum, the
+// first one leaves the result where k_reduce_final would.  Not more than
+// CFL_IN_UPDATE: every workgroup reads them all.
+struct CflStep {
+  const double* part;   // n > 0 partials, or n = 0: dt comes from elsewhere
+  int n;
+  double cfl;
+  double* result;
+};
+constexpr int CFL_IN_UPDATE = 1024;
+__device__ __forceinline__ double cfl_step(const CflStep& cs) {
+  double mx = 0.0;
+  for (int q = (int)(threadIdx.x & 63u); q < cs.n; q += 64) mx = fmax(mx, cs.part[q]);
+  mx = wave_max(mx);
+  const bool ok = mx > 0.0 && isfinite(mx);
+  const double dt = ok ? cs.cfl / mx : 0.0;
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    cs.result[0] = mx;
+    cs.result[1] = 0.0;
+    cs.result[2] = dt;
+    cs.result[3] = ok ? 0.0 : 1.0;
+  }
+  return dt;
 }
 
 // One stage over the interior.  With RATE (stage 2) every workgroup also
@@ -1523,7 +1598,7 @@ k_update(Dev g, Sched box, const double* __restrict__ Pin, double* __restrict__ 
          double dt, const double* __restrict__ dt_dev, unsigned long long* fails,
          unsigned char* __restrict__ flags, double* __restrict__ rate_partial,
          unsigned char* __restrict__ mark, const double* __restrict__ ph1,
-         const double* __restrict__ ph2, const double* __restrict__ ph3, double* __restrict__ ustar) {
+         const double* __restrict__ ph2, const double* __restrict__ ph3, double* __restrict__ ustar, CflStep cs) {
   if (MODE == U_FINAL) {
     const unsigned long long nmark = fails[C_MARKS];
     if (nmark == 0) return;
@@ -1531,7 +1606,10 @@ k_update(Dev g, Sched box, const double* __restrict__ Pin, double* __restrict__ 
   }
   int i, j, k;
   const bool in = sched_index(box, blockIdx.x, gridDim.x, i, j, k);
-  if (dt_dev) dt = *dt_dev;
+  if (cs.n > 0)
+    dt = cfl_step(cs);
+  else if (dt_dev)
+    dt = *dt_dev;
   if (!RATE) {
     if (in)
       update_zone<STAGE, FT, false, MODE, FIELD, INTEG>(g, Pin, Pout, V, F1, F2, F3, em, tabC, dgs,
@@ -1856,6 +1934,9 @@ struct grmhd_ctx {
   bool ghosts_valid = false;  // the ghost zones of P hold the boundary conditions of its interior
   bool plane_valid = false;   // those of plane 0 do (flat grids)
   int rate_n = 0;
+  // partials the step's first update reduces itself (step_cfl on small grids)
+  const double* cfl_part = nullptr;
+  int cfl_n = 0;
   // x3 planes per chunk run of the flux/EMF and update schedules
   int kg_flux = 8, kg_update = 8;
   // optional per-kernel-class timing with HIP events on the context's stream
@@ -2211,12 +2292,14 @@ int stage_update(grmhd_ctx* c, const double* Pin, double* Pout, double dt,
   Sched bz = make_sched(make_box(0, g.n1 - 1, 0, g.n2 - 1, 0, g.n3 - 1), c->kg_update);
   const int cls = STAGE == 1 ? T_UPDATE1 : T_UPDATE2;
   const unsigned nb = blocks_for(bz);
+  CflStep cs{};
+  if (STAGE == 1 && dt_dev) cs = CflStep{c->cfl_part, c->cfl_n, c->params.cfl, c->result};
   auto go = [&](auto kernel, double* partial) {
     return launch(c, cls, kernel, nb, g, bz, Pin, Pout, c->V, (const FT*)c->F[0], (const FT*)c->F[1],
                   (const FT*)c->F[2], Emfs<FT>{(const FT*)c->E[0], (const FT*)c->E[1], (const FT*)c->E[2]},
                   (const double*)c->tabC, (const double*)c->dgs, dt, dt_dev,
                   fails ? fails : c->fails, flags,
-                  partial, c->mark, p1, p2, p3, c->ustar);
+                  partial, c->mark, p1, p2, p3, c->ustar, cs);
   };
   const bool partials = rate && nb <= (unsigned)MAX_PARTIALS;
   auto plain = [&](auto field) {  // Flux-CT
@@ -2392,6 +2475,7 @@ int do_step(grmhd_ctx* c, double dt, const double* dt_dev = nullptr) {
   if ((rc = ensure_ghosts(c))) return rc;
   c->ghosts_valid = c->plane_valid = false;
   const Dev& g = c->dev;
+  const bool images = c->flat.images != 0;  // the updates fill their results' ghosts
   if (c->params.egrmhd) {  // Extended GRMHD: the predictor-corrector with implicit stages
     if ((rc = emhd_stage<1>(c, c->P, c->X, c->P1, c->X1, dt, dt_dev, false))) return rc;
     if ((rc = fill_ghosts(c, c->P1))) return rc;
@@ -2400,13 +2484,13 @@ int do_step(grmhd_ctx* c, double dt, const double* dt_dev = nullptr) {
     // five stages, the prims alternating between P1 and P (U^n lives in a
     // register from the first stage on); the last one's result copied back
     if ((rc = stage_ssp54<1, R, FT>(c, c->P, c->P1, dt, dt_dev, false))) return rc;
-    if ((rc = fill_ghosts(c, c->P1))) return rc;
+    if (!images && (rc = fill_ghosts(c, c->P1))) return rc;
     if ((rc = stage_ssp54<2, R, FT>(c, c->P1, c->P, dt, dt_dev, false))) return rc;
-    if ((rc = fill_ghosts(c, c->P))) return rc;
+    if (!images && (rc = fill_ghosts(c, c->P))) return rc;
     if ((rc = stage_ssp54<3, R, FT>(c, c->P, c->P1, dt, dt_dev, false))) return rc;
-    if ((rc = fill_ghosts(c, c->P1))) return rc;
+    if (!images && (rc = fill_ghosts(c, c->P1))) return rc;
     if ((rc = stage_ssp54<4, R, FT>(c, c->P1, c->P, dt, dt_dev, false))) return rc;
-    if ((rc = fill_ghosts(c, c->P))) return rc;
+    if (!images && (rc = fill_ghosts(c, c->P))) return rc;
     if ((rc = stage_ssp54<5, R, FT>(c, c->P, c->P1, dt, dt_dev, true))) return rc;
     if (hipMemcpyAsync(c->P, c->P1, sizeof(double) * NVAR * g.nz, hipMemcpyDeviceToDevice, c->stream) !=
         hipSuccess)
@@ -2418,12 +2502,13 @@ int do_step(grmhd_ctx* c, double dt, const double* dt_dev = nullptr) {
       return GRMHD_E_HIP;
   } else {
     if ((rc = stage<1, R, FT>(c, c->P, c->P1, dt, dt_dev, false))) return rc;
-    if ((rc = fill_ghosts(c, c->P1, c->phi1))) return rc;
+    if (!images && (rc = fill_ghosts(c, c->P1, c->phi1))) return rc;
     if ((rc = stage<2, R, FT>(c, c->P1, c->P, dt, dt_dev, true))) return rc;
   }
   const long nb = blocks_for(make_sched(make_box(0, g.n1 - 1, 0, g.n2 - 1, 0, g.n3 - 1), c->kg_update));
   c->rate_ready = nb <= MAX_PARTIALS;
   c->rate_n = (int)nb;
+  if (images) (c->flat.flat ? c->plane_valid : c->ghosts_valid) = true;
   return GRMHD_OK;
 }
 
@@ -2431,7 +2516,20 @@ int do_step(grmhd_ctx* c, double dt, const double* dt_dev = nullptr) {
 // ghost fill): result[0] = max signal rate, result[2] = cfl / max,
 // result[3] = 0 if that dt is usable.  When the last step's stage-2 update
 // left the partials of this state, only the final pass runs.
-int launch_dt(grmhd_ctx* c) {
+// With in_update, if there are few, the final pass is left to the step's first
+// update.
+int launch_dt(grmhd_ctx* c, bool in_update = false) {
+  const Dev& g = c->dev;
+  Box bz = make_box(0, g.n1 - 1, 0, g.n2 - 1, 0, g.n3 - 1);
+  long nb = blocks_for(bz.count());
+  if (nb > MAX_PARTIALS) nb = MAX_PARTIALS;
+  c->cfl_n = 0;
+  if (in_update && !(c->timing & (1u << T_DT)) && (c->rate_ready ? c->rate_n : nb) <= CFL_IN_UPDATE) {
+    c->cfl_part = c->rate_ready ? c->pdt : c->pmax;
+    c->cfl_n = c->rate_ready ? c->rate_n : (int)nb;
+    if (c->rate_ready) return GRMHD_OK;
+    return launch(c, T_DT, k_dt_partial, (unsigned)nb, g, bz, (const double*)c->P, (const double*)c->tabC, c->pmax);
+  }
   EvPair e = timing_events(c, T_DT);
   if (c->rate_ready) {
     hipExtLaunchKernelGGL(k_reduce_final, dim3(1), dim3(BLOCK), 0, c->stream, e.a, e.b, 0,
@@ -2439,10 +2537,6 @@ int launch_dt(grmhd_ctx* c) {
                           c->params.cfl);
     return hip_check();
   }
-  const Dev& g = c->dev;
-  Box bz = make_box(0, g.n1 - 1, 0, g.n2 - 1, 0, g.n3 - 1);
-  long nb = blocks_for(bz.count());
-  if (nb > MAX_PARTIALS) nb = MAX_PARTIALS;
   hipExtLaunchKernelGGL(k_dt_partial, dim3((unsigned)nb), dim3(BLOCK), 0, c->stream, e.a, nullptr, 0, g,
                         bz, (const double*)c->P, (const double*)c->tabC, c->pmax);
   hipExtLaunchKernelGGL(k_reduce_final, dim3(1), dim3(BLOCK), 0, c->stream, nullptr, e.b, 0,
@@ -2464,7 +2558,7 @@ Dev make_dev(const grmhd_grid* grid, const grmhd_metric* metric, const grmhd_par
   g.nz = (long)g.s1 * g.s2 * g.s3;
   g.plane = (long)g.s1 * g.s2;
   g.sk = g.plane;
-  g.flat = 0;
+  g.flat = g.images = 0;
   g.dx1 = (grid->x1max - grid->x1min) / g.n1;
   g.dx2 = (grid->x2max - grid->x2min) / g.n2;
   g.dx3 = (grid->x3max - grid->x3min) / g.n3;
@@ -2613,6 +2707,14 @@ int grmhd_create(grmhd_ctx** out, const grmhd_grid* grid, const grmhd_metric* me
     c->flat.sk = 0;
     c->flat.stream = streams(c->flat.plane, params);
   }
+  // The update fills its zones' ghosts itself where that is the last word on
+  // them (no floors, no other pass after it; no frozen side, whose ghosts other
+  // ghosts copy) and a launch counts more than the extra stores.
+  bool frozen = false;
+  for (int a = 0; a < 6; a++) frozen = frozen || grid->bc[a] == GRMHD_BC_FROZEN;
+  c->flat.images = params->ct == GRMHD_CT_FLUX && !params->floors && !params->fofc && !params->egrmhd &&
+                   params->inverter != GRMHD_INV_IMPLICIT && !frozen && grid->n1 >= 2 * NG && grid->n2 >= 2 * NG &&
+                   (grid->n3 >= 2 * NG || c->flat.flat) && c->dev.nz <= IMAGE_ZONES && !c->flat.stream;
   Dev& g = c->dev;
   k_geometry<<<blocks_for(g.plane), BLOCK, 0, c->stream>>>(g, c->tabC, c->tabF1, c->tabF2, c->corner,
                                                            c->conn, c->dgs);
@@ -2732,9 +2834,12 @@ int grmhd_estimate_dt(grmhd_ctx* c, double* dt_out) {
 int grmhd_step_cfl(grmhd_ctx* c) {
   if (!c) return GRMHD_E_ARG;
   int rc;
-  if ((rc = launch_dt(c))) return rc;
-  if (c->params.precision == GRMHD_PREC_FP64) return do_step<double, double>(c, 0.0, c->result + 2);
-  return do_step<float, float>(c, 0.0, c->result + 2);
+  // (the plain step's first update is the only one of its stage)
+  if ((rc = launch_dt(c, !c->params.fofc && !c->params.egrmhd && c->params.inverter != GRMHD_INV_IMPLICIT))) return rc;
+  rc = c->params.precision == GRMHD_PREC_FP64 ? do_step<double, double>(c, 0.0, c->result + 2)
+                                              : do_step<float, float>(c, 0.0, c->result + 2);
+  c->cfl_n = 0;
+  return rc;
 }
 
 int grmhd_last_dt(grmhd_ctx* c, double* dt_out) {
@@ -3221,7 +3326,7 @@ int grmhd_pack_create(grmhd_pack** out, int nblocks, const int* n, const int* of
     g.nz = (long)g.s1 * g.s2 * g.s3;
     g.plane = (long)g.s1 * g.s2;
     g.sk = g.plane;
-    g.flat = 0;
+    g.flat = g.images = 0;
     double x1lo = global->x1min + o[0] * gd1, x2lo = global->x2min + o[1] * gd2;
     double x1hi = global->x1min + (o[0] + n[b]) * gd1, x2hi = global->x2min + (o[1] + n[b]) * gd2;
     double x3lo = global->x3min + o[2] * gd3, x3hi = global->x3min + (o[2] + n[b]) * gd3;
