@@ -1292,21 +1292,14 @@ __device__ void block_reduce(double& mx, double& sm) {
 // (fmax drops NaN operands) carry it and the step size comes out unusable.
 __device__ __forceinline__ double zone_rate(const Dev& g, const double p[NVAR],
                                             const PointMetric<double>& m) {
-  Fluid<double> f;
-  fluid_state(p, m, f);
-  double cp, cm, z = 0.0;
-  if (g.n1 > 1) {
-    char_speeds(p, f, m, g.gam, 1, cp, cm);
-    z += fmax(fabs(cp), fabs(cm)) / g.dx1;
-  }
-  if (g.n2 > 1) {
-    char_speeds(p, f, m, g.gam, 2, cp, cm);
-    z += fmax(fabs(cp), fabs(cm)) / g.dx2;
-  }
-  if (g.n3 > 1) {
-    char_speeds(p, f, m, g.gam, 3, cp, cm);
-    z += fmax(fabs(cp), fabs(cm)) / g.dx3;
-  }
+#pragma clang fp contract(off)
+  ZoneState s;
+  zone_state(p, m, g.gam, s);
+  double c[3], z = 0.0;
+  zone_speeds(p[RHO], p[UU], s, m, g.gam, c);
+  if (g.n1 > 1) z += c[0] * g.idx1;
+  if (g.n2 > 1) z += c[1] * g.idx2;
+  if (g.n3 > 1) z += c[2] * g.idx3;
   return isfinite(z) ? z : (double)INFINITY;
 }
 
@@ -1316,24 +1309,6 @@ __device__ __forceinline__ void load_conn(const double* __restrict__ conn, long 
                                           double cn[40]) {
 #pragma unroll
   for (int f = 0; f < 40; f++) cn[f] = conn[f * plane + q];
-}
-
-// Geometric source of the x1 and x2 momentum equations, S[0] and S[1], from
-// the zone's metric-derivative rows (the energy and x3-momentum sources
-// vanish identically in a metric independent of x0 and x3).
-__device__ __forceinline__ void geometric_source(const double p[NVAR], const Fluid<double>& f,
-                                                 const PointMetric<double>& m,
-                                                 const double* __restrict__ dgs, long plane, long q,
-                                                 double gam, double S[2]) {
-  double D[NDG];
-#pragma unroll
-  for (int r = 0; r < 10; r++) {
-    Pair<double> x{0.0, 0.0};
-    if (!x2_offdiag(r)) x = ((const Pair<double>*)dgs)[dgs_entry(r) * plane + q];
-    D[r] = x.a;
-    D[10 + r] = x.b;
-  }
-  metric_source(p, f, m, gam, D, S);
 }
 
 // One stage for every interior zone.  STAGE 1: V = (Un + U1)/2 with
@@ -1437,7 +1412,7 @@ __device__ __forceinline__ void update_zone(const Dev& g, const double* __restri
                                             const double* __restrict__ ph2 = nullptr,
                                             const double* __restrict__ ph3 = nullptr,
                                             double* __restrict__ ustar = nullptr) {
-  // the FP64 update is rounded operation by operation, in the order written
+  // (contraction off: only the fused multiply-adds written out)
 #pragma clang fp contract(off)
   const long c = zid(g, i, j, k), nz = g.nz, si = 1, sj = g.s1, sk = g.sk;
   const long q2 = pid(g, i, j);
@@ -1447,12 +1422,12 @@ __device__ __forceinline__ void update_zone(const Dev& g, const double* __restri
   load8(Pin, nz, c, p);
   PointMetric<double> m;
   load_metric<double>(tabC, g.plane, q2, m);
-  Fluid<double> f;
-  fluid_state(p, m, f);
+  ZoneState f;
+  zone_state(p, m, g.gam, f);
 
   {
     double S[2];
-    geometric_source(p, f, m, dgs, g.plane, q2, g.gam, S);
+    zone_source(f, m, [&](int n) { return ((const Pair<double>*)dgs)[n * g.plane + q2]; }, S);
     double lo[5], hi[5];
     load_flux5(F1, nz, c, lo);
     load_flux5(F1, nz, c + si, hi);
@@ -1490,7 +1465,7 @@ __device__ __forceinline__ void update_zone(const Dev& g, const double* __restri
     double* R1 = V + NVAR * nz;
     double* R2 = V + 2 * NVAR * nz;
     double U0[NVAR];
-    if constexpr (STAGE == 1) prim_to_flux(p, f, m, g.gam, 0, U0);
+    if constexpr (STAGE == 1) zone_cons(p, f, m.gdet, U0);
 #pragma unroll
     for (int v = 0; v < NVAR; v++) {
       const double dtl = dt * L[v];
@@ -1516,7 +1491,7 @@ __device__ __forceinline__ void update_zone(const Dev& g, const double* __restri
     }
   } else if (STAGE == 1) {
     double U0[NVAR];
-    prim_to_flux(p, f, m, g.gam, 0, U0);
+    zone_cons(p, f, m.gdet, U0);
     const double h = INTEG == GRMHD_INTEG_PC ? 0.5 * dt : dt;
     double reg[NVAR];
 #pragma unroll

@@ -9,62 +9,88 @@
 
 // ---------------------------------------------------------------- U -> P --
 
-// 1D_W (Noble et al. 2006) Newton solve for W = w gamma^2 with the normal
-// observer n_mu = (-alpha, 0, 0, 0): D = alpha U_rho/sqrt(-g),
-// Q_mu = alpha T^t_mu, Bn^i = alpha B^i.  Residual
+// The conserved variables in the frame of the normal observer n_mu =
+// (-alpha, 0, 0, 0): D = alpha U_rho/sqrt(-g), Q_mu = alpha T^t_mu, Bn^i =
+// alpha B^i (B^i = U_B/sqrt(-g), into P), Q.n, Bn^2, Q.Bn, and the part of Q
+// orthogonal to n, Qt^i = (g^{ij} + n^i n^j) Q_j.  Its square is taken as
+// Q.Q + (Q.n)^2 with the rounded Q.n, whose error then cancels in what the
+// residual forms from the two (Q_i Qt^i leaves u 15 % further from the exact
+// root).  Metric entries that are identically zero (x2_offdiag, g^{t3}) are
+// left out.
+struct NormalFrame {
+  double D, Qn, Qt2, QB, Bsq;
+  double Bn[3], Qt[3];
+};
+__device__ __forceinline__ NormalFrame normal_frame(const PointMetric<double>& m, const double U[NVAR],
+                                                    double P[NVAR]) {
+#pragma clang fp contract(off)
+  NormalFrame f;
+  const double al = m.alpha, gd = m.gdet, igd = face_rcp(gd);
+  auto dens = [&](double u) { return quotient(al * u, gd, igd); };
+#pragma unroll
+  for (int i = 0; i < 3; i++) {   // rounded: a field that does not change must not drift
+    P[B1 + i] = quotient(U[B1 + i], gd, igd);
+    f.Bn[i] = al * P[B1 + i];
+  }
+  f.D = dens(U[RHO]);
+  const double Q0 = dens(U[UU] - U[RHO]), Q1 = dens(U[U1]), Q2 = dens(U[U2]), Q3 = dens(U[U3]);
+  const double ctt = m.gcon[sidx(0, 0)], ct1 = m.gcon[sidx(0, 1)], c13 = m.gcon[sidx(1, 3)];
+  const double n1 = -al * ct1, c11Q = m.gcon[sidx(1, 1)] * Q1 + c13 * Q3;
+  f.Qn = fma(Q0, -al * ctt, Q1 * n1);
+  f.Qt[0] = fma(n1 * n1, Q1, c11Q);
+  f.Qt[1] = m.gcon[sidx(2, 2)] * Q2;
+  f.Qt[2] = fma(c13, Q1, m.gcon[sidx(3, 3)] * Q3);
+  const double QQ = Q0 * (ctt * Q0 + ct1 * Q1) + Q1 * (ct1 * Q0 + c11Q) + Q2 * f.Qt[1] + Q3 * f.Qt[2];
+  f.Qt2 = fmax(QQ + f.Qn * f.Qn, 0.0);
+  f.QB = fma(Q1, f.Bn[0], fma(Q2, f.Bn[1], Q3 * f.Bn[2]));
+  f.Bsq = fma(m.gcov[sidx(1, 1)] * f.Bn[0], f.Bn[0],
+              fma(m.gcov[sidx(2, 2)] * f.Bn[1], f.Bn[1],
+                  fma(m.gcov[sidx(3, 3)] * f.Bn[2], f.Bn[2], 2.0 * (m.gcov[sidx(1, 3)] * f.Bn[0]) * f.Bn[2])));
+  return f;
+}
+
+// 1D_W (Noble et al. 2006) Newton solve for W = w gamma^2.  Residual
 //   Q.n + W - p(W) + Bn^2 (1 + v^2)/2 - (Q.Bn)^2/(2 W^2),
 //   v^2 = [Qt^2 W^2 + (Q.Bn)^2 (Bn^2 + 2W)] / [(Bn^2 + W)^2 W^2],
 //   p = (gam-1)/gam [W (1 - v^2) - D sqrt(1 - v^2)].
 // Start from the guess's W (doubled while v^2 >= 1); steps leaving W > 0,
 // v^2 < 1 are halved (at most 20 times); stop at |dW| < tol W or maxit, then
 // one more step.  Returns 1 (and the guess's hydro prims) on failure.
+// The iteration carries 1/W, 1/(W + Bn^2) and v^2 of its W, which the test of a
+// step forms anyway: two reciprocals, one of the derivative and one square
+// root per step, from the hardware estimates, where the written form has eight
+// correctly rounded quotients.
 __device__ int invert_1dw(const Dev& g, const PointMetric<double>& m, const double U[NVAR],
                           const double guess[NVAR], double P[NVAR]) {
 #pragma clang fp contract(off)
-  const double gam = g.gam;
-  const double gd = m.gdet;
-  P[B1] = U[B1] / gd;
-  P[B2] = U[B2] / gd;
-  P[B3] = U[B3] / gd;
-  const double al = m.alpha;
-  const double D = al * U[RHO] / gd;
-  double Q[4] = {al * (U[UU] / gd - U[RHO] / gd), al * U[U1] / gd, al * U[U2] / gd, al * U[U3] / gd};
-  double Bn1 = al * P[B1], Bn2 = al * P[B2], Bn3 = al * P[B3];
-  // n^mu = g^{mu t} (-alpha); Q^mu = g^{mu nu} Q_nu
-  double ncon[4], Qup[4];
-#pragma unroll
-  for (int a = 0; a < 4; a++) {
-    ncon[a] = -al * m.gcon[sidx(a, 0)];
-    Qup[a] = m.gcon[sidx(a, 0)] * Q[0] + m.gcon[sidx(a, 1)] * Q[1] + m.gcon[sidx(a, 2)] * Q[2] +
-             m.gcon[sidx(a, 3)] * Q[3];
-  }
-  double Qn = Q[0] * ncon[0] + Q[1] * ncon[1] + Q[2] * ncon[2] + Q[3] * ncon[3];
-  double QQ = Q[0] * Qup[0] + Q[1] * Qup[1] + Q[2] * Qup[2] + Q[3] * Qup[3];
-  double QB = Q[1] * Bn1 + Q[2] * Bn2 + Q[3] * Bn3;
-  double Bsq = m.gcov[sidx(1, 1)] * Bn1 * Bn1 + m.gcov[sidx(2, 2)] * Bn2 * Bn2 +
-               m.gcov[sidx(3, 3)] * Bn3 * Bn3 +
-               2.0 * (m.gcov[sidx(1, 2)] * Bn1 * Bn2 + m.gcov[sidx(1, 3)] * Bn1 * Bn3 +
-                      m.gcov[sidx(2, 3)] * Bn2 * Bn3);
-  // |Q projected orthogonal to n|^2 is non-negative; roundoff below zero is cleared
-  double Qt2 = fmax(QQ + Qn * Qn, 0.0);
-  double QB2 = QB * QB;
-  const double gf = (gam - 1.0) / gam;
+  const double gam = g.gam, igam = face_rcp(gam), gf = quotient(gam - 1.0, gam, igam);
+  const NormalFrame q = normal_frame(m, U, P);
+  const double D = q.D, Bsq = q.Bsq, QB2 = q.QB * q.QB;
 
-  auto vsq = [&](double W) {
-    double WB = Bsq + W;
-    return (Qt2 * W * W + QB2 * (Bsq + 2.0 * W)) / (WB * WB * W * W);
+  struct Point {
+    double W, iW, iWB, v2;
   };
-  auto step = [&](double W) {
-    double v2 = vsq(W);
-    double sq = sqrt(1.0 - v2);
-    double pr = gf * (W * (1.0 - v2) - D * sq);
-    double W2 = W * W, WB = W + Bsq;
-    double f = Qn + W - pr + 0.5 * Bsq * (1.0 + v2) - QB2 / (2.0 * W2);
-    double dv2 = -2.0 * (Qt2 + QB2 * (3.0 * W * W + 3.0 * W * Bsq + Bsq * Bsq) / (W2 * W)) / (WB * WB * WB);
-    double dpdW = gf * (1.0 - v2);
-    double dpdv2 = gf * (-W + D / (2.0 * sq));
-    double df = 1.0 - (dpdW + dpdv2 * dv2) + 0.5 * Bsq * dv2 + QB2 / (W2 * W);
-    return -f / df;
+  auto at = [&](double W) {
+    Point x;
+    x.W = W;
+    x.iW = face_rcp(W);
+    x.iWB = face_rcp(W + Bsq);
+    const double r = x.iWB * x.iWB;
+    x.v2 = r * fma(QB2 * fma(2.0, W, Bsq), x.iW * x.iW, q.Qt2);
+    return x;
+  };
+  auto step = [&](const Point& x) {
+    const double W = x.W, g2 = 1.0 - x.v2;
+    double h;   // 1 / (2 sqrt(1 - v^2))
+    const double sq = face_sqrt(g2, h);
+    const double iW2 = x.iW * x.iW, qw = QB2 * iW2, qw3 = qw * x.iW;
+    const double pr = gf * fma(W, g2, -(D * sq));
+    const double f = fma(-0.5, qw, fma(0.5 * Bsq, 1.0 + x.v2, (q.Qn + W) - pr));
+    const double poly = fma(3.0 * W, W + Bsq, Bsq * Bsq);
+    const double dv2 = -2.0 * ((x.iWB * x.iWB) * x.iWB) * fma(qw3, poly, q.Qt2);
+    const double dpdv2 = gf * fma(D, h, -W);
+    const double df = fma(dv2, fma(0.5, Bsq, -dpdv2), fma(-gf, g2, 1.0) + qw3);
+    return -f * face_rcp(df);
   };
   auto fail = [&]() {
 #pragma unroll
@@ -73,45 +99,48 @@ __device__ int invert_1dw(const Dev& g, const PointMetric<double>& m, const doub
   };
 
   const double g1 = guess[U1], g2 = guess[U2], g3 = guess[U3];
-  double qsq = m.gcov[sidx(1, 1)] * g1 * g1 + m.gcov[sidx(2, 2)] * g2 * g2 + m.gcov[sidx(3, 3)] * g3 * g3 +
-               2.0 * (m.gcov[sidx(1, 2)] * g1 * g2 + m.gcov[sidx(1, 3)] * g1 * g3 +
-                      m.gcov[sidx(2, 3)] * g2 * g3);
-  double W = (guess[RHO] + gam * guess[UU]) * (1.0 + qsq);
-  for (int b = 0; b < 60 && !(vsq(W) < 1.0); b++) W *= 2.0;
+  const double qsq = fma(m.gcov[sidx(1, 1)] * g1, g1,
+                         fma(m.gcov[sidx(2, 2)] * g2, g2,
+                             fma(m.gcov[sidx(3, 3)] * g3, g3, 2.0 * (m.gcov[sidx(1, 3)] * g1) * g3)));
+  Point x = at(fma(gam, guess[UU], guess[RHO]) * (1.0 + qsq));
+  for (int b = 0; b < 60 && !(x.v2 < 1.0); b++) x = at(2.0 * x.W);
   bool conv = false;
   for (int it = 0; it < g.maxit; it++) {
-    double dW = step(W);
-    double Wn = W + dW;
-    for (int b = 0; b < 20 && !(Wn > 0.0 && vsq(Wn) < 1.0); b++) {
+    double dW = step(x);
+    Point y = at(x.W + dW);
+    for (int b = 0; b < 20 && !(y.W > 0.0 && y.v2 < 1.0); b++) {
       dW *= 0.5;
-      Wn = W + dW;
+      y = at(x.W + dW);
     }
-    if (!isfinite(Wn) || Wn <= 0.0) return fail();
-    W = Wn;
-    if (fabs(dW) < g.tol * fabs(W)) {
+    if (!isfinite(y.W) || y.W <= 0.0) return fail();
+    x = y;
+    if (fabs(dW) < g.tol * fabs(x.W)) {
       conv = true;
       break;
     }
   }
   if (!conv) return fail();
-  W += step(W);
-  if (!isfinite(W) || W <= 0.0) return fail();
-  double v2 = vsq(W);
-  if (!(v2 >= 0.0 && v2 < 1.0)) return fail();
-  double gamma = 1.0 / sqrt(1.0 - v2);
-  double rho = D / gamma;
-  double u = (W * (1.0 - v2) - rho) / gam;
+  x = at(x.W + step(x));
+  if (!isfinite(x.W) || x.W <= 0.0) return fail();
+  if (!(x.v2 >= 0.0 && x.v2 < 1.0)) return fail();
+  double h;
+  const double w2 = 1.0 - x.v2, sq = face_sqrt(w2, h);   // 1/gamma
+  const double rho = D * sq;
+  const double u = quotient(fma(x.W, w2, -rho), gam, igam);
   if (!(rho > 0.0) || !(u > 0.0)) return fail();
-  double pre = gamma / (W + Bsq);
-  double ut1 = pre * ((Qup[1] + ncon[1] * Qn) + QB * Bn1 / W);
-  double ut2 = pre * ((Qup[2] + ncon[2] * Qn) + QB * Bn2 / W);
-  double ut3 = pre * ((Qup[3] + ncon[3] * Qn) + QB * Bn3 / W);
-  if (!isfinite(ut1) || !isfinite(ut2) || !isfinite(ut3)) return fail();
+  const double gi = h + h, gamma = fma(fma(-sq, gi, 1.0), gi, gi);
+  const double pre = gamma * x.iWB, qbw = q.QB * x.iW;
+  double ut[3];
+#pragma unroll
+  for (int i = 0; i < 3; i++) {
+    ut[i] = pre * fma(qbw, q.Bn[i], q.Qt[i]);
+    if (!isfinite(ut[i])) return fail();
+  }
   P[RHO] = rho;
   P[UU] = u;
-  P[U1] = ut1;
-  P[U2] = ut2;
-  P[U3] = ut3;
+  P[U1] = ut[0];
+  P[U2] = ut[1];
+  P[U3] = ut[2];
   return 0;
 }
 
@@ -131,77 +160,82 @@ __device__ int invert_1dw(const Dev& g, const PointMetric<double>& m, const doub
 // 1e-10); the root in [0, mu+] is bracketed and taken by the Illinois
 // (modified regula falsi) iteration to |d mu| <= tol mu, at most 4 maxit
 // iterations each.  No guess is used except as the failure value (the
-// guess's hydro prims, as in 1D_W).  Evaluated in the same operation order
-// as the CPU reference of the method, without contraction.
+// guess's hydro prims, as in 1D_W).  1 - v^2 loses W^2 to cancellation, so
+// the frame and v^2 are rounded in the order of the CPU reference of the
+// method (quotients by corrected reciprocals, nothing fused): the two then
+// differ far less than either does from the exact root.
 __device__ int invert_kastaun(const Dev& g, const PointMetric<double>& m, const double U[NVAR],
                               const double guess[NVAR], double P[NVAR]) {
 #pragma clang fp contract(off)
   const double gam = g.gam;
-  const double gd = m.gdet;
-  P[B1] = U[B1] / gd;
-  P[B2] = U[B2] / gd;
-  P[B3] = U[B3] / gd;
+  const double gd = m.gdet, igd = face_rcp(gd);
+#pragma unroll
+  for (int i = 0; i < 3; i++) P[B1 + i] = quotient(U[B1 + i], gd, igd);
   auto fail = [&]() {
 #pragma unroll
     for (int v = 0; v < 5; v++) P[v] = guess[v];
     return 1;
   };
   const double al = m.alpha;
-  const double D = al * U[RHO] / gd;
+  const double D = quotient(al * U[RHO], gd, igd);
   if (!(D > 0.0) || !isfinite(D)) return fail();
-  double Q[4] = {al * (U[UU] / gd - U[RHO] / gd), al * U[U1] / gd, al * U[U2] / gd, al * U[U3] / gd};
-  const double Bn[4] = {0.0, al * P[B1], al * P[B2], al * P[B3]};
-  double ncon[4], Qup[4];
-#pragma unroll
-  for (int a = 0; a < 4; a++) {
-    ncon[a] = m.gcon[sidx(a, 0)] * -al;
-    Qup[a] = m.gcon[sidx(a, 0)] * Q[0] + m.gcon[sidx(a, 1)] * Q[1] + m.gcon[sidx(a, 2)] * Q[2] +
-             m.gcon[sidx(a, 3)] * Q[3];
-  }
-  const double Qn = Q[0] * ncon[0] + Q[1] * ncon[1] + Q[2] * ncon[2] + Q[3] * ncon[3];
-  const double QQ = Q[0] * Qup[0] + Q[1] * Qup[1] + Q[2] * Qup[2] + Q[3] * Qup[3];
-  const double QB = Q[1] * Bn[1] + Q[2] * Bn[2] + Q[3] * Bn[3];
-  double Bsq = 0.0;
-#pragma unroll
-  for (int a = 1; a < 4; a++)
-#pragma unroll
-    for (int b = 1; b < 4; b++) Bsq += m.gcov[sidx(a, b)] * Bn[a] * Bn[b];
+  const double Q0 = al * (quotient(U[UU], gd, igd) - quotient(U[RHO], gd, igd)), Q1 = quotient(al * U[U1], gd, igd),
+               Q2 = quotient(al * U[U2], gd, igd), Q3 = quotient(al * U[U3], gd, igd);
+  const double Bn[3] = {al * P[B1], al * P[B2], al * P[B3]};
+  const double ctt = m.gcon[sidx(0, 0)], ct1 = m.gcon[sidx(0, 1)], c13 = m.gcon[sidx(1, 3)];
+  const double n0 = ctt * -al, n1 = ct1 * -al;
+  const double Qu0 = ctt * Q0 + ct1 * Q1, Qu1 = ct1 * Q0 + m.gcon[sidx(1, 1)] * Q1 + c13 * Q3,
+               Qu2 = m.gcon[sidx(2, 2)] * Q2, Qu3 = c13 * Q1 + m.gcon[sidx(3, 3)] * Q3;
+  const double Qn = Q0 * n0 + Q1 * n1;
+  const double QQ = Q0 * Qu0 + Q1 * Qu1 + Q2 * Qu2 + Q3 * Qu3;
+  const double QB = Q1 * Bn[0] + Q2 * Bn[1] + Q3 * Bn[2];
+  const double g13 = m.gcov[sidx(1, 3)];
+  const double Bsq = m.gcov[sidx(1, 1)] * Bn[0] * Bn[0] + g13 * Bn[0] * Bn[2] + m.gcov[sidx(2, 2)] * Bn[1] * Bn[1] +
+                     g13 * Bn[2] * Bn[0] + m.gcov[sidx(3, 3)] * Bn[2] * Bn[2];
   const double Ssq = fmax(QQ + Qn * Qn, 0.0);
-  const double r2 = Ssq / (D * D), b2 = Bsq / D, rb = QB / (D * sqrt(D)), q = -Qn / D - 1.0;
-  const double rb2 = rb * rb;
+  const double iD = face_rcp(D), D2 = D * D;
+  double hD;
+  const double D32 = D * face_sqrt(D, hD);
+  const double r2 = quotient(Ssq, D2, face_rcp(D2)), b2 = quotient(Bsq, D, iD), rb = quotient(QB, D32, face_rcp(D32)),
+               q = quotient(-Qn, D, iD) - 1.0;
+  const double rb2 = rb * rb, br = b2 * r2 - rb2;
   const double vmax2 = g.vmax2;
   const int maxit = 4 * g.maxit;
 
   struct St {
-    double x, rbar2, qbar, W, eps, nu;
+    double x, rbar2, iW, W, eps, f;
   };
   auto state = [&](double mu) {
     St s;
-    s.x = 1.0 / (1.0 + mu * b2);
+    s.x = face_rcp(1.0 + mu * b2);
     s.rbar2 = s.x * s.x * r2 + mu * s.x * (1.0 + s.x) * rb2;
-    s.qbar = q - 0.5 * b2 - 0.5 * (mu * mu) * (s.x * s.x) * (b2 * r2 - rb2);
-    double v2 = fmin(mu * mu * s.rbar2, vmax2);
-    s.W = 1.0 / sqrt(1.0 - v2);
-    s.eps = fmax(s.W * (s.qbar - mu * s.rbar2) + v2 * s.W * s.W / (1.0 + s.W), 0.0);
-    double a = (gam - 1.0) * s.eps / (1.0 + s.eps);
-    s.nu = fmax((1.0 + a) * (1.0 + s.eps) / s.W, (1.0 + a) * (1.0 + s.qbar - mu * s.rbar2));
+    const double qbar = q - 0.5 * b2 - 0.5 * (mu * mu) * (s.x * s.x) * br;
+    const double v2 = fmin(mu * mu * s.rbar2, vmax2);
+    double h;   // 1 / (2 sqrt(1 - v^2))
+    s.iW = face_sqrt(1.0 - v2, h);
+    s.W = fma(fma(-s.iW, h + h, 1.0), h + h, h + h);
+    const double W1 = 1.0 + s.W;
+    s.eps = fmax(s.W * (qbar - mu * s.rbar2) + quotient(v2 * s.W * s.W, W1, face_rcp(W1)), 0.0);
+    const double e1 = 1.0 + s.eps;
+    const double a1 = 1.0 + quotient((gam - 1.0) * s.eps, e1, face_rcp(e1));
+    const double nu = fmax(a1 * e1 * s.iW, a1 * (1.0 + qbar - mu * s.rbar2));
+    s.f = mu - face_rcp(nu + mu * s.rbar2);
     return s;
   };
-  auto f = [&](double mu) {
-    St s = state(mu);
-    return mu - 1.0 / (s.nu + mu * s.rbar2);
-  };
+  auto f = [&](double mu) { return state(mu).f; };
   auto fa = [&](double mu) {
-    double x = 1.0 / (1.0 + mu * b2);
-    double rbar2 = x * x * r2 + mu * x * (1.0 + x) * rb2;
-    return mu * sqrt(1.0 + rbar2) - 1.0;
+    const double x = face_rcp(1.0 + mu * b2);
+    const double rbar2 = x * x * r2 + mu * x * (1.0 + x) * rb2;
+    double h;
+    return mu * face_sqrt(1.0 + rbar2, h) - 1.0;
   };
   // root of h in [lo, hi] with h(lo) < 0 <= h(hi); false after maxit steps
   auto illinois = [&](auto h, double lo, double hi, double hlo, double hhi, double tol, double& root) {
     int side = 0;
     double prev = hi;
     for (int it = 0; it < maxit; it++) {
-      double mid = (lo * hhi - hi * hlo) / (hhi - hlo);
+      const double dh = hhi - hlo;
+      double mid = quotient(lo * hhi - hi * hlo, dh, face_rcp(dh));
       if (!(mid > lo && mid < hi)) mid = 0.5 * (lo + hi);
       double hm = h(mid);
       if (hm == 0.0 || fabs(mid - prev) <= tol * mid) {
@@ -230,17 +264,18 @@ __device__ int invert_kastaun(const Dev& g, const PointMetric<double>& m, const 
   if (!(f0 < 0.0) || !(f1 >= 0.0)) return fail();
   double mu = mup;
   if (f1 != 0.0 && !illinois(f, 0.0, mup, f0, f1, g.tol, mu)) return fail();
-  St s = state(mu);
-  const double rho = D / s.W;
+  const St s = state(mu);
+  const double rho = D * s.iW;
   const double u = rho * s.eps;
   // eps clamped at 0 stands when floors are on: the energy floor raises u
   if (!(rho > 0.0) || !(u > 0.0 || (g.floors && u == 0.0)) || !isfinite(u)) return fail();
-  const double pre = s.W * mu * s.x / D;
+  const double pre = quotient(s.W * mu * s.x, D, iD), mqd = mu * QB;
+  const double Qt[3] = {Qu1 + n1 * Qn, Qu2, Qu3};
   double ut[3];
 #pragma unroll
-  for (int a = 1; a < 4; a++) {
-    ut[a - 1] = pre * ((Qup[a] + ncon[a] * Qn) + mu * QB * Bn[a] / D);
-    if (!isfinite(ut[a - 1])) return fail();
+  for (int i = 0; i < 3; i++) {
+    ut[i] = pre * (Qt[i] + quotient(mqd * Bn[i], D, iD));
+    if (!isfinite(ut[i])) return fail();
   }
   P[RHO] = rho;
   P[UU] = u;

@@ -583,6 +583,12 @@ __device__ __forceinline__ double face_rcp(double x) {
 }
 __device__ __forceinline__ float face_rcp(float x) { return __builtin_amdgcn_rcpf(x); }
 
+// a / b from r = 1/b: correctly rounded but for rare ties.
+__device__ __forceinline__ double quotient(double a, double b, double r) {
+  const double q = a * r;
+  return fma(fma(-b, q, a), r, q);
+}
+
 __device__ __forceinline__ double hw_rsqrt(double x) {
 #ifdef __AMDGCN__
   return __builtin_amdgcn_rsq(x);
@@ -756,6 +762,111 @@ __device__ __forceinline__ R face_side(const R p[NVAR], const FaceMetric<R>& m, 
   const R cdd = D == 1 ? m.c11 : (D == 2 ? m.c22 : m.c33);
   const R ctd = D == 1 ? m.ct1 : (R)0;
   return fast_speed(rho, uu, pg, bsq, gam, ut, ud, m.ctt, ctd, cdd);
+}
+
+// ---------------------------------------------------------- zone physics --
+//
+// The state at a zone centre as the update and the CFL rate need it, arranged
+// as the face states are: only the metric entries that are not identically
+// zero, reciprocals and square roots from the hardware estimates, fused
+// multiply-adds written out.
+struct ZoneState {
+  double ut, u1, u2, u3;      // four-velocity
+  double l0, l1, l2, l3;      // lowered
+  double bt, b1, b2, b3;      // magnetic four-vector
+  double k0, k1, k2, k3;      // lowered
+  double bsq, w, ptot, pg;    // w = rho + u + p + b^2
+};
+__device__ __forceinline__ void zone_state(const double p[NVAR], const PointMetric<double>& m, double gam,
+                                           ZoneState& z) {
+  const double gtt = m.gcov[sidx(0, 0)], gt1 = m.gcov[sidx(0, 1)], gt3 = m.gcov[sidx(0, 3)], g11 = m.gcov[sidx(1, 1)],
+               g13 = m.gcov[sidx(1, 3)], g22 = m.gcov[sidx(2, 2)], g33 = m.gcov[sidx(3, 3)];
+  const double ctt = m.gcon[sidx(0, 0)], ct1 = m.gcon[sidx(0, 1)];
+  const double v1 = p[U1], v2 = p[U2], v3 = p[U3], Bc1 = p[B1], Bc2 = p[B2], Bc3 = p[B3];
+  const double qsq = fma(g11 * v1, v1, fma(g22 * v2, v2, fma(g33 * v3, v3, 2.0 * (g13 * v1) * v3)));
+  double iut;
+  const double gamma = lorentz(1.0 + qsq, m.alpha, iut);
+  z.ut = quotient(gamma, m.alpha, inverse_lapse(m.alpha, ctt));
+  z.u1 = fma(-(gamma * m.alpha), ct1, v1);
+  z.u2 = v2;
+  z.u3 = v3;
+  z.l0 = fma(gtt, z.ut, fma(gt1, z.u1, gt3 * z.u3));
+  z.l1 = fma(gt1, z.ut, fma(g11, z.u1, g13 * z.u3));
+  z.l2 = g22 * z.u2;
+  z.l3 = fma(gt3, z.ut, fma(g13, z.u1, g33 * z.u3));
+  z.bt = fma(Bc1, z.l1, fma(Bc2, z.l2, Bc3 * z.l3));
+  z.b1 = fma(z.bt, z.u1, Bc1) * iut;
+  z.b2 = fma(z.bt, z.u2, Bc2) * iut;
+  z.b3 = fma(z.bt, z.u3, Bc3) * iut;
+  z.k0 = fma(gtt, z.bt, fma(gt1, z.b1, gt3 * z.b3));
+  z.k1 = fma(gt1, z.bt, fma(g11, z.b1, g13 * z.b3));
+  z.k2 = g22 * z.b2;
+  z.k3 = fma(gt3, z.bt, fma(g13, z.b1, g33 * z.b3));
+  z.bsq = fma(z.bt, z.k0, fma(z.b1, z.k1, fma(z.b2, z.k2, z.b3 * z.k3)));
+  z.pg = (gam - 1.0) * p[UU];
+  z.w = ((p[RHO] + p[UU]) + z.pg) + z.bsq;
+  z.ptot = fma(0.5, z.bsq, z.pg);
+}
+
+// Conserved variables sqrt(-g) (rho u^t, T^t_t + rho u^t, T^t_i, B^i).
+__device__ __forceinline__ void zone_cons(const double p[NVAR], const ZoneState& z, double gdet, double U[NVAR]) {
+  const double wu = z.w * z.ut, ru = p[RHO] * z.ut;
+  U[RHO] = gdet * ru;
+  U[UU] = gdet * (fma(wu, z.l0, fma(-z.bt, z.k0, z.ptot)) + ru);
+  U[U1] = gdet * fma(wu, z.l1, -z.bt * z.k1);
+  U[U2] = gdet * fma(wu, z.l2, -z.bt * z.k2);
+  U[U3] = gdet * fma(wu, z.l3, -z.bt * z.k3);
+  U[B1] = gdet * p[B1];
+  U[B2] = gdet * p[B2];
+  U[B3] = gdet * p[B3];
+}
+
+// Geometric source of the x1 and x2 momentum equations (metric_source in
+// physics_body.inc has the derivation): sqrt(-g) sum_kl T^{kl} d_nu g_kl / 2
+// over the seven entries that vary, d(n) the derivative pair of entry n
+// (dgs_entry), T^{kl} = w u^k u^l + ptot g^{kl} - b^k b^l.
+template <typename Deriv>
+__device__ __forceinline__ void zone_source(const ZoneState& z, const PointMetric<double>& m, Deriv d, double S[2]) {
+  const double u[4] = {z.ut, z.u1, z.u2, z.u3}, b[4] = {z.bt, z.b1, z.b2, z.b3};
+  double s1 = 0.0, s2 = 0.0;
+#pragma unroll
+  for (int x = 0; x < 4; x++) {
+    const double wu = z.w * u[x];
+#pragma unroll
+    for (int y = x; y < 4; y++) {
+      if (x2_offdiag(sidx(x, y))) continue;
+      const double t = fma(-b[x], b[y], wu * u[y]);
+      const double T = x == 0 && y == 3 ? t : fma(z.ptot, m.gcon[sidx(x, y)], t);
+      const Pair<double> q = d(dgs_entry(sidx(x, y)));
+      s1 = fma(T, q.a, s1);
+      s2 = fma(T, q.b, s2);
+    }
+  }
+  S[0] = m.gdet * s1;
+  S[1] = m.gdet * s2;
+}
+
+// Larger magnitudes of the fast speeds along x1, x2 and x3 (fast_speed above;
+// the quadratics' A, scale and enthalpy terms are common to the three).
+__device__ __forceinline__ void zone_speeds(double rho, double uu, const ZoneState& z, const PointMetric<double>& m,
+                                            double gam, double c[3]) {
+  const double n0 = fma(gam, z.pg, z.bsq);
+  const double m0 = fma(gam * (2.0 - gam), uu, rho);
+  const double sc = unit_scale(n0 + m0);
+  const double n = n0 * sc, mm = m0 * sc;
+  const double mut = mm * z.ut;
+  const double A = fma(mut, z.ut, -n * m.gcon[sidx(0, 0)]);
+  const double iA = fabs(face_rcp(A));
+  const double ud[3] = {z.u1, z.u2, z.u3};
+#pragma unroll
+  for (int d = 0; d < 3; d++) {
+    const double b = d == 0 ? fma(mut, ud[d], -n * m.gcon[sidx(0, 1)]) : mut * ud[d];
+    const double C = fma(mm * ud[d], ud[d], -n * m.gcon[sidx(d + 1, d + 1)]);
+    const double disc = fma(b, b, -(A * C));
+    double h;
+    const double s = face_sqrt(disc > 1e-280 ? disc : 1e-280, h);
+    c[d] = (fabs(b) + s) * iA;
+  }
 }
 
 }  // namespace grmhd
