@@ -27,7 +27,9 @@
 // equations, linear in X for a given hydro state, solved for X inside
 // every residual evaluation.
 //
-// FP64 throughout, every operation rounded on its own in the order written.
+// FP64 throughout, every operation rounded on its own in the order written;
+// quotients and roots by plain_div and plain_sqrt, whose bits are those of the
+// correctly rounded ones.
 //
 // Included inside the anonymous namespace of grmhd.hip.
 
@@ -37,24 +39,24 @@ constexpr int NXV = 2;  // extra variables per zone (stored as a pair per zone: 
 __device__ __forceinline__ void emhd_unscale(const Dev& g, const double p[NVAR], const double x[NXV], double& q,
                                              double& dP) {
 #pragma clang fp contract(off)
-  const double theta = (g.gam - 1.0) * p[UU] / p[RHO];
-  q = x[0] * theta * sqrt(g.chi * p[RHO] / g.tau);
-  dP = x[1] * sqrt(g.nu * p[RHO] * theta / g.tau);
+  const double theta = plain_div((g.gam - 1.0) * p[UU], p[RHO]), itau = plain_rcp(g.tau);
+  q = x[0] * theta * plain_sqrt(quotient(g.chi * p[RHO], g.tau, itau));
+  dP = x[1] * plain_sqrt(quotient(g.nu * p[RHO] * theta, g.tau, itau));
 }
 
 // Row mu of the extended mixed stress-energy tensor.
 __device__ __forceinline__ void tmunu_row_emhd(const double p[NVAR], const Fluid<double>& f, double gam, double q,
                                                double dP, int mu, double T[4]) {
 #pragma clang fp contract(off)
-  tmunu_row(p, f, gam, mu, T);
+  fplain::tmunu_row(p, f, gam, mu, T);
   if (!(f.bsq > 0.0) || (q == 0.0 && dP == 0.0)) return;
-  const double sb = sqrt(f.bsq);
-  const double bm = f.bcon[mu] / sb;
+  const double sb = plain_sqrt(f.bsq), isb = plain_rcp(sb), third = 1.0 / 3.0;
+  const double bm = quotient(f.bcon[mu], sb, isb);
 #pragma unroll
   for (int nu = 0; nu < 4; nu++) {
-    const double bn = f.bcov[nu] / sb;
+    const double bn = quotient(f.bcov[nu], sb, isb);
     const double h = (mu == nu ? 1.0 : 0.0) + f.ucon[mu] * f.ucov[nu];
-    T[nu] = ((T[nu] + q * bm * f.ucov[nu]) + q * bn * f.ucon[mu]) - dP * (bm * bn - h / 3.0);
+    T[nu] = ((T[nu] + q * bm * f.ucov[nu]) + q * bn * f.ucon[mu]) - dP * (bm * bn - quotient(h, 3.0, third));
   }
 }
 
@@ -121,6 +123,60 @@ __global__ void __launch_bounds__(BLOCK) k_read_extra(long nz, const double* __r
   dst[nz + c] = x.b;
 }
 
+// WENO5 on the zone values (12 times the smoothness indicators, the candidates
+// over a common denominator, a correctly rounded quotient), where the ideal
+// step works on differences.  A torus's atmosphere holds tens to thousands of
+// zones whose implicit solve does not converge; there the step amplifies a
+// changed last bit of a face state or of dt to 1e-3 of the prims.  Extended
+// GRMHD therefore rounds as it always has (here, zone_rate_ordered, and the
+// sums of every kernel below), so that a run repeats the runs before it.
+namespace wv {
+#pragma clang fp contract(off)
+__device__ __forceinline__ void indicators(double a, double b, double c, double d, double e, double eps, double& s0,
+                                           double& s1, double& s2) {
+  const double eps12 = 12.0 * eps;
+  const double t0 = fma(-2.0, b, a + c), u0 = fma(-4.0, b, fma(3.0, c, a));
+  const double t1 = fma(-2.0, c, b + d), u1 = b - d;
+  const double t2 = fma(-2.0, d, c + e), u2 = fma(-4.0, d, fma(3.0, c, e));
+  s0 = fma(13.0 * t0, t0, fma(3.0 * u0, u0, eps12));
+  s1 = fma(13.0 * t1, t1, fma(3.0 * u1, u1, eps12));
+  s2 = fma(13.0 * t2, t2, fma(3.0 * u2, u2, eps12));
+  s0 *= s0;
+  s1 *= s1;
+  s2 *= s2;
+}
+__device__ __forceinline__ double weno5(double a, double b, double c, double d, double e, double eps) {
+  double s0, s1, s2;
+  indicators(a, b, c, d, e, eps, s0, s1, s2);
+  const double w0 = s1 * s2, w1 = 6.0 * (s0 * s2), w2 = 3.0 * (s0 * s1);
+  const double p0 = fma(11.0, c, fma(-7.0, b, 2.0 * a));
+  const double p1 = fma(2.0, d, fma(5.0, c, -b));
+  const double p2 = fma(5.0, d, fma(2.0, c, -e));
+  const double den = 6.0 * ((w0 + w1) + w2);
+  double r = __builtin_amdgcn_rcp(den);
+  r = fma(fma(-den, r, 1.0), r, r);
+  r = fma(fma(-den, r, 1.0), r, r);
+  return quotient(fma(w0, p0, fma(w1, p1, w2 * p2)), den, r);
+}
+}  // namespace wv
+// Far edge of a zone for the two variables of pair index c, the zones behind
+// it s apart on the side away from the edge: the left state of a face comes
+// from the zones below it (s > 0, c the zone below), the right state is the
+// same expression on the mirrored stencil (s < 0, c the zone above).
+template <int RECON>
+__device__ __forceinline__ void recon_edge(const Pair<double>* __restrict__ q, long c, long s, double eps, double& a,
+                                           double& b) {
+  const Pair<double> m1 = q[c - s], z = q[c], p1 = q[c + s];
+  if (RECON == GRMHD_RECON_MC) {
+    a = mc_left(m1.a, z.a, p1.a);
+    b = mc_left(m1.b, z.b, p1.b);
+  } else {
+    const Pair<double> m2 = q[c - 2 * s], p2 = q[c + 2 * s];
+    a = wv::weno5(m2.a, m1.a, z.a, p1.a, p2.a, eps);
+    b = wv::weno5(m2.b, m1.b, z.b, p1.b, p2.b, eps);
+  }
+}
+
 // LLF flux of the ten variables through the lower D-face of zone (i, j, k),
 // the face metric from tab; pole faces get zero.  The normal field's flux is
 // not stored (Flux-CT reads only the tangential ones).
@@ -138,37 +194,46 @@ __device__ __forceinline__ void emhd_face(const Dev& g, const double* __restrict
     return;
   }
   const long s = D == 1 ? 1 : (D == 2 ? (long)g.s1 : g.plane);
-  double qL[NVAR], qR[NVAR], xL[NXV], xR[NXV];
-  recon_pair<RECON, double>(P, g.nz, c, s, g.weno_eps, qL, qR);
-#pragma unroll
-  for (int n = 0; n < NXV; n++) recon_face<RECON, double>(X + 2 * c + n, 2 * s, g.weno_eps, xL[n], xR[n]);
   PointMetric<double> m;
   load_metric<double>(tab, g.plane, pid(g, i, j), m);
-  Fluid<double> fl, fr;
-  fluid_state(qL, m, fl);
-  fluid_state(qR, m, fr);
-  double FL[NVAR + NXV], FR[NVAR + NXV], UL[NVAR + NXV], UR[NVAR + NXV];
-  prim_to_flux_emhd(g, qL, xL, fl, m, D, FL);
-  prim_to_flux_emhd(g, qR, xR, fr, m, D, FR);
-  prim_to_flux_emhd(g, qL, xL, fl, m, 0, UL);
-  prim_to_flux_emhd(g, qR, xR, fr, m, 0, UR);
-  double cpl, cml, cpr, cmr;
-  char_speeds(qL, fl, m, g.gam, D, cpl, cml);
-  char_speeds(qR, fr, m, g.gam, D, cpr, cmr);
-  double cmax = 0.0;
-  if (cpl > cmax) cmax = cpl;
-  if (cpr > cmax) cmax = cpr;
-  if (-cml > cmax) cmax = -cml;
-  if (-cmr > cmax) cmax = -cmr;
+  // one side at a time: F_L + F_R in S, U_R - U_L in J
+  double S[NVAR + NXV] = {}, J[NVAR + NXV] = {}, cmax = 0.0;
+#pragma unroll 1
+  for (int side = 0; side < 2; side++) {
+    const long z = side ? c : c - s, t = side ? -s : s;
+    double q[NVAR], x[NXV];
+#pragma unroll
+    for (int v = 0; v < NVAR; v += 2)
+      recon_edge<RECON>((const Pair<double>*)P + (v >> 1) * g.nz, z, t, g.weno_eps, q[v], q[v + 1]);
+    recon_edge<RECON>((const Pair<double>*)X, z, t, g.weno_eps, x[0], x[1]);
+    Fluid<double> f;
+    fplain::fluid_state(q, m, f);
+    double Fd[NVAR + NXV], Ut[NVAR + NXV], cp, cm;
+    prim_to_flux_emhd(g, q, x, f, m, D, Fd);
+    prim_to_flux_emhd(g, q, x, f, m, 0, Ut);
+#pragma unroll
+    for (int v = 0; v < NVAR + NXV; v++)
+      if (v != B1 + D - 1) {
+        S[v] = S[v] + Fd[v];
+        J[v] = Ut[v] - J[v];
+      }
+    fplain::char_speeds(q, f, m, g.gam, D, cp, cm);
+    if (cp > cmax) cmax = cp;
+    if (-cm > cmax) cmax = -cm;
+  }
   double f[NVAR + NXV];
 #pragma unroll
   for (int v = 0; v < NVAR + NXV; v++)
-    if (v != B1 + D - 1) f[v] = 0.5 * (FL[v] + FR[v]) - 0.5 * cmax * (UR[v] - UL[v]);
+    if (v != B1 + D - 1) f[v] = 0.5 * S[v] - 0.5 * cmax * J[v];
   store_flux<D>(F, g.nz, c, f, g.stream);
   ((Pair<double>*)FX)[c] = Pair<double>{f[NVAR], f[NVAR + 1]};
 }
 
-// All three face directions in one launch, partitioned as k_flux_all.
+// All three face directions in one launch, partitioned as k_flux_all.  Bound by
+// FP64 arithmetic (about 3000 operations per WENO5 face).  One side's states at
+// a time, in a loop that is not unrolled: both at once need more than the 256
+// registers of two waves per SIMD (64^3 torus, WENO5: 151 us with 396 bytes of
+// scratch, 76 us so, with 154 registers and three waves).
 template <int RECON>
 __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(2, 8)))
 k_flux_emhd(Dev g, Sched b1, Sched b2, Sched b3, unsigned nb1, unsigned nb2, unsigned nb3,
@@ -217,8 +282,8 @@ __device__ __forceinline__ void emhd_targets(const Dev& g, const double* __restr
     load_metric<double>(tabC, g.plane, q2 + qs, mp);
     load_metric<double>(tabC, g.plane, q2 - qs, mm);
     Fluid<double> sp, sm;
-    fluid_state(pp, mp, sp);
-    fluid_state(pm, mm, sm);
+    fplain::fluid_state(pp, mp, sp);
+    fplain::fluid_state(pm, mm, sm);
     const double thp = (gam - 1.0) * pp[UU] / pp[RHO];
     const double thm = (gam - 1.0) * pm[UU] / pm[RHO];
     const double h2 = 2.0 * dx[a];
@@ -282,7 +347,7 @@ k_targets_emhd(Dev g, Sched box, const double* __restrict__ Pin, const double* _
   PointMetric<double> m;
   load_metric<double>(tabC, g.plane, pid(g, i, j), m);
   Fluid<double> f;
-  fluid_state(p, m, f);
+  fplain::fluid_state(p, m, f);
   double Xt[NXV], dsp;
   emhd_targets(g, Pin, tabC, conn, i, j, k, p, f, m, Xt, dsp);
   ((Pair<double>*)xt)[c] = Pair<double>{Xt[0], Xt[1]};
@@ -318,7 +383,7 @@ k_update_emhd(Dev g, Sched box, const double* __restrict__ Pin, const double* __
   PointMetric<double> m;
   load_metric<double>(tabC, g.plane, q2, m);
   Fluid<double> f;
-  fluid_state(p, m, f);
+  fplain::fluid_state(p, m, f);
   double qh, dPh;
   emhd_unscale(g, p, x, qh, dPh);
 
@@ -335,19 +400,20 @@ k_update_emhd(Dev g, Sched box, const double* __restrict__ Pin, const double* __
 #pragma unroll
         for (int l = 0; l < 4; l++) s[nu] += Tk[l] * conn[(l * 10 + sidx(nu, kk)) * g.plane + q2];
     }
+    const double r1 = plain_rcp(g.dx1), r2 = plain_rcp(g.dx2), r3 = plain_rcp(g.dx3);
     double lo[5], hi[5];
     load_flux5(F1, nz, c, lo);
     load_flux5(F1, nz, c + si, hi);
 #pragma unroll
-    for (int v = 0; v < 5; v++) L[v] = (hi[v] - lo[v]) / g.dx1;
+    for (int v = 0; v < 5; v++) L[v] = quotient(hi[v] - lo[v], g.dx1, r1);
     load_flux5(F2, nz, c, lo);
     load_flux5(F2, nz, c + sj, hi);
 #pragma unroll
-    for (int v = 0; v < 5; v++) L[v] = L[v] + (hi[v] - lo[v]) / g.dx2;
+    for (int v = 0; v < 5; v++) L[v] = L[v] + quotient(hi[v] - lo[v], g.dx2, r2);
     load_flux5(F3, nz, c, lo);
     load_flux5(F3, nz, c + sk, hi);
 #pragma unroll
-    for (int v = 0; v < 5; v++) L[v] = -(L[v] + (hi[v] - lo[v]) / g.dx3) + (v == RHO ? 0.0 : m.gdet * s[v - 1]);
+    for (int v = 0; v < 5; v++) L[v] = -(L[v] + quotient(hi[v] - lo[v], g.dx3, r3)) + (v == RHO ? 0.0 : m.gdet * s[v - 1]);
     ct_field_rate(g, E1, E2, E3, c, L);
   }
   double LX[NXV];
@@ -387,7 +453,12 @@ k_update_emhd(Dev g, Sched box, const double* __restrict__ Pin, const double* __
 // solved for X inside every residual; the Newton runs on the five hydro
 // prims from the stage input (the guess), the field is xrhs's B /
 // sqrt(-g).  On failure the zone keeps the guess's hydro prims and X (the
-// field still updated) and is counted.  With RATE the CFL-rate partials of
+// field still updated) and is counted.  Bound by FP64 arithmetic, some 30
+// residuals per zone and more where a lane of the wave does not converge:
+// shared reciprocals and the quotients without range handling took a residual
+// from ~550 to ~300 instructions (64^3 torus: 387 -> 250 us per launch, 1080 ->
+// 700 in a first step).  Three waves per SIMD (168 registers) spill: 6 % slower
+// step.  With RATE the CFL-rate partials of
 // the new prims (ideal signal speeds), over the update's schedule.
 template <int STAGE, bool RATE>
 __global__ void __launch_bounds__(BLOCK)
@@ -423,13 +494,15 @@ k_implicit_emhd(Dev g, Sched box, const double* __restrict__ Pin, const double* 
     out[B2] = Us[B2] / gd;
     out[B3] = Us[B3] / gd;
     const double B[3] = {out[B1], out[B2], out[B3]};
+    const double ih = plain_rcp(h), htau = h * gd / g.tau;
     // X of a hydro state with fluid state fz
     auto xsolve = [&](const Fluid<double>& fz, double Xz[NXV]) {
       const double ut = fz.ucon[0];
-      const double du = dsp + (ut - ut_n) / h;
-      const double coef = gd * ut + h * gd / g.tau - 0.5 * h * gd * du;
+      const double du = dsp + quotient(ut - ut_n, h, ih);
+      const double coef = gd * ut + htau - 0.5 * h * gd * du;
+      const double ic = plain_rcp(coef);
 #pragma unroll
-      for (int n = 0; n < NXV; n++) Xz[n] = Ux[n] / coef;
+      for (int n = 0; n < NXV; n++) Xz[n] = quotient(Ux[n], coef, ic);
     };
     double scale = 0.0;
 #pragma unroll
@@ -438,10 +511,11 @@ k_implicit_emhd(Dev g, Sched box, const double* __restrict__ Pin, const double* 
     bool ok = scale > 0.0 && isfinite(scale);
     double xs[5];
     if (ok) {
+      const double iscale = plain_rcp(scale);
       auto res = [&](const double xx[5], double R[5]) {
         const double Pz[NVAR] = {xx[0], xx[1], xx[2], xx[3], xx[4], B[0], B[1], B[2]};
         Fluid<double> fz;
-        fluid_state(Pz, m, fz);
+        fplain::fluid_state(Pz, m, fz);
         double Xz[NXV];
         xsolve(fz, Xz);
         double q, dP;
@@ -455,14 +529,14 @@ k_implicit_emhd(Dev g, Sched box, const double* __restrict__ Pin, const double* 
         U[U2] = gd * T[2];
         U[U3] = gd * T[3];
 #pragma unroll
-        for (int kk = 0; kk < 5; kk++) R[kk] = (U[kk] - Us[kk]) / scale;
+        for (int kk = 0; kk < 5; kk++) R[kk] = quotient(U[kk] - Us[kk], scale, iscale);
       };
       ok = newton_hydro(g, gs, res, xs, jac + threadIdx.x);
     }
     if (ok) {
       const double Pn[NVAR] = {xs[0], xs[1], xs[2], xs[3], xs[4], B[0], B[1], B[2]};
       Fluid<double> fz;
-      fluid_state(Pn, m, fz);
+      fplain::fluid_state(Pn, m, fz);
       xsolve(fz, xo);
 #pragma unroll
       for (int n = 0; n < NXV; n++)
@@ -481,7 +555,7 @@ k_implicit_emhd(Dev g, Sched box, const double* __restrict__ Pin, const double* 
     store8(Pout, nz, c, out);
 #pragma unroll
     for (int n = 0; n < NXV; n++) Xout[2 * c + n] = xo[n];
-    if (RATE) r = zone_rate(g, out, m);
+    if (RATE) r = zone_rate_ordered(g, out, m);
   }
   if (RATE) {
     double sm = 0.0;

@@ -1303,6 +1303,28 @@ __device__ __forceinline__ double zone_rate(const Dev& g, const double p[NVAR],
   return isfinite(z) ? z : (double)INFINITY;
 }
 
+// The same bound, every operation rounded in the order written: Extended
+// GRMHD's steps (see recon_ordered for the reason).
+__device__ __forceinline__ double zone_rate_ordered(const Dev& g, const double p[NVAR],
+                                                    const PointMetric<double>& m) {
+  Fluid<double> f;
+  fluid_state(p, m, f);
+  double cp, cm, z = 0.0;
+  if (g.n1 > 1) {
+    char_speeds(p, f, m, g.gam, 1, cp, cm);
+    z += fmax(fabs(cp), fabs(cm)) / g.dx1;
+  }
+  if (g.n2 > 1) {
+    char_speeds(p, f, m, g.gam, 2, cp, cm);
+    z += fmax(fabs(cp), fabs(cm)) / g.dx2;
+  }
+  if (g.n3 > 1) {
+    char_speeds(p, f, m, g.gam, 3, cp, cm);
+    z += fmax(fabs(cp), fabs(cm)) / g.dx3;
+  }
+  return isfinite(z) ? z : (double)INFINITY;
+}
+
 // ----------------------------------------------------------------- update --
 
 __device__ __forceinline__ void load_conn(const double* __restrict__ conn, long plane, long q,
@@ -1699,6 +1721,7 @@ k_implicit(Dev g, Sched box, const double* __restrict__ Pin, const double* __res
 // Per zone sum_d max(|c+|, |c-|)/dx_d over axes with more than one zone;
 // workgroup maxima to partial[].  Grid-stride over the box, so any grid size
 // reduces through at most MAX_PARTIALS partials.
+template <bool ORDERED>
 __global__ void __launch_bounds__(BLOCK) k_dt_partial(Dev g, Box box, const double* __restrict__ P,
                                                       const double* __restrict__ tabC,
                                                       double* partial) {
@@ -1712,7 +1735,7 @@ __global__ void __launch_bounds__(BLOCK) k_dt_partial(Dev g, Box box, const doub
     load8(P, g.nz, c, p);
     PointMetric<double> m;
     load_metric<double>(tabC, g.plane, pid(g, i, j), m);
-    s = fmax(s, zone_rate(g, p, m));
+    s = fmax(s, ORDERED ? zone_rate_ordered(g, p, m) : zone_rate(g, p, m));
   }
   double sm = 0.0;
   block_reduce(s, sm);
@@ -2499,11 +2522,12 @@ int launch_dt(grmhd_ctx* c, bool in_update = false) {
   long nb = blocks_for(bz.count());
   if (nb > MAX_PARTIALS) nb = MAX_PARTIALS;
   c->cfl_n = 0;
+  const auto partial = c->params.egrmhd ? k_dt_partial<true> : k_dt_partial<false>;
   if (in_update && !(c->timing & (1u << T_DT)) && (c->rate_ready ? c->rate_n : nb) <= CFL_IN_UPDATE) {
     c->cfl_part = c->rate_ready ? c->pdt : c->pmax;
     c->cfl_n = c->rate_ready ? c->rate_n : (int)nb;
     if (c->rate_ready) return GRMHD_OK;
-    return launch(c, T_DT, k_dt_partial, (unsigned)nb, g, bz, (const double*)c->P, (const double*)c->tabC, c->pmax);
+    return launch(c, T_DT, partial, (unsigned)nb, g, bz, (const double*)c->P, (const double*)c->tabC, c->pmax);
   }
   EvPair e = timing_events(c, T_DT);
   if (c->rate_ready) {
@@ -2512,7 +2536,7 @@ int launch_dt(grmhd_ctx* c, bool in_update = false) {
                           c->params.cfl);
     return hip_check();
   }
-  hipExtLaunchKernelGGL(k_dt_partial, dim3((unsigned)nb), dim3(BLOCK), 0, c->stream, e.a, nullptr, 0, g,
+  hipExtLaunchKernelGGL(partial, dim3((unsigned)nb), dim3(BLOCK), 0, c->stream, e.a, nullptr, 0, g,
                         bz, (const double*)c->P, (const double*)c->tabC, c->pmax);
   hipExtLaunchKernelGGL(k_reduce_final, dim3(1), dim3(BLOCK), 0, c->stream, nullptr, e.b, 0,
                         (const double*)c->pmax, (const double*)nullptr, (int)nb, c->result, c->params.cfl);

@@ -362,7 +362,7 @@ __device__ __forceinline__ bool qr_pivot_solve(const LdsMat& A, double b[5], dou
     double nrm = 0.0;
 #pragma unroll
     for (int i = k; i < 5; i++) nrm += A(i, k) * A(i, k);
-    nrm = sqrt(nrm);
+    nrm = plain_sqrt(nrm);
     if (!(nrm > 0.0) || !isfinite(nrm)) return false;
     const double alpha = A(k, k) > 0.0 ? -nrm : nrm;
     double v[5];
@@ -373,19 +373,20 @@ __device__ __forceinline__ bool qr_pivot_solve(const LdsMat& A, double b[5], dou
 #pragma unroll
     for (int i = k; i < 5; i++) vv += v[i] * v[i];
     if (!(vv > 0.0)) return false;
+    const double ivv = plain_rcp(vv);
 #pragma unroll
     for (int j = k; j < 5; j++) {
       double d = 0.0;
 #pragma unroll
       for (int i = k; i < 5; i++) d += v[i] * A(i, j);
-      const double f = 2.0 * d / vv;
+      const double f = quotient(2.0 * d, vv, ivv);
 #pragma unroll
       for (int i = k; i < 5; i++) A(i, j) = A(i, j) - f * v[i];
     }
     double d = 0.0;
 #pragma unroll
     for (int i = k; i < 5; i++) d += v[i] * b[i];
-    const double f = 2.0 * d / vv;
+    const double f = quotient(2.0 * d, vv, ivv);
 #pragma unroll
     for (int i = k; i < 5; i++) b[i] = b[i] - f * v[i];
 #pragma unroll
@@ -402,7 +403,7 @@ __device__ __forceinline__ bool qr_pivot_solve(const LdsMat& A, double b[5], dou
 #pragma unroll
     for (int j = i + 1; j < 5; j++) t = t - A(i, j) * z[j];
     if (!(fabs(A(i, i)) > 0.0)) return false;
-    z[i] = t / A(i, i);
+    z[i] = plain_div(t, A(i, i));
   }
 #pragma unroll
   for (int mm = 0; mm < 5; mm++) {
@@ -558,9 +559,9 @@ __device__ __forceinline__ bool newton_hydro(const Dev& g, const double x0[5], R
       for (int mm = 0; mm < 5; mm++) xp[mm] = mm == k ? xkh : x[mm];
       double Rp[5];
       res(xp, Rp);
-      const double hh = xkh - xk;
+      const double hh = xkh - xk, ihh = plain_rcp(hh);
 #pragma unroll
-      for (int mm = 0; mm < 5; mm++) J(mm, k) = (Rp[mm] - R[mm]) / hh;
+      for (int mm = 0; mm < 5; mm++) J(mm, k) = quotient(Rp[mm] - R[mm], hh, ihh);
     }
     double rhs[5], dx[5];
 #pragma unroll

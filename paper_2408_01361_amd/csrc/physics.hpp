@@ -199,6 +199,50 @@ __device__ __forceinline__ R fdiv(R a, R b) { return a * __builtin_amdgcn_rcpf(b
 #include "physics_body.inc"
 }  // namespace f32
 
+// a / b from r = 1/b: correctly rounded but for rare ties.
+__device__ __forceinline__ double quotient(double a, double b, double r) {
+  const double q = a * r;
+  return fma(fma(-b, q, a), r, q);
+}
+
+__device__ __forceinline__ double hw_rsqrt(double x) {
+#ifdef __AMDGCN__
+  return __builtin_amdgcn_rsq(x);
+#else
+  return 1.0 / sqrt(x);
+#endif
+}
+
+// FP64 quotient and square root without the scaling and the special cases of
+// the correctly rounded ones: the same reciprocal, Newton and residual steps,
+// so the same bits wherever no operand or intermediate is subnormal, infinite
+// or NaN (a quotient by zero or infinity is NaN here).  A reciprocal shared by
+// several quotients is formed once.
+__device__ __forceinline__ double plain_rcp(double d) {
+  double r = __builtin_amdgcn_rcp(d);
+  r = fma(fma(-d, r, 1.0), r, r);
+  return fma(fma(-d, r, 1.0), r, r);
+}
+__device__ __forceinline__ double plain_div(double n, double d) { return quotient(n, d, plain_rcp(d)); }
+__device__ __forceinline__ double plain_sqrt(double x) {
+  const double y = hw_rsqrt(x), k = 0.5 * y;
+  double g = x * y;
+  const double r = fma(-k, g, 0.5);
+  const double h = fma(k, r, k);
+  g = fma(g, r, g);
+  g = fma(fma(-g, g, x), h, g);
+  g = fma(fma(-g, g, x), h, g);
+  return x == 0.0 ? x : g;
+}
+// The per-point physics on them (Extended GRMHD).
+namespace fplain {
+using R = double;
+#pragma clang fp contract(off)
+__device__ __forceinline__ R fdiv(R a, R b) { return plain_div(a, b); }
+__device__ __forceinline__ R sqrt(R x) { return plain_sqrt(x); }
+#include "physics_body.inc"
+}  // namespace fplain
+
 // Dual numbers: local Jacobians for the adjoint.
 namespace fdual {
 using R = Dual;
@@ -583,19 +627,6 @@ __device__ __forceinline__ double face_rcp(double x) {
 }
 __device__ __forceinline__ float face_rcp(float x) { return __builtin_amdgcn_rcpf(x); }
 
-// a / b from r = 1/b: correctly rounded but for rare ties.
-__device__ __forceinline__ double quotient(double a, double b, double r) {
-  const double q = a * r;
-  return fma(fma(-b, q, a), r, q);
-}
-
-__device__ __forceinline__ double hw_rsqrt(double x) {
-#ifdef __AMDGCN__
-  return __builtin_amdgcn_rsq(x);
-#else
-  return 1.0 / sqrt(x);
-#endif
-}
 // sqrt(x) for normal x > 0 (Goldschmidt from the hardware estimate; about an
 // ulp), and with it h close to 1 / (2 sqrt(x)) (2^-46 relative).
 __device__ __forceinline__ double face_sqrt(double x, double& h) {
