@@ -1,6 +1,6 @@
-// Forward-mode dual number (value and one directional derivative) used to
-// form the local Jacobians of the per-point physics in the hand-written
-// adjoint.  Comparisons act on the value, so min/max and limiter branches
+// Forward-mode dual number (value and one directional derivative): the
+// derivatives of the per-point physics that the hand-written adjoint's
+// reverse sweeps are tested against.  Comparisons act on the value, so min/max and limiter branches
 // select the derivative of the branch taken (a subgradient at ties).
 #pragma once
 

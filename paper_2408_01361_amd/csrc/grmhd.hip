@@ -236,25 +236,6 @@ __device__ __forceinline__ int bc_map(int x, int n, int bclo, int bchi, bool& fl
   return x;
 }
 
-// Padded positions along one axis whose ghost fill copies interior x (x
-// itself included), with the polar sign.
-__device__ __forceinline__ int bc_preimages(int x, int n, int bclo, int bchi, int ys[7], bool fl[7]) {
-  int cnt = 0;
-  ys[cnt] = x;
-  fl[cnt++] = false;
-  for (int y = -NG; y < 0; y++) {
-    bool f = false;
-    if (bclo == GRMHD_BC_FROZEN) continue;
-    if (bc_map(y, n, bclo, bchi, f) == x) { ys[cnt] = y; fl[cnt++] = f; }
-  }
-  for (int y = n; y < n + NG; y++) {
-    bool f = false;
-    if (bchi == GRMHD_BC_FROZEN) continue;
-    if (bc_map(y, n, bclo, bchi, f) == x) { ys[cnt] = y; fl[cnt++] = f; }
-  }
-  return cnt;
-}
-
 // Ghost shell of the padded grid, enumerated without touching interior
 // zones: the 6 x3 ghost planes (all x1, x2), then the 6 x2 ghost rows of every
 // interior x3 plane (all x1), then the 6 x1 ghost zones of every interior
@@ -2978,15 +2959,30 @@ const char* grmhd_strerror(int code) {
 
 namespace {
 
+// The boxes of the adjoint's face and zone kernels, and their workgroups.
+struct AdjBoxes {
+  Box b1, b2, b3, bz;
+  AdjBoxes(int n1, int n2, int n3)
+      : b1(make_box(0, n1, -1, n2, -1, n3)),
+        b2(make_box(-1, n1, 0, n2, -1, n3)),
+        b3(make_box(-1, n1, -1, n2, 0, n3)),
+        bz(make_box(0, n1 - 1, 0, n2 - 1, 0, n3 - 1)) {}
+  unsigned faces() const { return blocks_for(b1.count()) + blocks_for(b2.count()) + blocks_for(b3.count()); }
+  unsigned zones() const { return blocks_for(bz.count()); }
+};
+
 struct VjpCarve {
-  double *A, *B, *C, *LV, *LL, *LP, *LPh, *LG, *LE[3], *LS[3], *GZ, *GF[3];
+  double *A, *B, *C, *LV, *LL, *LP, *LPh, *LE[3], *G[3], *part;
+  long npart;   // gamma parts: one per workgroup of the kernels that have any
   unsigned char *fl1, *fl2;
   unsigned long long* fails;
 };
 
 size_t vjp_carve(const grmhd_grid* g, int recon, char* base, VjpCarve* out) {
   long nz = (long)(g->n1 + 2 * NG) * (g->n2 + 2 * NG) * (g->n3 + 2 * NG);
-  int W = recon == GRMHD_RECON_MC ? Stencil<GRMHD_RECON_MC>::W : Stencil<GRMHD_RECON_WENO5>::W;
+  const AdjBoxes x(g->n1, g->n2, g->n3);
+  // per face: both states' adjoints (MC), or those of all stencil inputs
+  const long per_face = recon == GRMHD_RECON_MC ? 2 * NVAR : NVAR * Stencil<GRMHD_RECON_WENO5>::W;
   Carve cv;
   VjpCarve v;
   v.A = cv.take<double>(base, NVAR * nz);
@@ -2994,13 +2990,12 @@ size_t vjp_carve(const grmhd_grid* g, int recon, char* base, VjpCarve* out) {
   v.C = cv.take<double>(base, NVAR * nz);
   v.LV = cv.take<double>(base, NVAR * nz);
   v.LL = cv.take<double>(base, NVAR * nz);
-  v.LP = cv.take<double>(base, NVAR * nz);
+  v.LP = cv.take<double>(base, 5 * nz);
   v.LPh = cv.take<double>(base, NVAR * nz);
-  v.LG = cv.take<double>(base, 5 * nz);
   for (int d = 0; d < 3; d++) v.LE[d] = cv.take<double>(base, nz);
-  for (int d = 0; d < 3; d++) v.LS[d] = cv.take<double>(base, (long)NVAR * W * nz);
-  v.GZ = cv.take<double>(base, nz);
-  for (int d = 0; d < 3; d++) v.GF[d] = cv.take<double>(base, nz);
+  for (int d = 0; d < 3; d++) v.G[d] = cv.take<double>(base, per_face * nz);
+  v.npart = blocks_for(nz) + 2L * (x.faces() + x.zones());
+  v.part = cv.take<double>(base, v.npart);
   v.fl1 = cv.take<unsigned char>(base, nz);
   v.fl2 = cv.take<unsigned char>(base, nz);
   v.fails = cv.take<unsigned long long>(base, 8);
@@ -3008,29 +3003,24 @@ size_t vjp_carve(const grmhd_grid* g, int recon, char* base, VjpCarve* out) {
   return cv.off;
 }
 
-template <int RECON>
-int adj_stage(grmhd_ctx* c, const VjpCarve& w, const double* Pin, bool stage1, double* LPout) {
+// One stage of the reverse sweep, from LL (and, in stage 1, LV) to the adjoint
+// of the stage's input: into gin (stage 1), or on through stage 1's inversion
+// into LV and LL (k_adj_zone).  Gamma parts from part on.
+template <int RECON, bool STAGE1>
+int adj_stage(grmhd_ctx* c, const VjpCarve& w, const double* Pin, const unsigned char* flags, const double* LPout,
+              double dt, double* gin, double*& part) {
   const Dev& g = c->dev;
-  const long nz = g.nz;
-  k_adj_emf<<<blocks_for(nz), BLOCK, 0, c->stream>>>(g, w.LL, w.LE[0], w.LE[1], w.LE[2]);
-  Box b1 = make_box(0, g.n1, -1, g.n2, -1, g.n3);
-  Box b2 = make_box(-1, g.n1, 0, g.n2, -1, g.n3);
-  Box b3 = make_box(-1, g.n1, -1, g.n2, 0, g.n3);
-  k_adj_face<1, RECON><<<blocks_for(b1.count()), BLOCK, 0, c->stream>>>(g, b1, Pin, c->tabF1, w.LL, w.LE[0],
-                                                                      w.LE[1], w.LE[2], w.LS[0], w.GF[0]);
-  k_adj_face<2, RECON><<<blocks_for(b2.count()), BLOCK, 0, c->stream>>>(g, b2, Pin, c->tabF2, w.LL, w.LE[0],
-                                                                      w.LE[1], w.LE[2], w.LS[1], w.GF[1]);
-  k_adj_face<3, RECON><<<blocks_for(b3.count()), BLOCK, 0, c->stream>>>(g, b3, Pin, c->tabC, w.LL, w.LE[0],
-                                                                      w.LE[1], w.LE[2], w.LS[2], w.GF[2]);
-  k_adj_gather<RECON><<<blocks_for(nz), BLOCK, 0, c->stream>>>(g, b1, b2, b3, w.LS[0], w.LS[1], w.LS[2],
-                                                               w.LPh);
-  Box bz = make_box(0, g.n1 - 1, 0, g.n2 - 1, 0, g.n3 - 1);
-  if (stage1)
-    k_adj_zone<true><<<blocks_for(bz.count()), BLOCK, 0, c->stream>>>(g, bz, Pin, c->tabC, c->conn, w.LPh,
-                                                                      w.LL, w.LV, w.LG, LPout, w.GZ);
-  else
-    k_adj_zone<false><<<blocks_for(bz.count()), BLOCK, 0, c->stream>>>(g, bz, Pin, c->tabC, c->conn, w.LPh,
-                                                                       w.LL, nullptr, w.LG, LPout, w.GZ);
+  const AdjBoxes x(g.n1, g.n2, g.n3);
+  k_adj_emf<<<blocks_for(g.nz), BLOCK, 0, c->stream>>>(g, w.LL, w.LE[0], w.LE[1], w.LE[2]);
+  k_adj_face<RECON><<<x.faces(), BLOCK, 0, c->stream>>>(g, x.b1, x.b2, x.b3, blocks_for(x.b1.count()),
+                                                        blocks_for(x.b2.count()), Pin, c->tabF1, c->tabF2, c->tabC,
+                                                        w.LL, w.LE[0], w.LE[1], w.LE[2], w.G[0], w.G[1], w.G[2], part);
+  part += x.faces();
+  k_adj_gather<RECON><<<blocks_for(g.nz), BLOCK, 0, c->stream>>>(g, Pin, w.G[0], w.G[1], w.G[2], w.LPh,
+                                                                 STAGE1 ? gin : nullptr);
+  k_adj_zone<STAGE1><<<x.zones(), BLOCK, 0, c->stream>>>(g, x.bz, Pin, flags, w.fl1, c->tabC, c->dgs, dt, w.LPh, LPout,
+                                                         w.LL, w.LV, STAGE1 ? gin : w.LP, part);
+  part += x.zones();
   return hip_check();
 }
 
@@ -3039,7 +3029,6 @@ int step_vjp(grmhd_ctx* c, const VjpCarve& w, const double* d_in, double dt, con
              double* d_gin, double* g_gamma) {
   const Dev& g = c->dev;
   const long nz = g.nz;
-  const size_t bytes = sizeof(double) * NVAR * nz;
   int rc;
   // forward recompute from the checkpoint: A = P^n, B = P^(1), C = P^(n+1).
   // The updates write interior zones (prims and failure flags); B's ghosts
@@ -3049,11 +3038,7 @@ int step_vjp(grmhd_ctx* c, const VjpCarve& w, const double* d_in, double dt, con
   bool frozen = false;
   for (int f = 0; f < 6; f++) frozen = frozen || c->grid.bc[f] == GRMHD_BC_FROZEN;
   k_load_state<<<blocks_for(nz), BLOCK, 0, c->stream>>>(nz, d_in, w.A, frozen ? w.B : nullptr);
-  if (hip_check() != GRMHD_OK || hipMemsetAsync(w.GZ, 0, sizeof(double) * nz, c->stream) != hipSuccess ||
-      hipMemsetAsync(d_gin, 0, bytes, c->stream) != hipSuccess)
-    return GRMHD_E_HIP;
-  for (int d = 0; d < 3; d++)
-    if (hipMemsetAsync(w.GF[d], 0, sizeof(double) * nz, c->stream) != hipSuccess) return GRMHD_E_HIP;
+  if ((rc = hip_check())) return rc;
   if ((rc = fill_ghosts(c, w.A))) return rc;
   if ((rc = stage_fluxes<double, double>(c, w.A))) return rc;
   if ((rc = stage_update<1, double>(c, w.A, w.B, dt, w.fails, w.fl1))) return rc;
@@ -3061,17 +3046,15 @@ int step_vjp(grmhd_ctx* c, const VjpCarve& w, const double* d_in, double dt, con
   if ((rc = stage_fluxes<double, double>(c, w.B))) return rc;
   if ((rc = stage_update<2, double>(c, w.B, w.C, dt, w.fails, w.fl2))) return rc;
   // reverse sweep
-  k_adj_ift<<<blocks_for(nz), BLOCK, 0, c->stream>>>(g, w.C, w.fl2, c->tabC, d_gout, 0, dt, w.LV, w.LL, w.LG,
-                                                     w.GZ);
+  double* part = w.part;
+  k_adj_ift<<<blocks_for(nz), BLOCK, 0, c->stream>>>(g, w.C, w.fl2, c->tabC, d_gout, dt, w.LV, w.LL, part);
+  part += blocks_for(nz);
   if ((rc = hip_check())) return rc;
-  if ((rc = adj_stage<RECON>(c, w, w.B, false, w.LP))) return rc;
-  k_adj_ift<<<blocks_for(nz), BLOCK, 0, c->stream>>>(g, w.B, w.fl1, c->tabC, w.LP, 1, dt, w.LV, w.LL, w.LG,
-                                                     w.GZ);
-  if ((rc = hip_check())) return rc;
-  if ((rc = adj_stage<RECON>(c, w, w.A, true, d_gin))) return rc;
-  long nb = blocks_for(nz);
+  if ((rc = adj_stage<RECON, false>(c, w, w.B, w.fl2, d_gout, dt, nullptr, part))) return rc;
+  if ((rc = adj_stage<RECON, true>(c, w, w.A, w.fl1, w.LP, dt, d_gin, part))) return rc;
+  long nb = blocks_for(w.npart);
   if (nb > MAX_PARTIALS) nb = MAX_PARTIALS;
-  k_adj_gsum<<<(unsigned)nb, BLOCK, 0, c->stream>>>(nz, w.GZ, w.GF[0], w.GF[1], w.GF[2], c->pmax, c->psum);
+  k_adj_gsum<<<(unsigned)nb, BLOCK, 0, c->stream>>>(w.npart, w.part, c->pmax, c->psum);
   k_reduce_final<<<1, BLOCK, 0, c->stream>>>(c->pmax, c->psum, (int)nb, c->result, 0.0);
   if ((rc = hip_check())) return rc;
   double res[2];

@@ -205,6 +205,13 @@ __device__ __forceinline__ double quotient(double a, double b, double r) {
   return fma(fma(-b, q, a), r, q);
 }
 
+// 1 / x to about an ulp.
+__device__ __forceinline__ double face_rcp(double x) {
+  const double r = __builtin_amdgcn_rcp(x);
+  const double e = fma(-x, r, 1.0);
+  return fma(r, fma(e, e, e), r);
+}
+
 __device__ __forceinline__ double hw_rsqrt(double x) {
 #ifdef __AMDGCN__
   return __builtin_amdgcn_rsq(x);
@@ -243,7 +250,8 @@ __device__ __forceinline__ R sqrt(R x) { return plain_sqrt(x); }
 #include "physics_body.inc"
 }  // namespace fplain
 
-// Dual numbers: local Jacobians for the adjoint.
+// Dual numbers: the derivatives that the adjoint's reverse sweeps are tested
+// against.
 namespace fdual {
 using R = Dual;
 __device__ __forceinline__ R fdiv(R a, R b) { return a / b; }
@@ -534,17 +542,18 @@ __device__ __forceinline__ void weno5_grad(double a, double b, double c, double 
   const double s0 = eps + (k * t0 * t0 + 0.25 * u0 * u0);
   const double s1 = eps + (k * t1 * t1 + 0.25 * u1 * u1);
   const double s2 = eps + (k * t2 * t2 + 0.25 * u2 * u2);
-  const double w0 = 0.1 / (s0 * s0), w1 = 0.6 / (s1 * s1), w2 = 0.3 / (s2 * s2);
-  const double iW = 1.0 / ((w0 + w1) + w2);
+  const double i0 = face_rcp(s0), i1 = face_rcp(s1), i2 = face_rcp(s2);
+  const double w0 = 0.1 * (i0 * i0), w1 = 0.6 * (i1 * i1), w2 = 0.3 * (i2 * i2);
+  const double iW = face_rcp((w0 + w1) + w2);
   const double o0 = w0 * iW, o1 = w1 * iW, o2 = w2 * iW;
-  const double p0 = ((2.0 * a - 7.0 * b) + 11.0 * c) / 6.0;
-  const double p1 = ((-b + 5.0 * c) + 2.0 * d) / 6.0;
-  const double p2 = ((2.0 * c + 5.0 * d) - e) / 6.0;
+  const double p0 = ((2.0 * a - 7.0 * b) + 11.0 * c) * (1.0 / 6.0);
+  const double p1 = ((-b + 5.0 * c) + 2.0 * d) * (1.0 / 6.0);
+  const double p2 = ((2.0 * c + 5.0 * d) - e) * (1.0 / 6.0);
   const double v = (o0 * p0 + o1 * p1) + o2 * p2;
   // -2 o_k (p_k - v) / s_k: the weight of dbeta_k/dx
-  const double r0 = -2.0 * o0 * (p0 - v) / s0;
-  const double r1 = -2.0 * o1 * (p1 - v) / s1;
-  const double r2 = -2.0 * o2 * (p2 - v) / s2;
+  const double r0 = -2.0 * o0 * (p0 - v) * i0;
+  const double r1 = -2.0 * o1 * (p1 - v) * i1;
+  const double r2 = -2.0 * o2 * (p2 - v) * i2;
   const double h = 13.0 / 6.0;
   g0 = o0 * (2.0 / 6.0) + r0 * (h * t0 + 0.5 * u0);
   g1 = (o0 * (-7.0 / 6.0) + o1 * (-1.0 / 6.0)) + (r0 * (-2.0 * h * t0 - 2.0 * u0) + r1 * (h * t1 + 0.5 * u1));
@@ -620,11 +629,6 @@ __device__ __forceinline__ void mc_right_grad(double l, double c, double r, doub
 // written form by rounding only.
 #pragma clang fp contract(off)
 
-__device__ __forceinline__ double face_rcp(double x) {
-  const double r = __builtin_amdgcn_rcp(x);
-  const double e = fma(-x, r, 1.0);
-  return fma(r, fma(e, e, e), r);
-}
 __device__ __forceinline__ float face_rcp(float x) { return __builtin_amdgcn_rcpf(x); }
 
 // sqrt(x) for normal x > 0 (Goldschmidt from the hardware estimate; about an
@@ -807,6 +811,7 @@ struct ZoneState {
   double bt, b1, b2, b3;      // magnetic four-vector
   double k0, k1, k2, k3;      // lowered
   double bsq, w, ptot, pg;    // w = rho + u + p + b^2
+  double iut;                 // 1 / u^t
 };
 __device__ __forceinline__ void zone_state(const double p[NVAR], const PointMetric<double>& m, double gam,
                                            ZoneState& z) {
@@ -815,8 +820,7 @@ __device__ __forceinline__ void zone_state(const double p[NVAR], const PointMetr
   const double ctt = m.gcon[sidx(0, 0)], ct1 = m.gcon[sidx(0, 1)];
   const double v1 = p[U1], v2 = p[U2], v3 = p[U3], Bc1 = p[B1], Bc2 = p[B2], Bc3 = p[B3];
   const double qsq = fma(g11 * v1, v1, fma(g22 * v2, v2, fma(g33 * v3, v3, 2.0 * (g13 * v1) * v3)));
-  double iut;
-  const double gamma = lorentz(1.0 + qsq, m.alpha, iut);
+  const double gamma = lorentz(1.0 + qsq, m.alpha, z.iut);
   z.ut = quotient(gamma, m.alpha, inverse_lapse(m.alpha, ctt));
   z.u1 = fma(-(gamma * m.alpha), ct1, v1);
   z.u2 = v2;
@@ -826,9 +830,9 @@ __device__ __forceinline__ void zone_state(const double p[NVAR], const PointMetr
   z.l2 = g22 * z.u2;
   z.l3 = fma(gt3, z.ut, fma(g13, z.u1, g33 * z.u3));
   z.bt = fma(Bc1, z.l1, fma(Bc2, z.l2, Bc3 * z.l3));
-  z.b1 = fma(z.bt, z.u1, Bc1) * iut;
-  z.b2 = fma(z.bt, z.u2, Bc2) * iut;
-  z.b3 = fma(z.bt, z.u3, Bc3) * iut;
+  z.b1 = fma(z.bt, z.u1, Bc1) * z.iut;
+  z.b2 = fma(z.bt, z.u2, Bc2) * z.iut;
+  z.b3 = fma(z.bt, z.u3, Bc3) * z.iut;
   z.k0 = fma(gtt, z.bt, fma(gt1, z.b1, gt3 * z.b3));
   z.k1 = fma(gt1, z.bt, fma(g11, z.b1, g13 * z.b3));
   z.k2 = g22 * z.b2;
