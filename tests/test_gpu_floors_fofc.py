@@ -190,3 +190,38 @@ def test_long_torus_run_with_kastaun_floors_and_correction():
     scale = np.abs(interior(P[5:8])).max() / min(grid.dx[:2])
     print("t", t, "counters", cnt, "divb max", mx, "scale", scale)
     assert mx < 1e-12 * scale
+
+
+def _reach_case(shape, bc, floors, roll):
+    import dataclasses
+    from workloads import BC_OUTFLOW, BC_PERIODIC
+    grid, P = magnetised_blast(48, noise=0.05 if floors else 0.0, seed=3)
+    n1, n2, n3 = shape
+    B = {"outflow": (BC_OUTFLOW,) * 6, "periodic": (BC_PERIODIC,) * 6,
+         "mixed": (BC_PERIODIC, BC_PERIODIC, BC_OUTFLOW, BC_OUTFLOW, BC_PERIODIC, BC_PERIODIC)}[bc]
+    at = lambda n, r: (np.arange(n) + r + max(0, (48 - n) // 2)) % 48
+    I = np.repeat(interior(P)[:, :, at(n2, 0)][..., at(n1, roll)], n3, axis=1)
+    Q = np.pad(I, ((0, 0), (3, 3), (3, 3), (3, 3)), mode="edge")
+    return dataclasses.replace(grid, n1=n1, n2=n2, n3=n3, bc=B), Q
+
+
+@pytest.mark.parametrize("shape,bc,floors,roll", [
+    ((48, 48, 1), "periodic", False, 24), ((48, 48, 1), "outflow", True, 12), ((37, 5, 3), "periodic", True, 20),
+    ((37, 6, 4), "mixed", True, 12), ((1, 40, 2), "periodic", True, 0), ((70, 9, 1), "mixed", True, 30)])
+def test_final_pass_where_the_correction_reaches(shape, bc, floors, roll):
+    """The final pass of the correction repeats the update only at zones that
+    share a face or an edge with a marked one (across periodic boundaries
+    too): prims, counters and the CFL step that follows are the oracle's, on
+    grids narrower than a stencil, with rows that are not a multiple of a
+    wavefront, and with open, periodic and mixed boundaries that the blast's
+    edge lies across.  Bars: the step bar, as above; the CFL step 1e-12 (it
+    follows the prims)."""
+    grid, Q = _reach_case(shape, bc, floors, roll)
+    out, ref, cnt, st, s, dts = run_both(grid, Q, 4 / 3, RECON_MC, 3, floors, True)
+    print(shape, bc, "gpu", cnt, "oracle", st, flush=True)
+    assert st["fofc_zones"] > 0
+    assert cnt == st
+    check(out, ref, label=f"{shape} {bc}", alt=run_both.alt)
+    c = oracle.cfg(grid, gam=4 / 3, recon=RECON_MC, floors=floors, fofc=True)
+    _, _, more = oracle.run(c, Q, -1, 4)
+    assert abs(s.dt() - more[3]) <= 1e-12 * more[3]
