@@ -112,6 +112,13 @@ __device__ __forceinline__ bool box_index(const Box& b, long t, int& i, int& j, 
   return true;
 }
 
+// Whether some side keeps the caller's ghosts.
+inline bool frozen_side(const Dev& g) {
+  bool frozen = false;
+  for (int a = 0; a < 6; a++) frozen = frozen || g.bc[a] == GRMHD_BC_FROZEN;
+  return frozen;
+}
+
 inline Box make_box(int lo1, int hi1, int lo2, int hi2, int lo3, int hi3) {
   return Box{lo1, lo2, lo3, hi1 - lo1 + 1, hi2 - lo2 + 1, hi3 - lo3 + 1};
 }
@@ -1104,23 +1111,40 @@ __global__ void k_export_fluxes(Dev g, Box box, const double* F1, const double* 
 
 // The caller's prims [8][padded] into the state (and, where given, the stage
 // buffer, which carries the same frozen ghosts), and the state back out.
-__global__ void __launch_bounds__(BLOCK) k_load_state(long nz, const double* __restrict__ src, double* __restrict__ P,
+// The stage buffer P1 (when given) gets the ghost zones only: its updates
+// write its interior, and its ghosts are filled except at frozen sides.  Of a
+// flat grid plane 0 alone is loaded, and read into every plane.  Bound by
+// memory (256^3: 629 us with a whole copy in P1, 421 so; 512^2 blast, 5 steps:
+// 1218 -> 1129 us).
+__device__ __forceinline__ bool ghost_zone(const Dev& g, long c) {
+  const unsigned q = (unsigned)c, r = q / (unsigned)g.s1;
+  const int i = (int)(q % (unsigned)g.s1) - NG, j = (int)(r % (unsigned)g.s2) - NG, k = (int)(r / (unsigned)g.s2) - NG;
+  return i < 0 || i >= g.n1 || j < 0 || j >= g.n2 || k < 0 || k >= g.n3;
+}
+__global__ void __launch_bounds__(BLOCK) k_load_state(Dev g, const double* __restrict__ src, double* __restrict__ P,
                                                       double* __restrict__ P1) {
-  const long c = blockIdx.x * (long)BLOCK + threadIdx.x;
-  if (c >= nz) return;
+  const long t = blockIdx.x * (long)BLOCK + threadIdx.x, nz = g.nz;
+  if (t >= (g.flat ? g.plane : nz)) return;
+  const long c = g.flat ? NG * g.plane + t : t;
   double p[NVAR];
 #pragma unroll
   for (int v = 0; v < NVAR; v++) p[v] = src[v * nz + c];
   store8(P, nz, c, p);
-  if (P1) store8(P1, nz, c, p);
+  if (P1 && ghost_zone(g, c)) store8(P1, nz, c, p);
 }
-__global__ void __launch_bounds__(BLOCK) k_read_state(long nz, const double* __restrict__ P, double* __restrict__ dst) {
-  const long c = blockIdx.x * (long)BLOCK + threadIdx.x;
-  if (c >= nz) return;
+__global__ void __launch_bounds__(BLOCK) k_read_state(Dev g, const double* __restrict__ P, double* __restrict__ dst) {
+  const long t = blockIdx.x * (long)BLOCK + threadIdx.x, nz = g.nz;
+  if (t >= (g.flat ? g.plane : nz)) return;
   double p[NVAR];
-  load8(P, nz, c, p);
+  load8(P, nz, g.flat ? NG * g.plane + t : t, p);
+  if (!g.flat) {
 #pragma unroll
-  for (int v = 0; v < NVAR; v++) dst[v * nz + c] = p[v];
+    for (int v = 0; v < NVAR; v++) dst[v * nz + t] = p[v];
+    return;
+  }
+  for (int k = 0; k < 1 + 2 * NG; k++)
+#pragma unroll
+    for (int v = 0; v < NVAR; v++) dst[v * nz + k * g.plane + t] = p[v];
 }
 
 #include "inversion.hpp"
@@ -2752,8 +2776,7 @@ int grmhd_create(grmhd_ctx** out, const grmhd_grid* grid, const grmhd_metric* me
   // The update fills its zones' ghosts itself where that is the last word on
   // them (no floors, no other pass after it; no frozen side, whose ghosts other
   // ghosts copy) and a launch counts more than the extra stores.
-  bool frozen = false;
-  for (int a = 0; a < 6; a++) frozen = frozen || grid->bc[a] == GRMHD_BC_FROZEN;
+  const bool frozen = frozen_side(c->dev);
   c->flat.images = params->ct == GRMHD_CT_FLUX && !params->floors && !params->fofc && !params->egrmhd &&
                    params->inverter != GRMHD_INV_IMPLICIT && !frozen && grid->n1 >= 2 * NG && grid->n2 >= 2 * NG &&
                    (grid->n3 >= 2 * NG || c->flat.flat) && c->dev.nz <= IMAGE_ZONES && !c->flat.stream;
@@ -2779,7 +2802,9 @@ int grmhd_load_prims(grmhd_ctx* c, const double* d_prims) {
   if (!c || !d_prims) return GRMHD_E_ARG;
   c->rate_ready = false;
   c->ghosts_valid = c->plane_valid = false;
-  k_load_state<<<blocks_for(c->dev.nz), BLOCK, 0, c->stream>>>(c->dev.nz, d_prims, c->P, c->P1);
+  const Dev& g = c->flat;
+  k_load_state<<<blocks_for(g.flat ? g.plane : g.nz), BLOCK, 0, c->stream>>>(g, d_prims, c->P,
+                                                                             frozen_side(g) ? c->P1 : nullptr);
   int rc = hip_check();
   if (rc) return rc;
   // face-centred CT: the zones' field is their faces' mean
@@ -2899,8 +2924,12 @@ int grmhd_last_dt(grmhd_ctx* c, double* dt_out) {
 int grmhd_get_prims(grmhd_ctx* c, double* d_out) {
   if (!c || !d_out) return GRMHD_E_ARG;
   int rc;
-  if ((rc = ensure_ghosts(c))) return rc;
-  k_read_state<<<blocks_for(c->dev.nz), BLOCK, 0, c->stream>>>(c->dev.nz, (const double*)c->P, d_out);
+  const Dev& g = c->flat;
+  if (g.flat) c->cur = &c->flat;   // plane 0's ghosts are enough
+  rc = ensure_ghosts(c);
+  c->cur = &c->dev;
+  if (rc) return rc;
+  k_read_state<<<blocks_for(g.flat ? g.plane : g.nz), BLOCK, 0, c->stream>>>(g, (const double*)c->P, d_out);
   return hip_check();
 }
 
@@ -3097,9 +3126,7 @@ int step_vjp(grmhd_ctx* c, const VjpCarve& w, const double* d_in, double dt, con
   // are filled before they are read, except frozen ones, which keep the
   // input's (hence the copy only then); C and the flags are read at
   // interior zones only (the inversion's adjoint).
-  bool frozen = false;
-  for (int f = 0; f < 6; f++) frozen = frozen || c->grid.bc[f] == GRMHD_BC_FROZEN;
-  k_load_state<<<blocks_for(nz), BLOCK, 0, c->stream>>>(nz, d_in, w.A, frozen ? w.B : nullptr);
+  k_load_state<<<blocks_for(nz), BLOCK, 0, c->stream>>>(g, d_in, w.A, frozen_side(g) ? w.B : nullptr);
   if ((rc = hip_check())) return rc;
   if ((rc = fill_ghosts(c, w.A))) return rc;
   if ((rc = stage_fluxes<double, double>(c, w.A))) return rc;
@@ -3283,10 +3310,10 @@ int pack_upload(grmhd_pack* pk) {
   return GRMHD_OK;
 }
 
-// Blocks by chunks of the largest block's padded zones.
-dim3 pack_zone_grid(const grmhd_pack* pk) {
-  const unsigned chunks = ((unsigned)pk->max_nz + BLOCK - 1) / BLOCK;
-  return dim3((unsigned)pk->nb, chunks < 65535u ? chunks : 65535u);
+// Workgroups per block of k_pack_load and k_pack_read.
+unsigned pack_chunks(const grmhd_pack* pk) {
+  const unsigned chunks = ((unsigned)pk->max_nz + BLOCK - 1) / BLOCK, most = (1u << 30) / (unsigned)pk->nb;
+  return chunks < most ? chunks : most;
 }
 
 template <int RECON>
@@ -3434,8 +3461,8 @@ int grmhd_pack_set_tiles(grmhd_pack* pk, int n, int t1, int t2, int t3) {
 
 int grmhd_pack_load_prims(grmhd_pack* pk, const double* d_prims) {
   if (!pk || !d_prims) return GRMHD_E_ARG;
-  const dim3 grid = pack_zone_grid(pk);
-  k_pack_load<<<grid, BLOCK, 0, pk->stream>>>(pk->d_views, d_prims);
+  const unsigned chunks = pack_chunks(pk);
+  k_pack_load<<<(unsigned)pk->nb * chunks, BLOCK, 0, pk->stream>>>(pk->d_views, chunks, d_prims);
   return hip_check();
 }
 
@@ -3452,8 +3479,8 @@ int grmhd_pack_step(grmhd_pack* pk, double dt) {
 
 int grmhd_pack_get_prims(grmhd_pack* pk, double* d_out) {
   if (!pk || !d_out) return GRMHD_E_ARG;
-  const dim3 grid = pack_zone_grid(pk);
-  k_pack_read<<<grid, BLOCK, 0, pk->stream>>>(pk->d_views, d_out);
+  const unsigned chunks = pack_chunks(pk);
+  k_pack_read<<<(unsigned)pk->nb * chunks, BLOCK, 0, pk->stream>>>(pk->d_views, chunks, d_out);
   return hip_check();
 }
 
