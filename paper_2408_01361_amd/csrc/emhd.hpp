@@ -369,8 +369,10 @@ k_update_emhd(Dev g, Sched box, const double* __restrict__ Pin, const double* __
               const double* __restrict__ FX1, const double* __restrict__ FX2, const double* __restrict__ FX3,
               const double* __restrict__ E1, const double* __restrict__ E2, const double* __restrict__ E3,
               const double* __restrict__ tabC, const double* __restrict__ conn, double dt,
-              const double* __restrict__ dt_dev, double* __restrict__ ustar, double* __restrict__ xrhs) {
+              const double* __restrict__ dt_dev, double* __restrict__ ustar, double* __restrict__ xrhs,
+              unsigned long long* nopen) {
 #pragma clang fp contract(off)
+  if (blockIdx.x == 0 && threadIdx.x == 0) *nopen = 0;   // for the implicit pass
   int i, j, k;
   if (!sched_index(box, blockIdx.x, gridDim.x, i, j, k)) return;
   if (dt_dev) dt = *dt_dev;
@@ -453,86 +455,70 @@ k_update_emhd(Dev g, Sched box, const double* __restrict__ Pin, const double* __
 // solved for X inside every residual; the Newton runs on the five hydro
 // prims from the stage input (the guess), the field is xrhs's B /
 // sqrt(-g).  On failure the zone keeps the guess's hydro prims and X (the
-// field still updated) and is counted.  Bound by FP64 arithmetic, some 30
-// residuals per zone and more where a lane of the wave does not converge:
-// shared reciprocals and the quotients without range handling took a residual
-// from ~550 to ~300 instructions (64^3 torus: 387 -> 250 us per launch, 1080 ->
-// 700 in a first step).  Three waves per SIMD (168 registers) spill: 6 % slower
-// step.  With RATE the CFL-rate partials of
-// the new prims (ideal signal speeds), over the update's schedule.
-template <int STAGE, bool RATE>
-__global__ void __launch_bounds__(BLOCK)
-k_implicit_emhd(Dev g, Sched box, const double* __restrict__ Pin, const double* __restrict__ Xin,
-                const double* __restrict__ ustar, const double* __restrict__ xrhs,
-                const double* __restrict__ divu, const double* __restrict__ utn, double* __restrict__ Pout,
-                double* __restrict__ Xout, const double* __restrict__ tabC, double dt,
-                const double* __restrict__ dt_dev, unsigned long long* fails,
-                double* __restrict__ rate_partial) {
+// field still updated) and is counted.
+struct ImplicitZone {
+  PointMetric<double> m;
+  double Us[NVAR], Ux[NXV], B[3], dsp, ut_n, h, ih, htau, scale, iscale;
+
+  __device__ __forceinline__ void load(const Dev& g, long c, int i, int j, const double* __restrict__ ustar,
+                                       const double* __restrict__ xrhs, const double* __restrict__ divu,
+                                       const double* __restrict__ utn, const double* __restrict__ tabC, double step) {
 #pragma clang fp contract(off)
-  __shared__ double jac[25 * BLOCK];
-  int i, j, k;
-  const bool in = sched_index(box, blockIdx.x, gridDim.x, i, j, k);
-  if (dt_dev) dt = *dt_dev;
-  double r = 0.0;
-  if (in) {
-    const long c = zid(g, i, j, k), nz = g.nz;
-    double Us[NVAR], Ux[NXV], gs[NVAR], xg[NXV];
-    load8(ustar, nz, c, Us);
-    load8(Pin, nz, c, gs);
+    load8(ustar, g.nz, c, Us);
 #pragma unroll
-    for (int n = 0; n < NXV; n++) {
-      Ux[n] = xrhs[2 * c + n];
-      xg[n] = Xin[2 * c + n];
-    }
-    const double dsp = divu[c], ut_n = utn[c];
-    const double h = STAGE == 1 ? 0.5 * dt : dt;
-    PointMetric<double> m;
+    for (int n = 0; n < NXV; n++) Ux[n] = xrhs[2 * c + n];
+    dsp = divu[c];
+    ut_n = utn[c];
+    h = step;
     load_metric<double>(tabC, g.plane, pid(g, i, j), m);
-    const double gd = m.gdet;
-    double out[NVAR], xo[NXV];
-    out[B1] = Us[B1] / gd;
-    out[B2] = Us[B2] / gd;
-    out[B3] = Us[B3] / gd;
-    const double B[3] = {out[B1], out[B2], out[B3]};
-    const double ih = plain_rcp(h), htau = h * gd / g.tau;
-    // X of a hydro state with fluid state fz
-    auto xsolve = [&](const Fluid<double>& fz, double Xz[NXV]) {
-      const double ut = fz.ucon[0];
-      const double du = dsp + quotient(ut - ut_n, h, ih);
-      const double coef = gd * ut + htau - 0.5 * h * gd * du;
-      const double ic = plain_rcp(coef);
 #pragma unroll
-      for (int n = 0; n < NXV; n++) Xz[n] = quotient(Ux[n], coef, ic);
-    };
-    double scale = 0.0;
+    for (int k = 0; k < 3; k++) B[k] = Us[B1 + k] / m.gdet;
+    ih = plain_rcp(h);
+    htau = h * m.gdet / g.tau;
+    scale = 0.0;
 #pragma unroll
     for (int kk = 0; kk < 5; kk++)
       if (fabs(Us[kk]) > scale) scale = fabs(Us[kk]);
-    bool ok = scale > 0.0 && isfinite(scale);
-    double xs[5];
-    if (ok) {
-      const double iscale = plain_rcp(scale);
-      auto res = [&](const double xx[5], double R[5]) {
-        const double Pz[NVAR] = {xx[0], xx[1], xx[2], xx[3], xx[4], B[0], B[1], B[2]};
-        Fluid<double> fz;
-        fplain::fluid_state(Pz, m, fz);
-        double Xz[NXV];
-        xsolve(fz, Xz);
-        double q, dP;
-        emhd_unscale(g, Pz, Xz, q, dP);
-        double T[4];
-        tmunu_row_emhd(Pz, fz, g.gam, q, dP, 0, T);
-        double U[5];
-        U[RHO] = (gd * Pz[RHO]) * fz.ucon[0];
-        U[UU] = gd * (T[0] + Pz[RHO] * fz.ucon[0]);
-        U[U1] = gd * T[1];
-        U[U2] = gd * T[2];
-        U[U3] = gd * T[3];
+    iscale = plain_rcp(scale);
+  }
+  __device__ __forceinline__ bool solvable() const { return scale > 0.0 && isfinite(scale); }
+  // X of a hydro state with fluid state fz
+  __device__ __forceinline__ void xsolve(const Fluid<double>& fz, double Xz[NXV]) const {
+#pragma clang fp contract(off)
+    const double ut = fz.ucon[0];
+    const double du = dsp + quotient(ut - ut_n, h, ih);
+    const double coef = m.gdet * ut + htau - 0.5 * h * m.gdet * du;
+    const double ic = plain_rcp(coef);
 #pragma unroll
-        for (int kk = 0; kk < 5; kk++) R[kk] = quotient(U[kk] - Us[kk], scale, iscale);
-      };
-      ok = newton_hydro(g, gs, res, xs, jac + threadIdx.x);
-    }
+    for (int n = 0; n < NXV; n++) Xz[n] = quotient(Ux[n], coef, ic);
+  }
+  __device__ __forceinline__ void residual(const Dev& g, const double xx[5], double R[5]) const {
+#pragma clang fp contract(off)
+    const double gd = m.gdet;
+    const double Pz[NVAR] = {xx[0], xx[1], xx[2], xx[3], xx[4], B[0], B[1], B[2]};
+    Fluid<double> fz;
+    fplain::fluid_state(Pz, m, fz);
+    double Xz[NXV];
+    xsolve(fz, Xz);
+    double q, dP;
+    emhd_unscale(g, Pz, Xz, q, dP);
+    double T[4];
+    tmunu_row_emhd(Pz, fz, g.gam, q, dP, 0, T);
+    double U[5];
+    U[RHO] = (gd * Pz[RHO]) * fz.ucon[0];
+    U[UU] = gd * (T[0] + Pz[RHO] * fz.ucon[0]);
+    U[U1] = gd * T[1];
+    U[U2] = gd * T[2];
+    U[U3] = gd * T[3];
+#pragma unroll
+    for (int kk = 0; kk < 5; kk++) R[kk] = quotient(U[kk] - Us[kk], scale, iscale);
+  }
+  // Stores the solution from the root xs, or the guess; the zone's prims in
+  // out.
+  __device__ __forceinline__ void store(bool ok, const double xs[5], const double* __restrict__ Pin,
+                                        const double* __restrict__ Xin, long nz, long c, double* __restrict__ Pout,
+                                        double* __restrict__ Xout, unsigned long long* fails, double out[NVAR]) const {
+    double xo[NXV];
     if (ok) {
       const double Pn[NVAR] = {xs[0], xs[1], xs[2], xs[3], xs[4], B[0], B[1], B[2]};
       Fluid<double> fz;
@@ -546,20 +532,110 @@ k_implicit_emhd(Dev g, Sched box, const double* __restrict__ Pin, const double* 
 #pragma unroll
       for (int v = 0; v < 5; v++) out[v] = xs[v];
     } else {
+      load8(Pin, nz, c, out);
 #pragma unroll
-      for (int v = 0; v < 5; v++) out[v] = gs[v];
-#pragma unroll
-      for (int n = 0; n < NXV; n++) xo[n] = xg[n];
+      for (int n = 0; n < NXV; n++) xo[n] = Xin[2 * c + n];
       atomicAdd(&fails[C_FAILS], 1ull);
     }
+#pragma unroll
+    for (int k = 0; k < 3; k++) out[B1 + k] = B[k];
     store8(Pout, nz, c, out);
 #pragma unroll
     for (int n = 0; n < NXV; n++) Xout[2 * c + n] = xo[n];
-    if (RATE) r = zone_rate_ordered(g, out, m);
+  }
+};
+
+// Zones whose Newton is still open after this many iterations go to the
+// second kernel (64^3 torus, two steps: 2623 us with 3, 1892 with 4, 1632 with 5,
+// 1721 with 6; 1951 in one kernel).
+constexpr int EMHD_HEAD = 5;
+struct OpenZone {
+  int c, block;   // padded index; workgroup of the first kernel
+};
+
+// First kernel of the pass, a lane per zone.  Bound by FP64 arithmetic, some 30
+// residuals per zone: shared reciprocals and the quotients without range
+// handling took a residual from ~550 to ~300 instructions (64^3 torus: 387 -> 250
+// us per launch).  Three waves per SIMD (168 registers) spill: 6 % slower step.
+// A zone that has not converged after EMHD_HEAD iterations leaves its iterate in
+// Pout and goes to the list (open, fails[C_OPEN] entries).  With RATE the
+// CFL-rate partials of the new prims (ideal signal speeds), over the update's
+// schedule.
+template <int STAGE, bool RATE>
+__global__ void __launch_bounds__(BLOCK)
+k_implicit_emhd(Dev g, Sched box, const double* __restrict__ Pin, const double* __restrict__ Xin,
+                const double* __restrict__ ustar, const double* __restrict__ xrhs,
+                const double* __restrict__ divu, const double* __restrict__ utn, double* __restrict__ Pout,
+                double* __restrict__ Xout, const double* __restrict__ tabC, double dt,
+                const double* __restrict__ dt_dev, unsigned long long* fails,
+                double* __restrict__ rate_partial, OpenZone* __restrict__ open) {
+#pragma clang fp contract(off)
+  __shared__ double jac[25 * BLOCK];
+  int i, j, k;
+  const bool in = sched_index(box, blockIdx.x, gridDim.x, i, j, k);
+  if (dt_dev) dt = *dt_dev;
+  double r = 0.0;
+  if (in) {
+    const long c = zid(g, i, j, k), nz = g.nz;
+    ImplicitZone z;
+    z.load(g, c, i, j, ustar, xrhs, divu, utn, tabC, STAGE == 1 ? 0.5 * dt : dt);
+    double gs[NVAR], xs[5];
+    load8(Pin, nz, c, gs);
+    int how = NEWTON_FAILED;
+    if (z.solvable())
+      how = newton_hydro(g, gs, [&](const double xx[5], double R[5]) { z.residual(g, xx, R); }, xs, jac + threadIdx.x,
+                         g.maxit < EMHD_HEAD ? g.maxit : EMHD_HEAD);
+    double out[NVAR];
+    if (how == NEWTON_OPEN) {
+#pragma unroll
+      for (int v = 0; v < 5; v++) Pout[vx(v, nz, c)] = xs[v];
+      open[atomicAdd(&fails[C_OPEN], 1ull)] = OpenZone{(int)c, (int)blockIdx.x};
+    } else {
+      z.store(how == NEWTON_ROOT, xs, Pin, Xin, nz, c, Pout, Xout, fails, out);
+      if (RATE) r = zone_rate_ordered(g, out, z.m);
+    }
   }
   if (RATE) {
     double sm = 0.0;
     block_reduce(r, sm);
     if (threadIdx.x == 0) rate_partial[blockIdx.x] = r;
+  }
+}
+
+// Second kernel: the listed zones, eight lanes each (newton_hydro_group).  A
+// zone that does not converge runs to the iteration limit; with a lane per zone
+// its chain of some 15 residuals an iteration set the time of the whole pass.
+constexpr int EMHD_TAIL_BLOCKS = 512;
+template <int STAGE, bool RATE>
+__global__ void __launch_bounds__(BLOCK)
+k_implicit_emhd_open(Dev g, const double* __restrict__ Pin, const double* __restrict__ Xin,
+                     const double* __restrict__ ustar, const double* __restrict__ xrhs,
+                     const double* __restrict__ divu, const double* __restrict__ utn, double* __restrict__ Pout,
+                     double* __restrict__ Xout, const double* __restrict__ tabC, double dt,
+                     const double* __restrict__ dt_dev, unsigned long long* fails,
+                     double* __restrict__ rate_partial, const OpenZone* __restrict__ open) {
+#pragma clang fp contract(off)
+  __shared__ double jac[25 * BLOCK];
+  const long n = (long)fails[C_OPEN], nz = g.nz;
+  if (dt_dev) dt = *dt_dev;
+  for (long e = (blockIdx.x * (long)BLOCK + threadIdx.x) >> 3; e < n; e += (long)EMHD_TAIL_BLOCKS * (BLOCK / 8)) {
+    const OpenZone o = open[e];
+    const long c = o.c;
+    const int r = o.c / g.s1, i = o.c % g.s1 - NG, j = r % g.s2 - NG;
+    ImplicitZone z;
+    z.load(g, c, i, j, ustar, xrhs, divu, utn, tabC, STAGE == 1 ? 0.5 * dt : dt);
+    double xs[5];
+#pragma unroll
+    for (int v = 0; v < 5; v++) xs[v] = Pout[vx(v, nz, c)];
+    const int how = newton_hydro_group(g, [&](const double xx[5], double R[5]) { z.residual(g, xx, R); }, xs,
+                                       jac + threadIdx.x, EMHD_HEAD);
+    if ((threadIdx.x & 7u) == 0) {
+      double out[NVAR];
+      z.store(how == NEWTON_ROOT, xs, Pin, Xin, nz, c, Pout, Xout, fails, out);
+      // (rates are not negative: their bits order as they do)
+      if (RATE)
+        atomicMax((unsigned long long*)rate_partial + o.block,
+                  __builtin_bit_cast(unsigned long long, zone_rate_ordered(g, out, z.m)));
+    }
   }
 }

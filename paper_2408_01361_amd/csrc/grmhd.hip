@@ -1348,7 +1348,7 @@ __device__ __forceinline__ void load_conn(const double* __restrict__ conn, long 
 // (k_floors), with the same modes.
 enum { U_PLAIN = 0, U_PROVISIONAL = 2, U_FINAL = 3, U_STORE = 4 };
 // Counter slots of the context's counter array.
-enum { C_FAILS = 0, C_C2P = 1, C_FLOORS = 2, C_FOFC = 3, C_FLUID = 4, C_MARKS = 5 };
+enum { C_FAILS = 0, C_C2P = 1, C_FLOORS = 2, C_FOFC = 3, C_FLUID = 4, C_MARKS = 5, C_OPEN = 6 };
 
 // Rate of the zone field from its twelve edge EMFs (Flux-CT), e3[di][dj],
 // e2[di][dk], e1[dj][dk] at the edges offset by 0 or 1:
@@ -2512,15 +2512,22 @@ int emhd_stage(grmhd_ctx* c, const double* Pin, double* Xin, double* Pout, doubl
                    (const double*)F1, (const double*)F2, (const double*)F3, (const double*)c->FX[0],
                    (const double*)c->FX[1], (const double*)c->FX[2], (const double*)c->E[0],
                    (const double*)c->E[1], (const double*)c->E[2], (const double*)c->tabC,
-                   (const double*)c->conn, dt, dt_dev, c->ustar, c->xrhs)))
+                   (const double*)c->conn, dt, dt_dev, c->ustar, c->xrhs, c->fails + C_OPEN)))
     return rc;
-  auto implicit = [&](auto kernel, double* partial) {
-    return launch(c, cls, kernel, nb, g, bz, Pin, (const double*)Xin, (const double*)c->ustar,
+  // the open zones' list: the fluxes are not needed any more
+  OpenZone* open = (OpenZone*)c->F[0];
+  auto implicit = [&](auto kernel, auto rest, double* partial) {
+    if ((rc = launch(c, cls, kernel, nb, g, bz, Pin, (const double*)Xin, (const double*)c->ustar,
+                     (const double*)c->xrhs, (const double*)c->divu, (const double*)c->utn, Pout, Xout,
+                     (const double*)c->tabC, dt, dt_dev, c->fails, partial, open)))
+      return rc;
+    return launch(c, cls, rest, (unsigned)EMHD_TAIL_BLOCKS, g, Pin, (const double*)Xin, (const double*)c->ustar,
                   (const double*)c->xrhs, (const double*)c->divu, (const double*)c->utn, Pout, Xout,
-                  (const double*)c->tabC, dt, dt_dev, c->fails, partial);
+                  (const double*)c->tabC, dt, dt_dev, c->fails, partial, (const OpenZone*)open);
   };
-  if (STAGE == 2 && rate && nb <= (unsigned)MAX_PARTIALS) return implicit(k_implicit_emhd<STAGE, true>, c->pdt);
-  return implicit(k_implicit_emhd<STAGE, false>, (double*)nullptr);
+  if (STAGE == 2 && rate && nb <= (unsigned)MAX_PARTIALS)
+    return implicit(k_implicit_emhd<STAGE, true>, k_implicit_emhd_open<STAGE, true>, c->pdt);
+  return implicit(k_implicit_emhd<STAGE, false>, k_implicit_emhd_open<STAGE, false>, (double*)nullptr);
 }
 
 // One step of the configured integrator with dt from the host, or, when

@@ -520,17 +520,19 @@ __device__ __forceinline__ int invert_implicit(const Dev& g, const PointMetric<d
 // guess x0 (rho, u > 0), with the steps, Jacobian, pivoted QR, line search
 // and stopping rule of invert_implicit: res(x, R) fills the scaled residual
 // R[5]; jac is this thread's 25 LDS words for the Jacobian (LdsMat base).
-// Returns true with the root in x.  (invert_implicit keeps its own copy of
+// Returns NEWTON_ROOT with the root in x, or, after `limit` iterations of
+// fewer than g.maxit, NEWTON_OPEN with the iterate.  (invert_implicit keeps its own copy of
 // the loop: compiled through this template, its kernel produced different
 // and wrong states on torus steps, while this template gives parity here.)
+enum { NEWTON_FAILED = 0, NEWTON_ROOT = 1, NEWTON_OPEN = 2 };
 template <typename Res>
-__device__ __forceinline__ bool newton_hydro(const Dev& g, const double x0[5], Res res, double x[5],
-                                             double* jac) {
+__device__ __forceinline__ int newton_hydro(const Dev& g, const double x0[5], Res res, double x[5],
+                                            double* jac, int limit) {
 #pragma clang fp contract(off)
   const double fl[5] = {0.0, 0.0, 1e-3, 1e-3, 1e-3};
 #pragma unroll
   for (int k = 0; k < 5; k++) x[k] = x0[k];
-  if (!(x[0] > 0.0) || !(x[1] > 0.0)) return false;
+  if (!(x[0] > 0.0) || !(x[1] > 0.0)) return NEWTON_FAILED;
   double R[5];
   res(x, R);
   double r2 = 0.0;
@@ -539,7 +541,7 @@ __device__ __forceinline__ bool newton_hydro(const Dev& g, const double x0[5], R
   bool conv = false;
   const double tol = g.tol > 1e-12 ? g.tol : 1e-12;
   const LdsMat J{jac};
-  for (int it = 0; it < g.maxit && !conv; it++) {
+  for (int it = 0; it < limit && !conv; it++) {
     // secant Jacobian, one column per pass (components picked by compare,
     // so nothing in registers is indexed by the loop counter)
 #pragma unroll 1
@@ -566,7 +568,7 @@ __device__ __forceinline__ bool newton_hydro(const Dev& g, const double x0[5], R
     double rhs[5], dx[5];
 #pragma unroll
     for (int mm = 0; mm < 5; mm++) rhs[mm] = -R[mm];
-    if (!qr_pivot_solve(J, rhs, dx)) return false;
+    if (!qr_pivot_solve(J, rhs, dx)) return NEWTON_FAILED;
     double lam = 1.0, xn[5], Rn[5], rn2 = 0.0;
     bool ok = false;
     for (int ls = 0; ls <= 8; ls++) {
@@ -584,7 +586,7 @@ __device__ __forceinline__ bool newton_hydro(const Dev& g, const double x0[5], R
       }
       if (ls < 8) lam = 0.5 * lam;
     }
-    if (!ok) return false;
+    if (!ok) return NEWTON_FAILED;
     conv = true;
 #pragma unroll
     for (int mm = 0; mm < 5; mm++) {
@@ -595,11 +597,112 @@ __device__ __forceinline__ bool newton_hydro(const Dev& g, const double x0[5], R
     }
     r2 = rn2;
   }
-  if (!conv) return false;
+  if (!conv) return limit < g.maxit ? NEWTON_OPEN : NEWTON_FAILED;
 #pragma unroll
   for (int k = 0; k < 5; k++)
-    if (!isfinite(x[k])) return false;
-  return true;
+    if (!isfinite(x[k])) return NEWTON_FAILED;
+  return NEWTON_ROOT;
+}
+
+// The same iteration continued from the iterate x (not converged after `from`
+// iterations) by the eight lanes of a group together: lanes 0..4 take one
+// column of the Jacobian each, and lane l the line search's step 2^-l; the
+// first that reduces the residual is taken, as the steps one after the other
+// would.  Per iteration the chain is three residuals instead of six to
+// fourteen.  Every operation on a value is the one newton_hydro does, so the
+// root is the same bit for bit.
+template <typename Res>
+__device__ __forceinline__ int newton_hydro_group(const Dev& g, Res res, double x[5], double* jac, int from) {
+#pragma clang fp contract(off)
+  const double fl[5] = {0.0, 0.0, 1e-3, 1e-3, 1e-3};
+  const int lane = (int)(threadIdx.x & 63u), sub = lane & 7;
+  double R[5];
+  res(x, R);
+  double r2 = 0.0;
+#pragma unroll
+  for (int k = 0; k < 5; k++) r2 += R[k] * R[k];
+  bool conv = false;
+  const double tol = g.tol > 1e-12 ? g.tol : 1e-12;
+  const LdsMat J{jac};
+  for (int it = from; it < g.maxit && !conv; it++) {
+    double col[5];
+    {
+      const int k = sub < 5 ? sub : 0;
+      double xk = x[0], flk = fl[0];
+#pragma unroll
+      for (int mm = 1; mm < 5; mm++)
+        if (mm == k) {
+          xk = x[mm];
+          flk = fl[mm];
+        }
+      const double ax = fabs(xk);
+      const double h = 1e-7 * (ax > flk ? ax : flk);
+      const double xkh = xk + h;
+      double xp[5];
+#pragma unroll
+      for (int mm = 0; mm < 5; mm++) xp[mm] = mm == k ? xkh : x[mm];
+      double Rp[5];
+      res(xp, Rp);
+      const double hh = xkh - xk, ihh = plain_rcp(hh);
+#pragma unroll
+      for (int mm = 0; mm < 5; mm++) col[mm] = quotient(Rp[mm] - R[mm], hh, ihh);
+    }
+#pragma unroll
+    for (int k = 0; k < 5; k++)
+#pragma unroll
+      for (int mm = 0; mm < 5; mm++) J(mm, k) = __shfl(col[mm], k, 8);
+    double rhs[5], dx[5];
+#pragma unroll
+    for (int mm = 0; mm < 5; mm++) rhs[mm] = -R[mm];
+    if (!qr_pivot_solve(J, rhs, dx)) return NEWTON_FAILED;
+    double xn[5], Rn[5], rn2 = 0.0;
+    bool ok = false;
+    auto attempt = [&](double lam) {
+#pragma unroll
+      for (int mm = 0; mm < 5; mm++) {
+        xn[mm] = x[mm] + lam * dx[mm];
+        Rn[mm] = 0.0;
+      }
+      rn2 = 0.0;
+      ok = xn[0] > 0.0 && xn[1] > 0.0;
+      if (ok) {
+        res(xn, Rn);
+#pragma unroll
+        for (int mm = 0; mm < 5; mm++) rn2 += Rn[mm] * Rn[mm];
+        ok = isfinite(rn2);
+      }
+    };
+    double lam = 1.0;
+    for (int l = 0; l < sub; l++) lam = 0.5 * lam;
+    attempt(lam);
+    const unsigned good = (unsigned)(__ballot(ok && rn2 < r2) >> (lane & ~7)) & 255u;
+    if (good) {
+      const int from_lane = __ffs(good) - 1;
+#pragma unroll
+      for (int mm = 0; mm < 5; mm++) {
+        xn[mm] = __shfl(xn[mm], from_lane, 8);
+        Rn[mm] = __shfl(Rn[mm], from_lane, 8);
+      }
+      rn2 = __shfl(rn2, from_lane, 8);
+    } else {
+      attempt(0.00390625);   // the last step, 2^-8, taken if it is finite
+      if (!ok) return NEWTON_FAILED;
+    }
+    conv = true;
+#pragma unroll
+    for (int mm = 0; mm < 5; mm++) {
+      const double ax = fabs(xn[mm]);
+      if (fabs(xn[mm] - x[mm]) > tol * (ax > fl[mm] ? ax : fl[mm])) conv = false;
+      x[mm] = xn[mm];
+      R[mm] = Rn[mm];
+    }
+    r2 = rn2;
+  }
+  if (!conv) return NEWTON_FAILED;
+#pragma unroll
+  for (int k = 0; k < 5; k++)
+    if (!isfinite(x[k])) return NEWTON_FAILED;
+  return NEWTON_ROOT;
 }
 
 __device__ __forceinline__ int invert(const Dev& g, const PointMetric<double>& m, const double U[NVAR],
