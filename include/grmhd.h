@@ -365,7 +365,7 @@ int grmhd_pack_get_status(grmhd_pack* pack, long long* n_inv_fail);
  * blocks, E_NOMEM for a short map. */
 size_t grmhd_pack_exchange_bytes(const grmhd_grid* global);
 int grmhd_pack_set_exchange(grmhd_pack* pack, void* d_map, size_t map_bytes);
-/* Workgroups of one RK2 stage's three launches, and length (doubles) of
+/* Workgroups of one RK2 stage's launches, and length (doubles) of
  * the packed prims. */
 int grmhd_pack_info(grmhd_pack* pack, int* grid_blocks, long long* prim_doubles);
 int grmhd_pack_destroy(grmhd_pack* pack);

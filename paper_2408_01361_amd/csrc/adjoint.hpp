@@ -216,7 +216,11 @@ __device__ __forceinline__ void store_block_sum(double v, double* __restrict__ p
 }
 
 // The three directions' faces in one launch (one tail instead of three), nb1
-// and nb2 workgroups of the first two; each XCD takes a contiguous range.
+// and nb2 workgroups of the first two; each XCD takes a contiguous range.  Two
+// waves per SIMD (218 VGPRs with MC, 250 with WENO5, no scratch).  64^3 MC: 60
+// us a stage, where three launches on dense sums, with divisions and 32 stored
+// values a face, took 174; 111 MB written and some 90 MB read, about half the
+// memory rate, the rest the arithmetic and latency of the two sweeps.
 #ifndef ADJ_FACE_WAVES
 #define ADJ_FACE_WAVES 2
 #endif
@@ -295,7 +299,8 @@ __device__ __forceinline__ void gather_weno(const AdjAxis& f, int a, long nz, lo
   }
 }
 
-// Gather of the stencil adjoints onto every padded zone.  zero_ghosts, where
+// Gather of the stencil adjoints onto every padded zone.  Bound by memory (64^3
+// MC: 45 us for 111 MB of state adjoints and the prims).  zero_ghosts, where
 // given: an array in the caller's layout whose ghost zones are set to zero.
 template <int RECON>
 __global__ void __launch_bounds__(BLOCK) k_adj_gather(Dev g, const double* __restrict__ P,
@@ -491,7 +496,9 @@ __device__ __forceinline__ int adj_preimage(int x, int n, int bit) {
 // transposed combination U1 = U^n + dt L(P^n), V = (U^n + U1)/2: lambda_U1 =
 // lambda_U + lambda_V/2, lambda_Un = lambda_V/2 + lambda_U1 (into LV),
 // lambda_L = dt lambda_U1.  It stores its adjoint only where that inversion
-// (failed1) failed: stage 1 reads it there.
+// (failed1) failed: stage 1 reads it there.  64^3: 26 us, and 35 with the
+// inversion (50 and 50 us before, as two kernels with the connection's 40
+// coefficients, nine dual-number passes and preimage lists in scratch).
 template <bool STAGE1>
 __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(2, 8)))
 k_adj_zone(Dev g, Box box, const double* __restrict__ Pin, const unsigned char* __restrict__ flags,

@@ -9,9 +9,8 @@
 // All of it on the library's structured metric (the entries that are
 // identically zero are not in the sums), in terms of contractions with the
 // output's adjoint -- a row T^mu_nu with adjoint X^nu needs X.u and X.b only --
-// and with reciprocals that zone_state forms once.  The four divisions and
-// the square root of the speeds' sweep are one refined reciprocal of the
-// quadratic's slope: about 300 FP64 instructions per face state.
+// and with reciprocals that zone_state forms once; the speeds' sweep through
+// their quadratic divides by its slope only.
 //
 // Included by adjoint.hpp (and by host tests) after physics.hpp, where the
 // library's names are visible.
