@@ -198,14 +198,17 @@ __device__ __forceinline__ void state_vjp(const double q[NVAR], const PointMetri
   FluidAdj a;
   adj_zero(a);
   const SpeedQuadratic r = speed_quadratic<D>(q, m, gam, z);
-  speed_rev<D>(q, m, gam, z, r, 1.0, cpb, a);
-  speed_rev<D>(q, m, gam, z, r, -1.0, cmb, a);
+  const double sg = r.A < 0.0 ? -1.0 : 1.0;
+  speed_rev<D>(q, m, gam, z, r, sg, cpb, a);
+  speed_rev<D>(q, m, gam, z, r, -sg, cmb, a);
   rows_rev<D>(q, m, z, Fb, Ub, a);
   fluid_rev(q, m, gam, z, a, qb, gamb);
 }
 
 // The same with the adjoint vb of the speed of larger magnitude alone (the
-// larger root on a tie): what a Lax-Friedrichs flux depends on.
+// larger root on a tie): what a Lax-Friedrichs flux depends on.  That root is
+// (b + sg s)/A with sg the sign of b, its own sign that of sg A: A is negative
+// in states whose density or internal energy the reconstruction undershot.
 template <int D>
 __device__ __forceinline__ void face_state_vjp(const double q[NVAR], const PointMetric<double>& m, double gam,
                                                const double Fb[NVAR], const double Ub[NVAR], double vb,
@@ -215,8 +218,9 @@ __device__ __forceinline__ void face_state_vjp(const double q[NVAR], const Point
   FluidAdj a;
   adj_zero(a);
   const SpeedQuadratic r = speed_quadratic<D>(q, m, gam, z);
-  const double sg = r.b < 0.0 ? -1.0 : 1.0;
-  speed_rev<D>(q, m, gam, z, r, sg, sg * vb, a);
+  const double sa = r.A < 0.0 ? -1.0 : 1.0;
+  const double sg = r.b < 0.0 || (r.b == 0.0 && r.A < 0.0) ? -1.0 : 1.0;
+  speed_rev<D>(q, m, gam, z, r, sg, sa * sg * vb, a);
   rows_rev<D>(q, m, z, Fb, Ub, a);
   fluid_rev(q, m, gam, z, a, qb, gamb);
 }
