@@ -2584,6 +2584,14 @@ int do_step(grmhd_ctx* c, double dt, const double* dt_dev = nullptr) {
   return GRMHD_OK;
 }
 
+// Whether a device-dt step's first update may do the final pass of the dt
+// reduction: no launch before it reads dt (the faces of face-centred CT
+// advance before the update), and it is its stage's only update.
+bool update_reduces(const grmhd_ctx* c) {
+  const grmhd_params& p = c->params;
+  return p.ct == GRMHD_CT_FLUX && !p.fofc && !p.egrmhd && p.inverter != GRMHD_INV_IMPLICIT;
+}
+
 // Enqueue the CFL reduction of the current prims (interior zones only, so no
 // ghost fill): result[0] = max signal rate, result[2] = cfl / max,
 // result[3] = 0 if that dt is usable.  When the last step's stage-2 update
@@ -2908,8 +2916,7 @@ int grmhd_estimate_dt(grmhd_ctx* c, double* dt_out) {
 int grmhd_step_cfl(grmhd_ctx* c) {
   if (!c) return GRMHD_E_ARG;
   int rc;
-  // (the plain step's first update is the only one of its stage)
-  if ((rc = launch_dt(c, !c->params.fofc && !c->params.egrmhd && c->params.inverter != GRMHD_INV_IMPLICIT))) return rc;
+  if ((rc = launch_dt(c, update_reduces(c)))) return rc;
   rc = c->params.precision == GRMHD_PREC_FP64 ? do_step<double, double>(c, 0.0, c->result + 2)
                                               : do_step<float, float>(c, 0.0, c->result + 2);
   c->cfl_n = 0;

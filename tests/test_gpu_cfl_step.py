@@ -1,0 +1,40 @@
+"""A step at the CFL dt of the device (step_cfl) against the same step at the
+dt the host reads (dt, then step): one reduction, so the same dt and the same
+state bit for bit, whatever launches read the dt and wherever its final pass
+runs."""
+
+import pytest
+
+from workloads import fm_torus
+
+pytestmark = pytest.mark.gpu
+
+GAM = 13.0 / 9.0
+
+
+def _same(shape, nsteps, **kw):
+    import torch
+    from paper_2408_01361_amd import grmhd as gr
+    grid, P, info = fm_torus(*shape)
+    a, b = gr.Grmhd(grid, GAM, **kw), gr.Grmhd(grid, GAM, **kw)
+    for s in (a, b):
+        s.load(torch.from_numpy(P).cuda())
+        if kw.get("ct"):
+            s.load_faces(torch.from_numpy(info["faces"]).cuda())
+    for n in range(nsteps):
+        a.step_cfl()      # (the first one right after the load: no dt reduced before)
+        dt = b.dt()
+        b.step(dt)
+        assert a.last_dt() == dt
+        assert torch.equal(a.prims(), b.prims()), n
+        if kw.get("ct"):
+            assert torch.equal(a.faces(), b.faces()), n
+
+
+@pytest.mark.parametrize("opts", [dict(), dict(precision=1), dict(floors=True), dict(floors=True, fofc=True), dict(inverter=2)],
+                         ids=["plain", "mixed", "floors", "fofc", "implicit"])
+@pytest.mark.parametrize("ct", [1, 2])
+@pytest.mark.parametrize("shape", [(24, 22, 7), (64, 64, 64)], ids=["small", "largest"])
+def test_face_ct_advances_its_faces_with_the_steps_dt(shape, ct, opts):
+    """64^3 has 1024 workgroups of partials, the most that an update reduces."""
+    _same(shape, 3, recon=1, ct=ct, **opts)
