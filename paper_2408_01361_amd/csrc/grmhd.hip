@@ -2586,10 +2586,13 @@ int do_step(grmhd_ctx* c, double dt, const double* dt_dev = nullptr) {
 
 // Whether a device-dt step's first update may do the final pass of the dt
 // reduction: no launch before it reads dt (the faces of face-centred CT
-// advance before the update), and it is its stage's only update.
+// advance before the update), it is its stage's only update, and it does not
+// write the partials that its workgroups read (RK1's update ends the step, so
+// it leaves the next step's).
 bool update_reduces(const grmhd_ctx* c) {
   const grmhd_params& p = c->params;
-  return p.ct == GRMHD_CT_FLUX && !p.fofc && !p.egrmhd && p.inverter != GRMHD_INV_IMPLICIT;
+  return p.ct == GRMHD_CT_FLUX && !p.fofc && !p.egrmhd && p.inverter != GRMHD_INV_IMPLICIT &&
+         p.integrator != GRMHD_INTEG_RK1;
 }
 
 // Enqueue the CFL reduction of the current prims (interior zones only, so no

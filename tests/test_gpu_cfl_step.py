@@ -38,3 +38,12 @@ def _same(shape, nsteps, **kw):
 def test_face_ct_advances_its_faces_with_the_steps_dt(shape, ct, opts):
     """64^3 has 1024 workgroups of partials, the most that an update reduces."""
     _same(shape, 3, recon=1, ct=ct, **opts)
+
+
+@pytest.mark.parametrize("opts", [dict(recon=0), dict(recon=1), dict(recon=1, precision=1)], ids=["mc", "weno5", "mixed"])
+@pytest.mark.parametrize("integrator", [0, 1, 2, 3])
+@pytest.mark.parametrize("shape", [(60, 61, 58), (64, 64, 64)], ids=["resident_and_late", "largest"])
+def test_every_integrator_steps_with_one_dt(shape, integrator, opts):
+    """960 and 1024 workgroups of an update, more than are resident at a
+    time: the last ones start when the first have left their results."""
+    _same(shape, 4, integrator=integrator, **opts)
