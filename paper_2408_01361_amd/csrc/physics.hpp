@@ -642,6 +642,13 @@ __device__ __forceinline__ double face_sqrt(double x, double& h) {
   h = fma(k, r, k);
   return fma(fma(-g1, g1, x), h, g1);
 }
+// sqrt(x) of a discriminant, zero if it is not positive: cold gas at rest has
+// no signal speed at all, and a CFL step of it is refused.
+__device__ __forceinline__ double speed_root(double x) {
+  double h;
+  const double s = face_sqrt(x, h);
+  return x > 0.0 ? s : 0.0;
+}
 // 2^-e with 2^e <= |x| < 2^(e+1): scales a homogeneous expression without
 // rounding (x normal, below 2^1023).
 __device__ __forceinline__ double unit_scale(double x) {
@@ -713,11 +720,8 @@ __device__ __forceinline__ double fast_speed(double rho, double uu, double pg, d
   const double A = fma(mut, ut, -n * ctt);
   const double b = fma(mut, ud, -n * ctd);
   const double C = fma(mud, ud, -n * cdd);
-  // a discriminant that is not positive counts as zero (1e-280: its root
-  // vanishes against every speed)
-  const double disc = fma(b, b, -(A * C));
-  double h;
-  const double s = face_sqrt(disc > 1e-280 ? disc : 1e-280, h);
+  // a discriminant that is not positive counts as zero
+  const double s = speed_root(fma(b, b, -(A * C)));
   return (fabs(b) + s) * fabs(face_rcp(A));
 }
 __device__ __forceinline__ float fast_speed(float rho, float uu, float pg, float bsq, float gam, float ut, float ud,
@@ -897,9 +901,7 @@ __device__ __forceinline__ void zone_speeds(double rho, double uu, const ZoneSta
   for (int d = 0; d < 3; d++) {
     const double b = d == 0 ? fma(mut, ud[d], -n * m.gcon[sidx(0, 1)]) : mut * ud[d];
     const double C = fma(mm * ud[d], ud[d], -n * m.gcon[sidx(d + 1, d + 1)]);
-    const double disc = fma(b, b, -(A * C));
-    double h;
-    const double s = face_sqrt(disc > 1e-280 ? disc : 1e-280, h);
+    const double s = speed_root(fma(b, b, -(A * C)));
     c[d] = (fabs(b) + s) * iA;
   }
 }

@@ -47,3 +47,32 @@ def test_every_integrator_steps_with_one_dt(shape, integrator, opts):
     """960 and 1024 workgroups of an update, more than are resident at a
     time: the last ones start when the first have left their results."""
     _same(shape, 4, integrator=integrator, **opts)
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+def test_no_cfl_step_without_a_signal_speed(precision):
+    """Cold gas at rest in flat space has no signal speed: there is no step
+    size, and a device-dt step leaves the state as it is.  With internal
+    energy in a single zone, that zone's rate is the grid's."""
+    import torch
+    from paper_2408_01361_amd import grmhd as gr
+    from workloads import GridSpec
+    grid = GridSpec(9, 8, 7)
+    P = torch.zeros((8, 13, 14, 15), dtype=torch.float64, device="cuda")
+    P[0] = 1.0
+    s = gr.Grmhd(grid, GAM, precision=precision)
+    s.load(P)
+    with pytest.raises(gr.GrmhdError):
+        s.dt()
+    with pytest.raises(gr.GrmhdError):
+        gr.cfl_dt_noalloc(grid, GAM, P)
+    s.step_cfl()
+    with pytest.raises(gr.GrmhdError):
+        s.last_dt()
+    assert torch.equal(s.prims(), P)
+    P[1, 5, 6, 7] = 0.1
+    s.load(P)
+    u = 0.1
+    cs = (GAM * (GAM - 1.0) * u / (1.0 + GAM * u)) ** 0.5
+    assert s.dt() == pytest.approx(0.9 / (cs * (9 + 8 + 7)), rel=1e-14)
+    assert gr.cfl_dt_noalloc(grid, GAM, P) == s.dt()
