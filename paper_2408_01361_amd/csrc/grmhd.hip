@@ -3327,12 +3327,6 @@ int pack_upload(grmhd_pack* pk) {
   return GRMHD_OK;
 }
 
-// Workgroups per block of k_pack_load and k_pack_read.
-unsigned pack_chunks(const grmhd_pack* pk) {
-  const unsigned chunks = ((unsigned)pk->max_nz + BLOCK - 1) / BLOCK, most = (1u << 30) / (unsigned)pk->nb;
-  return chunks < most ? chunks : most;
-}
-
 template <int RECON>
 int pack_launch(grmhd_pack* pk, int stage, double dt) {
   if (pk->d_owner) {
@@ -3478,8 +3472,7 @@ int grmhd_pack_set_tiles(grmhd_pack* pk, int n, int t1, int t2, int t3) {
 
 int grmhd_pack_load_prims(grmhd_pack* pk, const double* d_prims) {
   if (!pk || !d_prims) return GRMHD_E_ARG;
-  const unsigned chunks = pack_chunks(pk);
-  k_pack_load<<<(unsigned)pk->nb * chunks, BLOCK, 0, pk->stream>>>(pk->d_views, chunks, d_prims);
+  k_pack_load<<<(unsigned)pk->items[PH_COPY], BLOCK, 0, pk->stream>>>(pk->d_views, pk->nb, pk->d_pre, d_prims);
   return hip_check();
 }
 
@@ -3496,8 +3489,7 @@ int grmhd_pack_step(grmhd_pack* pk, double dt) {
 
 int grmhd_pack_get_prims(grmhd_pack* pk, double* d_out) {
   if (!pk || !d_out) return GRMHD_E_ARG;
-  const unsigned chunks = pack_chunks(pk);
-  k_pack_read<<<(unsigned)pk->nb * chunks, BLOCK, 0, pk->stream>>>(pk->d_views, chunks, d_out);
+  k_pack_read<<<(unsigned)pk->items[PH_COPY], BLOCK, 0, pk->stream>>>(pk->d_views, pk->nb, pk->d_pre, d_out);
   return hip_check();
 }
 

@@ -24,9 +24,9 @@ struct BlockView {
   long off;        // offset (doubles) of the block in the packed prims
 };
 
-enum { PH_FLUX = 0, PH_UPDATE = 1, PH_N = 2 };
+enum { PH_FLUX = 0, PH_UPDATE = 1, PH_COPY = 2, PH_N = 3 };
 
-// Boxes of the two phases of a block (flux boxes per direction).
+// Boxes of a block's flux (per direction) and update phases.
 __host__ __device__ inline Box phase_box(const Dev& g, int ph, int d) {
   if (ph == PH_FLUX) {
     if (d == 1) return Box{0, -1, -1, g.n1 + 1, g.n2 + 2, g.n3 + 2};
@@ -55,8 +55,10 @@ __host__ __device__ inline int x1_items(const BlockView& b) {
   return tiles_of(phase_box(b.g, PH_FLUX, 1), b.t1, b.t2, b.t3);
 }
 
-// Work items of a block in a phase (the flux phase holds all three directions).
+// Work items of a block in a phase (the flux phase holds all three directions;
+// a copy's are runs of BLOCK padded zones).
 __host__ __device__ inline int block_items(const BlockView& b, int ph) {
+  if (ph == PH_COPY) return (int)((b.g.nz + BLOCK - 1) / BLOCK);
   if (ph == PH_FLUX)
     return x1_items(b) + tiles_of(phase_box(b.g, PH_FLUX, 2), b.t1, b.t2, b.t3) +
            tiles_of(phase_box(b.g, PH_FLUX, 3), b.t1, b.t2, b.t3);
@@ -208,31 +210,38 @@ __global__ void __launch_bounds__(BLOCK) k_pack_exchange(const BlockView* __rest
 }
 
 // The caller's packed prims (each block [8][padded], at its offset) into the
-// blocks' states (and the ghosts of their stage buffers), and back.  `chunks`
-// workgroups per block, enough for the largest one's padded zones, one block
-// after the other: dispatched across the blocks in turn they touch the twelve
-// streams of every block at a time (96 blocks: 281 and 179 us so, 171 and 100
-// in order).
-__global__ void __launch_bounds__(BLOCK) k_pack_load(const BlockView* __restrict__ views,
-                                                     unsigned chunks, const double* __restrict__ packed) {
-  const BlockView& b = views[blockIdx.x / chunks];
-  const long nz = b.g.nz;
-  for (long c = blockIdx.x % chunks * (long)BLOCK + threadIdx.x; c < nz; c += chunks * (long)BLOCK) {
-    double p[NVAR];
-#pragma unroll
-    for (int v = 0; v < NVAR; v++) p[v] = packed[b.off + v * nz + c];
-    store8(b.P, nz, c, p);
-    if (ghost_zone(b.g, c)) store8(b.P1, nz, c, p);   // the updates write its interior
-  }
+// blocks' states (and the ghosts of their stage buffers), and back.  A workgroup
+// per item, one block after the other: dispatched across the blocks in turn
+// they touch the twelve streams of every block at a time (96 blocks: 281 and 179
+// us so, 171 and 100 in order).  As many workgroups per block as the largest one
+// needs would leave most of them empty (one 256^3 and 200 8^3 blocks: 2265 and
+// 2209 us, 512 and 477 so).
+__device__ __forceinline__ int copy_zone(int nb, const int* __restrict__ pre, long& c) {
+  const int* p = pre + PH_COPY * (nb + 1);
+  const int blk = find_block(p, nb, (int)blockIdx.x);
+  c = ((int)blockIdx.x - p[blk]) * (long)BLOCK + threadIdx.x;
+  return blk;
 }
-__global__ void __launch_bounds__(BLOCK) k_pack_read(const BlockView* __restrict__ views, unsigned chunks,
-                                                     double* __restrict__ packed) {
-  const BlockView& b = views[blockIdx.x / chunks];
+__global__ void __launch_bounds__(BLOCK) k_pack_load(const BlockView* __restrict__ views, int nb,
+                                                     const int* __restrict__ pre, const double* __restrict__ packed) {
+  long c;
+  const BlockView& b = views[copy_zone(nb, pre, c)];
   const long nz = b.g.nz;
-  for (long c = blockIdx.x % chunks * (long)BLOCK + threadIdx.x; c < nz; c += chunks * (long)BLOCK) {
-    double p[NVAR];
-    load8(b.P, nz, c, p);
+  if (c >= nz) return;
+  double p[NVAR];
 #pragma unroll
-    for (int v = 0; v < NVAR; v++) packed[b.off + v * nz + c] = p[v];
-  }
+  for (int v = 0; v < NVAR; v++) p[v] = packed[b.off + v * nz + c];
+  store8(b.P, nz, c, p);
+  if (ghost_zone(b.g, c)) store8(b.P1, nz, c, p);   // the updates write its interior
+}
+__global__ void __launch_bounds__(BLOCK) k_pack_read(const BlockView* __restrict__ views, int nb,
+                                                     const int* __restrict__ pre, double* __restrict__ packed) {
+  long c;
+  const BlockView& b = views[copy_zone(nb, pre, c)];
+  const long nz = b.g.nz;
+  if (c >= nz) return;
+  double p[NVAR];
+  load8(b.P, nz, c, p);
+#pragma unroll
+  for (int v = 0; v < NVAR; v++) packed[b.off + v * nz + c] = p[v];
 }
