@@ -193,10 +193,11 @@ __device__ int invert_kastaun(const Dev& g, const PointMetric<double>& m, const 
   const double Bsq = m.gcov[sidx(1, 1)] * Bn[0] * Bn[0] + g13 * Bn[0] * Bn[2] + m.gcov[sidx(2, 2)] * Bn[1] * Bn[1] +
                      g13 * Bn[2] * Bn[0] + m.gcov[sidx(3, 3)] * Bn[2] * Bn[2];
   const double Ssq = fmax(QQ + Qn * Qn, 0.0);
-  const double iD = face_rcp(D), D2 = D * D;
+  // (D^2 scaled to order one: it leaves the reciprocal's range long before D does)
+  const double iD = face_rcp(D), DD = fmin(D * D, 0x1.fffffffffffffp1023), s2 = unit_scale(0.5 * DD), D2 = s2 * DD;
   double hD;
   const double D32 = D * face_sqrt(D, hD);
-  const double r2 = quotient(Ssq, D2, face_rcp(D2)), b2 = quotient(Bsq, D, iD), rb = quotient(QB, D32, face_rcp(D32)),
+  const double r2 = quotient(s2 * Ssq, D2, face_rcp(D2)), b2 = quotient(Bsq, D, iD), rb = quotient(QB, D32, face_rcp(D32)),
                q = quotient(-Qn, D, iD) - 1.0;
   const double rb2 = rb * rb, br = b2 * r2 - rb2;
   const double vmax2 = g.vmax2;

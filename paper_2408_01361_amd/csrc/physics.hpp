@@ -650,7 +650,8 @@ __device__ __forceinline__ double speed_root(double x) {
   return x > 0.0 ? s : 0.0;
 }
 // 2^-e with 2^e <= |x| < 2^(e+1): scales a homogeneous expression without
-// rounding (x normal, below 2^1023).
+// rounding (x normal, below 2^1023; 2^1023 for a subnormal x, -inf for an
+// infinite one).
 __device__ __forceinline__ double unit_scale(double x) {
   const unsigned hi = (unsigned)(__builtin_bit_cast(unsigned long long, x) >> 32);
   return __builtin_bit_cast(double, (unsigned long long)(0x7fe00000u - (hi & 0x7ff00000u)) << 32);
