@@ -595,7 +595,7 @@ __device__ __forceinline__ int newton_hydro_group(const Dev& g, Res res, double 
     double rhs[5], dx[5];
 #pragma unroll
     for (int mm = 0; mm < 5; mm++) rhs[mm] = -R[mm];
-    if (!qr_pivot_solve(J, rhs, dx)) return NEWTON_FAILED;
+    if (!qr_pivot_solve(J, x, rhs, dx)) return NEWTON_FAILED;
     double xn[5], Rn[5], rn2 = 0.0;
     bool ok = false;
     auto attempt = [&](double lam) {

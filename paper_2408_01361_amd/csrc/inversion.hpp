@@ -324,7 +324,10 @@ struct LdsMat {
   __device__ __forceinline__ double& operator()(int i, int j) const { return base[(i * 5 + j) * BLOCK]; }
 };
 
-__device__ __forceinline__ bool qr_pivot_solve(const LdsMat& A, double b[5], double y[5]) {
+// TINY: columns may be so small that the square of one's norm is no normal
+// number.
+template <bool TINY>
+__device__ __forceinline__ bool qr_pivot(const LdsMat& A, double b[5], double y[5]) {
 #pragma clang fp contract(off)
   int perm[5] = {0, 1, 2, 3, 4};
   double cn[5];
@@ -370,6 +373,11 @@ __device__ __forceinline__ bool qr_pivot_solve(const LdsMat& A, double b[5], dou
 #pragma unroll
     for (int i = 0; i < 5; i++) v[i] = i < k ? 0.0 : A(i, k);
     v[k] = v[k] - alpha;
+    // (the reflection is the same for any multiple of v)
+    if (TINY) {
+#pragma unroll
+      for (int i = k; i < 5; i++) v[i] = nrm < 0x1p-500 ? 0x1p500 * v[i] : v[i];
+    }
     double vv = 0.0;
 #pragma unroll
     for (int i = k; i < 5; i++) vv += v[i] * v[i];
@@ -418,6 +426,13 @@ __device__ __forceinline__ bool qr_pivot_solve(const LdsMat& A, double b[5], dou
   for (int k = 0; k < 5; k++)
     if (!isfinite(y[k])) return false;
   return true;
+}
+
+// The Newton step from the iterate x: the Jacobian's columns of rho and u are of
+// the order of 1 / rho and 1 / u.
+__device__ __forceinline__ bool qr_pivot_solve(const LdsMat& A, const double x[5], double b[5], double y[5]) {
+  if (x[0] > 0x1p480 || x[1] > 0x1p480) return qr_pivot<true>(A, b, y);
+  return qr_pivot<false>(A, b, y);
 }
 
 // jac: this thread's 25 LDS words for the Jacobian (LdsMat base).
@@ -479,7 +494,7 @@ __device__ __forceinline__ int invert_implicit(const Dev& g, const PointMetric<d
     double rhs[5], dx[5];
 #pragma unroll
     for (int mm = 0; mm < 5; mm++) rhs[mm] = -R[mm];
-    if (!qr_pivot_solve(J, rhs, dx)) return fail();
+    if (!qr_pivot_solve(J, x, rhs, dx)) return fail();
     double lam = 1.0, xn[5], Rn[5], rn2 = 0.0;
     bool ok = false;
     for (int ls = 0; ls <= 8; ls++) {
@@ -569,7 +584,7 @@ __device__ __forceinline__ int newton_hydro(const Dev& g, const double x0[5], Re
     double rhs[5], dx[5];
 #pragma unroll
     for (int mm = 0; mm < 5; mm++) rhs[mm] = -R[mm];
-    if (!qr_pivot_solve(J, rhs, dx)) return NEWTON_FAILED;
+    if (!qr_pivot_solve(J, x, rhs, dx)) return NEWTON_FAILED;
     double lam = 1.0, xn[5], Rn[5], rn2 = 0.0;
     bool ok = false;
     for (int ls = 0; ls <= 8; ls++) {

@@ -28,10 +28,10 @@ def _recover(inverter, k):
 
 
 # Kastaun forms D^2 (exact to a part in 2^52 down to 1e-154, to one in 1e8 at
-# 1e-158).
+# 1e-158), the implicit solver the square of a Jacobian column of order 10^-k.
 @pytest.mark.parametrize("inverter,k,bar", [(1, 0, 1e-12), (1, 150, 1e-12), (1, -150, 1e-12), (1, -155, 1e-12),
-                                            (1, -158, 1e-6), (1, 153, 1e-12), 
-                                            (0, 50, 1e-12), (0, -50, 1e-12)])
+                                            (1, -158, 1e-6), (1, 153, 1e-12), (2, 0, 1e-10), (2, -150, 1e-10), (2, 150, 1e-10),
+                                            (2, 155, 1e-10), (2, 160, 1e-10), (0, 50, 1e-12), (0, -50, 1e-12)])
 def test_scaled_prims_recover(inverter, k, bar):
     n, err = _recover(inverter, k)
     assert n == 0 and err <= bar, (n, err)
