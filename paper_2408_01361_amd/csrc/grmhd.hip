@@ -49,8 +49,9 @@ constexpr int BLOCK = 256;
 constexpr int MAX_PARTIALS = 65536;
 constexpr long LAST_LEVEL_CACHE = 256L << 20;  // bytes
 // Largest padded grid whose updates write their zones' ghost images instead of
-// a ghost fill per stage (32^3 MC, 10 steps: 458 -> 399 us, 48^3 WENO5, 5
-// steps: 514 -> 484, 64^3: no difference any more).
+// a ghost fill per stage (a step of n^3 zones, MC, with the fill and with the
+// images: 24^3 35.6 and 31.0 us, 48^3 58.6 and 53.6, 64^3 107 and 103, 93^3 325
+// and 323).
 constexpr long IMAGE_ZONES = 1000000;
 
 // Waves per SIMD the update kernel is compiled for (its register budget):
@@ -1560,15 +1561,17 @@ __device__ __forceinline__ void update_zone(const Dev& g, const double* __restri
 
 // The dt reduction's final pass inside the kernel that needs its dt, for few
 // partials (a launch less per step): every wavefront takes their maximum, the
-// first one leaves the result where k_reduce_final would.  Not more than
-// CFL_IN_UPDATE: every workgroup reads them all.
+// first one leaves the result where k_reduce_final would.  Every workgroup reads
+// them all, so the cost grows with the square of their number (step_cfl of
+// cubes, MC, a launch of its own against here: 72 partials 33.9 and 31.4 us, 432
+// 56.2 and 55.5, 560 65.6 and 65.4, 616 68.5 and 69.1, 1024 105.7 and 110.5).
 struct CflStep {
   const double* part;   // n > 0 partials, or n = 0: dt comes from elsewhere
   int n;
   double cfl;
   double* result;
 };
-constexpr int CFL_IN_UPDATE = 1024;
+constexpr int CFL_IN_UPDATE = 576;
 __device__ __forceinline__ double cfl_step(const CflStep& cs) {
   double mx = 0.0;
   for (int q = (int)(threadIdx.x & 63u); q < cs.n; q += 64) mx = fmax(mx, cs.part[q]);

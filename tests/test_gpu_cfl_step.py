@@ -34,18 +34,21 @@ def _same(shape, nsteps, **kw):
 @pytest.mark.parametrize("opts", [dict(), dict(precision=1), dict(floors=True), dict(floors=True, fofc=True), dict(inverter=2)],
                          ids=["plain", "mixed", "floors", "fofc", "implicit"])
 @pytest.mark.parametrize("ct", [1, 2])
-@pytest.mark.parametrize("shape", [(24, 22, 7), (64, 64, 64)], ids=["small", "largest"])
+@pytest.mark.parametrize("shape", [(24, 22, 7), (64, 32, 72), (64, 64, 64)], ids=["small", "largest", "above"])
 def test_face_ct_advances_its_faces_with_the_steps_dt(shape, ct, opts):
-    """64^3 has 1024 workgroups of partials, the most that an update reduces."""
+    """64x32x72 has 576 workgroups of partials, the most that an update
+    reduces."""
     _same(shape, 3, recon=1, ct=ct, **opts)
 
 
 @pytest.mark.parametrize("opts", [dict(recon=0), dict(recon=1), dict(recon=1, precision=1)], ids=["mc", "weno5", "mixed"])
 @pytest.mark.parametrize("integrator", [0, 1, 2, 3])
-@pytest.mark.parametrize("shape", [(60, 61, 58), (64, 64, 64)], ids=["resident_and_late", "largest"])
+@pytest.mark.parametrize("shape", [(64, 32, 72), (61, 33, 73), (60, 61, 58), (64, 64, 64)],
+                         ids=["largest", "above", "resident_and_late", "1024"])
 def test_every_integrator_steps_with_one_dt(shape, integrator, opts):
-    """960 and 1024 workgroups of an update, more than are resident at a
-    time: the last ones start when the first have left their results."""
+    """576 workgroups of partials, the most that an update reduces; 640; and
+    960 and 1024, more workgroups than are resident at a time: the last ones
+    start when the first have left their results."""
     _same(shape, 4, integrator=integrator, **opts)
 
 
