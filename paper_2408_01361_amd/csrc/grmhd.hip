@@ -2001,6 +2001,8 @@ struct grmhd_ctx {
   bool rate_ready = false;  // pdt describes the current state (rate_n partials)
   bool ghosts_valid = false;  // the ghost zones of P hold the boundary conditions of its interior
   bool plane_valid = false;   // those of plane 0 do (flat grids)
+  unsigned long long valid_in = 0;  // the stream capture in which they do, 0: outside of any
+  bool captured = false;      // some call was captured: its replays are not seen here
   int rate_n = 0;
   // partials the step's first update reduces itself (step_cfl on small grids)
   const double* cfl_part = nullptr;
@@ -2205,13 +2207,30 @@ int fill_ghosts(grmhd_ctx* c, double* P, double* const* ph = nullptr) {
   return launch(c, T_BC, k_bc, blocks_for(ghost_count(g) - (g.flat ? 6L * g.plane : 0)), g, P);
 }
 
+// The capture that the context's stream is in, 0 for none.
+unsigned long long capture_of(grmhd_ctx* c) {
+  hipStreamCaptureStatus status;
+  unsigned long long id = 0;
+  if (!c->stream || hipStreamGetCaptureInfo(c->stream, &status, &id) != hipSuccess ||
+      status != hipStreamCaptureStatusActive)
+    return 0;
+  c->captured = true;
+  return id;
+}
+
 // Ghost zones (and faces) of the state (of its plane 0 within a flat grid's
 // step), filled unless they already hold its boundary conditions (filled
-// since the state last changed).
+// since the state last changed).  A captured call counts on those that the same
+// capture left, and one outside on none once something has been captured: a
+// graph may be replayed on another state, and after other calls.
 int ensure_ghosts(grmhd_ctx* c) {
-  if (c->ghosts_valid || (c->cur->flat && c->plane_valid)) return GRMHD_OK;
+  const unsigned long long in = capture_of(c);
+  const bool known = in == c->valid_in && (in != 0 || !c->captured);
+  if (known && (c->ghosts_valid || (c->cur->flat && c->plane_valid))) return GRMHD_OK;
+  if (!known) c->ghosts_valid = c->plane_valid = false;
   int rc = fill_ghosts(c, c->P, c->phi);
   if (rc == GRMHD_OK) (c->cur->flat ? c->plane_valid : c->ghosts_valid) = true;
+  c->valid_in = in;
   return rc;
 }
 
@@ -2821,6 +2840,7 @@ int grmhd_create(grmhd_ctx** out, const grmhd_grid* grid, const grmhd_metric* me
 
 int grmhd_load_prims(grmhd_ctx* c, const double* d_prims) {
   if (!c || !d_prims) return GRMHD_E_ARG;
+  capture_of(c);
   c->rate_ready = false;
   c->ghosts_valid = c->plane_valid = false;
   const Dev& g = c->flat;
@@ -2852,6 +2872,7 @@ int grmhd_get_extended(grmhd_ctx* c, double* d_extra) {
 int grmhd_load_faces(grmhd_ctx* c, const double* d_faces) {
   if (!c || !d_faces) return GRMHD_E_ARG;
   if (c->params.ct == GRMHD_CT_FLUX) return GRMHD_E_STATE;
+  capture_of(c);
   const size_t bytes = sizeof(double) * c->dev.nz;
   for (int d = 0; d < 3; d++) {
     // the stage-1 faces carry the same (frozen) ghosts
