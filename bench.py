@@ -284,7 +284,7 @@ def extras(torch, gr, np, args):
     del ctxs
     out["batched"] = {
         "workload": "320 frozen-ghost blocks of the 128^3 torus, n in {16,32,64} (60/30/10 %, seed 7), "
-                    "WENO5, FP64, three launches per RK2 stage (fluxes, EMFs, update) over all blocks, "
+                    "WENO5, FP64, two launches per RK2 stage (fluxes; EMFs and update) over all blocks, "
                     "10 steps at fixed dt",
         "interior_zones": zones, "zone_cycles_per_s": zones * steps / tp,
         "per_block_zone_cycles_per_s": zones * steps / tb,
@@ -358,7 +358,7 @@ def tiling_extra(torch, gr, np, gam, dt, steps, args):
     zones = 128 ** 3
     counts = ", ".join(f"{sum(1 for b in blocks if b['n'] == m)} x {m}^3" for m in (16, 32, 64))
     return {"workload": f"128^3 torus tiled by {len(blocks)} blocks ({counts}), WENO5, FP64, "
-                        f"ghost exchange + three launches per stage over all blocks, {steps} steps at fixed dt",
+                        f"ghost exchange + two launches per stage over all blocks, {steps} steps at fixed dt",
             "zone_cycles_per_s": zones * steps / tp,
             "frozen_ghosts_zone_cycles_per_s": zones * steps / tf,
             "single_grid_zone_cycles_per_s": zones * steps / ts,

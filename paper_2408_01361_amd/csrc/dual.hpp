@@ -1,7 +1,8 @@
 // Forward-mode dual number (value and one directional derivative): the
 // derivatives of the per-point physics that the hand-written adjoint's
-// reverse sweeps are tested against.  Comparisons act on the value, so min/max and limiter branches
-// select the derivative of the branch taken (a subgradient at ties).
+// reverse sweeps are tested against.  Comparisons act on the value, so min/max
+// and limiter branches select the derivative of the branch taken (a
+// subgradient at ties).
 #pragma once
 
 #include <hip/hip_runtime.h>

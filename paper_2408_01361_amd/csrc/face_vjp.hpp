@@ -188,7 +188,8 @@ __device__ __forceinline__ void rows_rev(const double q[NVAR], const PointMetric
 }
 
 // One face state: flux along D (adjoint Fb), conserved variables (Ub) and
-// the two fast speeds, the larger (cpb) and the smaller root (cmb).
+// the two fast speeds, the larger (cpb) and the smaller root (cmb).  (For the
+// tests; the face kernel takes face_state_vjp below.)
 template <int D>
 __device__ __forceinline__ void state_vjp(const double q[NVAR], const PointMetric<double>& m, double gam,
                                           const double Fb[NVAR], const double Ub[NVAR], double cpb,
@@ -263,6 +264,7 @@ __device__ __forceinline__ void zone_terms_vjp(const double q[NVAR], const Point
 // The same from the connection, Gamma^l_{mn} at l * 10 + sidx(m, n), for
 // sources of all four components (Sb; those along t and x3 vanish with the
 // metric's derivatives): d_nu g_kl = g_km Gamma^m_{nu l} + g_lm Gamma^m_{nu k}.
+// (For the tests, which have the connection's dual-number products.)
 __device__ __forceinline__ void zone_vjp(const double q[NVAR], const PointMetric<double>& m, double gam,
                                          const double cn[40], const double Sb[4], const double* Ub,
                                          double qb[NVAR], double& gamb) {

@@ -1,20 +1,24 @@
 // HIP kernels (gfx950) and the C ABI of the HARM ideal-GRMHD step.
 //
 // Per stage the step runs, on one stream:
-//   bc      ghost zones from the stage's prims (index remap per axis)
+//   bc      ghost zones from the stage's prims (index remap per axis); on small
+//           grids the update before has stored them with its zones
 //   flux    per face, for the x1, x2 and x3 faces in one launch: reconstruct
 //           8 prims left/right, evaluate the face state, flux, conserved
 //           variables and characteristic speeds for both sides, and form the
 //           local Lax-Friedrichs flux (the paper keeps speeds, P->U and the
 //           Riemann solve in one kernel, Solvers section)
-//   update  per zone: flux divergence (the field's from the Flux-CT edge
-//           EMFs, averages of transverse B fluxes formed in place),
-//           geometric source, SSPRK2 combination and the 1D_W inversion;
-//           stage 2 also reduces the next step's CFL rate per workgroup
-// with every intermediate resident in the caller's HBM workspace, and a
-// single-workgroup pass over the CFL partials before the step when its dt
-// is taken on the device.  Layouts are variable-major and x1-fastest, so
-// each wavefront's loads and stores of one variable are contiguous.
+//   emf     where the fluxes of a launch exceed the last-level cache: the
+//           Flux-CT edge EMFs, averages of transverse B fluxes
+//   update  per zone: flux divergence (the field's from the edge EMFs, formed
+//           in place where there is no EMF pass), geometric source, SSPRK2
+//           combination and the 1D_W inversion; stage 2 also reduces the next
+//           step's CFL rate per workgroup
+// with every intermediate resident in the caller's HBM workspace.  When the
+// step's dt is taken on the device, the CFL partials are reduced before it: by
+// a single-workgroup launch, or, if there are few, by the first update.
+// Layouts hold variables in pairs, pair by pair and x1-fastest, so each
+// wavefront's loads and stores of one pair are contiguous.
 //
 // Options selected per context add passes to a stage: the Kastaun recovery
 // replaces 1D_W inside the update; the implicit solver's recovery runs as a
@@ -493,7 +497,7 @@ __device__ __forceinline__ bool plane_index(int m1, int lo1, int m2, int lo2, un
 #endif
 constexpr int TILE_FACES = 4 * TILE_STEPS - 1;
 constexpr int TILE_ROWS = 9;   // right-edge rows in LDS: two each of the first three wavefronts, three of the last
-constexpr long FLUX_TURN_BYTES = 4L << 20;  // (the L2 of an XCD)  // (the L2 of an XCD)
+constexpr long FLUX_TURN_BYTES = 4L << 20;  // (the L2 of an XCD)
 
 // Work order of the flux launch.  Each direction has a list of workgroups
 // that goes through the grid in blocks of kb x3 planes and, inside a block,
@@ -1310,7 +1314,7 @@ __device__ __forceinline__ double zone_rate(const Dev& g, const double p[NVAR],
 }
 
 // The same bound, every operation rounded in the order written: Extended
-// GRMHD's steps (see recon_ordered for the reason).
+// GRMHD's steps (wv::weno5 there has the reason).
 __device__ __forceinline__ double zone_rate_ordered(const Dev& g, const double p[NVAR],
                                                     const PointMetric<double>& m) {
   Fluid<double> f;
@@ -1332,12 +1336,6 @@ __device__ __forceinline__ double zone_rate_ordered(const Dev& g, const double p
 }
 
 // ----------------------------------------------------------------- update --
-
-__device__ __forceinline__ void load_conn(const double* __restrict__ conn, long plane, long q,
-                                          double cn[40]) {
-#pragma unroll
-  for (int f = 0; f < 40; f++) cn[f] = conn[f * plane + q];
-}
 
 // One stage for every interior zone.  STAGE 1: V = (Un + U1)/2 with
 // Un = U(Pin), U1 = Un + dt L(Pin); STAGE 2: U = V + dt L(Pin)/2.  Then

@@ -221,10 +221,12 @@ __device__ __forceinline__ double hw_rsqrt(double x) {
 }
 
 // FP64 quotient and square root without the scaling and the special cases of
-// the correctly rounded ones: the same reciprocal, Newton and residual steps,
-// so the same bits wherever no operand or intermediate is subnormal, infinite
-// or NaN (a quotient by zero or infinity is NaN here).  A reciprocal shared by
-// several quotients is formed once.
+// the correctly rounded ones: Newton's iteration for the reciprocal and
+// Goldschmidt's for the root, from the hardware estimates, each closed by
+// Markstein's correction with the residual in a fused multiply-add.  The same
+// bits as the correctly rounded ones wherever no operand or intermediate is
+// subnormal, infinite or NaN (a quotient by zero or infinity is NaN here).  A
+// reciprocal shared by several quotients is formed once.
 __device__ __forceinline__ double plain_rcp(double d) {
   double r = __builtin_amdgcn_rcp(d);
   r = fma(fma(-d, r, 1.0), r, r);
@@ -295,9 +297,6 @@ using f64::ppm_edges;
 using f32::ppm_edges;
 using f64::ppmx_edges;
 using f32::ppmx_edges;
-using f64::llf;
-using f32::llf;
-using fdual::llf;
 
 // WENO5 (Jiang-Shu weights d_k / (eps + beta_k)^2, d = (1, 6, 3)/10) from
 // point values a..e of zones c-2..c+2: the value at the right edge of zone c.
@@ -584,7 +583,8 @@ __device__ __forceinline__ void mc_slope_grad(double l, double c, double r, doub
   gc = pick_c ? 0.0 : (pick_r ? -kr : kl);
   gr = pick_c ? kc : (pick_r ? kr : 0.0);
 }
-// mc_left(l, c, r) = c + slope/2 and mc_right(l, c, r) = c - slope/2.
+// mc_left(l, c, r) = c + slope/2 and mc_right(l, c, r) = c - slope/2 (tests
+// check mc_slope_grad through them).
 __device__ __forceinline__ void mc_left_grad(double l, double c, double r, double& g0, double& g1, double& g2) {
   double sl, sc, sr;
   mc_slope_grad(l, c, r, sl, sc, sr);

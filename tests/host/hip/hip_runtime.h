@@ -1,9 +1,10 @@
-// Host stand-in for <hip/hip_runtime.h>, for the sanitizer test only: with
-// it the per-point device code of the library (geometry, physics and the
-// primitive-variable recoveries) compiles as plain C++ on the host.  The
-// function qualifiers become nothing and the hardware reciprocals become
-// divisions (used only in the reconstruction and face code, which the test
-// does not call).
+// Host stand-in for <hip/hip_runtime.h>: with it the per-point device code of
+// the library (geometry, physics, the primitive-variable recoveries and the
+// adjoint's sweeps) compiles as plain C++ on the host.  The function
+// qualifiers become nothing and the hardware reciprocals become divisions,
+// better estimates than the hardware's: the refinement steps that follow them
+// run as on the GPU, but from a start that is already rounded, so what they
+// correct there is not tested here.
 #pragma once
 #include <math.h>
 
