@@ -887,11 +887,12 @@ __device__ __forceinline__ void zone_source(const ZoneState& z, const PointMetri
 }
 
 // Larger magnitudes of the fast speeds along x1, x2 and x3 (fast_speed above;
-// the quadratics' A, scale and enthalpy terms are common to the three).
+// the quadratics' A, scale and enthalpy terms are common to the three).  An
+// infinite density counts as a large one: the speeds are the flow's.
 __device__ __forceinline__ void zone_speeds(double rho, double uu, const ZoneState& z, const PointMetric<double>& m,
                                             double gam, double c[3]) {
   const double n0 = fma(gam, z.pg, z.bsq);
-  const double m0 = fma(gam * (2.0 - gam), uu, rho);
+  const double m0 = fma(gam * (2.0 - gam), uu, rho == (double)INFINITY ? 0x1p1020 : rho);
   const double sc = unit_scale(n0 + m0);
   const double n = n0 * sc, mm = m0 * sc;
   const double mut = mm * z.ut;

@@ -3,6 +3,7 @@ dt the host reads (dt, then step): one reduction, so the same dt and the same
 state bit for bit, whatever launches read the dt and wherever its final pass
 runs."""
 
+import numpy as np
 import pytest
 
 from workloads import fm_torus
@@ -79,3 +80,31 @@ def test_no_cfl_step_without_a_signal_speed(precision):
     cs = (GAM * (GAM - 1.0) * u / (1.0 + GAM * u)) ** 0.5
     assert s.dt() == pytest.approx(0.9 / (cs * (9 + 8 + 7)), rel=1e-14)
     assert gr.cfl_dt_noalloc(grid, GAM, P) == s.dt()
+
+
+@pytest.mark.parametrize("flat", [True, False])
+def test_infinite_density_is_cold(flat):
+    """A zone of infinite density (and finite energy and field) has no sound or
+    Alfven speed: the oracle's rate of it is its flow's, and the CFL step that
+    of the other zones."""
+    import torch
+    import oracle
+    from paper_2408_01361_amd import grmhd as gr
+    from workloads import GridSpec
+    if flat:
+        grid, gam = GridSpec(9, 8, 7), GAM
+        rng = np.random.default_rng(2)
+        P = np.array([1, .5, .05, .02, .01, .5, .3, .2])[:, None, None, None] * (
+            1 + 0.1 * rng.uniform(-1, 1, (8, 13, 14, 15)))
+    else:
+        (grid, P), gam = fm_torus(16, 12, 4)[0:2], 13 / 9
+    P[0, 5, 8, 9] = np.inf
+    want = oracle.estimate_dt(oracle.cfg(grid, gam=gam), P)
+    assert np.isfinite(want) and want > 0.0
+    s = gr.Grmhd(grid, gam)
+    s.load(torch.from_numpy(P).cuda())
+    assert s.dt() == pytest.approx(want, rel=1e-13)
+    P[0, 5, 8, 9] = np.nan
+    s.load(torch.from_numpy(P).cuda())
+    with pytest.raises(gr.GrmhdError):
+        s.dt()
