@@ -196,9 +196,9 @@ __device__ int invert_kastaun(const Dev& g, const PointMetric<double>& m, const 
   // (D^2 scaled to order one: it leaves the reciprocal's range long before D does)
   const double iD = face_rcp(D), DD = fmin(D * D, 0x1.fffffffffffffp1023), s2 = unit_scale(0.5 * DD), D2 = s2 * DD;
   double hD;
-  const double D32 = D * face_sqrt(D, hD);
-  const double r2 = quotient(s2 * Ssq, D2, face_rcp(D2)), b2 = quotient(Bsq, D, iD), rb = quotient(QB, D32, face_rcp(D32)),
-               q = quotient(-Qn, D, iD) - 1.0;
+  const double D32 = D * face_sqrt(D, hD);   // (past FP64's range from D = 3e205 on)
+  const double r2 = quotient(s2 * Ssq, D2, face_rcp(D2)), b2 = quotient(Bsq, D, iD),
+               rb = isfinite(D32) ? quotient(QB, D32, face_rcp(D32)) : 0.0, q = quotient(-Qn, D, iD) - 1.0;
   const double rb2 = rb * rb, br = b2 * r2 - rb2;
   const double vmax2 = g.vmax2;
   const int maxit = 4 * g.maxit;

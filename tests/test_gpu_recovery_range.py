@@ -40,3 +40,24 @@ def test_scaled_prims_recover(inverter, k, bar):
 @pytest.mark.parametrize("k", [-163, -170])
 def test_kastaun_refuses_where_the_square_vanishes(k):
     assert _recover(1, k)[0] == 8 * 8 * 6
+
+
+@pytest.mark.parametrize("rho", [1e200, 1e206, 1e250, 1e300])
+def test_kastaun_recovers_a_dense_zone(rho):
+    """Past the range of D^2 the squared momentum counts as zero, past that of
+    D^3/2 the momentum along the field too: the zone still recovers, its density
+    to the Lorentz factor that is lost (1.03 here), its field exactly."""
+    import torch
+    from paper_2408_01361_amd import grmhd as gr
+    grid = GridSpec(8, 8, 6)
+    rng = np.random.default_rng(4)
+    P = np.array([1.0, 1.0, 0.2, 0.1, 0.05, 1.0, 0.3, 0.2])[:, None, None, None] * (
+        1.0 + 0.1 * rng.uniform(-1, 1, (8, 12, 14, 14)))
+    P[0, 6, 7, 8] = rho
+    P = torch.from_numpy(P).cuda()
+    s = gr.Grmhd(grid, 4.0 / 3.0, inverter=1)
+    out, n, _ = s.cons_to_prims(s.prims_to_cons(P), 1.01 * P)
+    got, want = out.cpu().numpy()[:, 6, 7, 8], P.cpu().numpy()[:, 6, 7, 8]
+    gamma = np.sqrt(1.0 + (want[2:5] ** 2).sum())
+    assert n == 0 and np.array_equal(got[5:], want[5:])
+    assert abs(got[0] / (gamma * want[0]) - 1.0) <= 1e-13 and np.isfinite(got).all()
